@@ -1,0 +1,218 @@
+"""The workloads the inference library is timed on: what an inference thread or a learner has it do.
+
+A case is a plain dict:
+
+  net     "tiny"      small feed-forward Atari-shaped policy in fp32, Gumbel-max
+          "atari"     R2D2 dueling-Q network, LSTM 512, greedy + optional epsilon-greedy
+          "dmlab"     deep ResNet + LSTM 256 policy on 72x96x3 frames, Gumbel-max
+          "football"  deep ResNet policy on 16 minimap planes, no core, Gumbel-max
+  obs_h, obs_w, obs_c  frame size (Atari: 1 or 4 stacked frames; Football: the three minimap sizes)
+  width   filter multiple of the ResNet sections (1, 2 or 4)
+  call    "step"      one batched step on frames that are in HBM
+          "loop"      `steps` successive steps of the same actors, the recurrent state carried from one to the next
+          "unroll"    `steps` time steps over stored trajectories in one call
+          "batcher"   one round of the host batching front-end: frames, rewards and flags in host memory in,
+                      actions in host memory out
+  rows    frames per step (actors, or trajectories)
+  steps   successive time steps ("loop", "unroll"), else 1
+  flags   episode flags are given (and, with the Atari network, epsilon-greedy exploration)
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_1910_06591_amd import seedinf, workloads as wl
+
+BASE = {"tiny": "C1", "atari": "C2", "dmlab": "C3", "football": "C4"}
+
+
+def listed():
+    def case(name, net, call, rows, steps=1, flags=False, width=1, size=None):
+        base = wl.CONFIGS[BASE[net]]
+        h, w, c = size or (base["obs_h"], base["obs_w"], base["obs_c"])
+        return dict(name=name, net=net, obs_h=h, obs_w=w, obs_c=c, width=width, call=call, rows=rows, steps=steps, flags=flags)
+
+    return [
+        # the smallest call: a handful of actors on a small fp32 policy; launches and latency
+        case("tiny_fp32_b8", "tiny", "step", 8),
+        # one small group of actors served step after step: every step waits for the state of the one before
+        case("dmlab_loop_8x64", "dmlab", "loop", 64, steps=8),
+        # the Atari agent at the batch of one inference thread
+        case("atari_b256", "atari", "step", 256),
+        # the Atari agent on a large, ragged batch of training actors: episode ends and epsilon-greedy exploration
+        case("atari_b3001_flags", "atari", "step", 3001, flags=True),
+        # the DeepMind Lab agent on an ordinary, ragged batch with episode flags
+        case("dmlab_b1000_flags", "dmlab", "step", 1000, flags=True),
+        # the DeepMind Lab agent on the largest batch one learner core serves (the benchmark's workload)
+        case("dmlab_b4096", "dmlab", "step", 4096),
+        # Football: feed-forward, sixteen sparse planes, the frames five times as large
+        case("football_b2048", "football", "step", 2048),
+        # Football's large minimap
+        case("football_map144_b1024", "football", "step", 1024, size=(108, 144, 16)),
+        # the larger models of the model-size study
+        case("dmlab_x2_b1024", "dmlab", "step", 1024, width=2),
+        case("dmlab_x4_b1024", "dmlab", "step", 1024, width=4),
+        # the learner's forward pass over a batch of stored trajectories
+        case("dmlab_unroll_32x128", "dmlab", "unroll", 128, steps=32, flags=True),
+        # actors' calls gathered on the host
+        case("dmlab_batcher_b512", "dmlab", "batcher", 512, flags=True),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["tiny", "loop", "atari", "atari", "dmlab", "dmlab", "football", "football_map", "wide", "unroll", "batcher"])
+    c = dict(net="dmlab", width=1, call="step", steps=1, flags=False)
+    if kind == "tiny":
+        c.update(net="tiny", rows=_log(rng, 1, 64))
+    elif kind == "loop":
+        c.update(net=rng.choice(["dmlab", "atari"]), call="loop", rows=_log(rng, 16, 256))
+        c["steps"] = max(4, -(-512 // c["rows"]))
+    elif kind == "atari":
+        c.update(net="atari", rows=_log(rng, 200, 4096), flags=rng.random() < 0.5)
+    elif kind == "dmlab":
+        c.update(rows=_log(rng, 200, 8192), flags=rng.random() < 0.5)
+    elif kind in ("football", "football_map"):
+        c.update(net="football", rows=_log(rng, 200, 2048))
+    elif kind == "wide":
+        c.update(width=rng.choice([2, 4]), rows=_log(rng, 128, 1024), flags=rng.random() < 0.5)
+    elif kind == "unroll":
+        c.update(net=rng.choice(["dmlab", "dmlab", "atari"]), call="unroll", steps=rng.randint(8, 80), flags=True)
+        c["rows"] = _log(rng, 16, 4096 // c["steps"])
+    else:
+        c.update(net=rng.choice(["dmlab", "atari"]), call="batcher", rows=_log(rng, 200, 1024), flags=True)
+    base = wl.CONFIGS[BASE[c["net"]]]
+    c.update(obs_h=base["obs_h"], obs_w=base["obs_w"], obs_c=base["obs_c"])
+    if kind == "atari" and rng.random() < 0.3:
+        c["obs_c"] = 1
+    if kind == "football_map":
+        c["obs_h"], c["obs_w"] = rng.choice([(90, 120), (108, 144)])
+    return c
+
+
+def _cfg(case):
+    base = wl.CONFIGS[BASE[case["net"]]]
+    cfg = dict(base, obs_h=case["obs_h"], obs_w=case["obs_w"], obs_c=case["obs_c"])
+    if case["width"] != 1:
+        cfg["sections"] = [case["width"] * ch for ch in base["sections"]]
+    return cfg
+
+
+def _frames(cfg, n, gen):
+    """[n, H, W, C] uint8 on the GPU with the value structure of the workload generator's frames."""
+    H, W, C = cfg["obs_h"], cfg["obs_w"], cfg["obs_c"]
+    dev, kind = gen.device, cfg["obs_kind"]
+    if kind == "uniform":
+        return torch.randint(0, 256, (n, H, W, C), dtype=torch.uint8, device=dev, generator=gen)
+    if kind == "sparse":
+        out = torch.empty(n, H, W, C, dtype=torch.uint8, device=dev)
+        for part in out.split(256):
+            part.copy_((torch.rand(part.shape, device=dev, generator=gen) < 0.01).to(torch.uint8) * 255)
+        return out
+    # blobs: six moving Gaussian spots per row over a little noise, one position per stacked frame
+    yy = torch.arange(H, device=dev, dtype=torch.float32).view(1, H, 1, 1)
+    xx = torch.arange(W, device=dev, dtype=torch.float32).view(1, 1, W, 1)
+    step = torch.arange(C, device=dev, dtype=torch.float32).view(1, 1, 1, C)
+    out = torch.empty(n, H, W, C, dtype=torch.uint8, device=dev)
+    for part in out.split(512):
+        m = part.shape[0]
+        img = torch.randint(0, 16, part.shape, device=dev, generator=gen).float()
+        for _ in range(6):
+            u = torch.rand(6, m, 1, 1, 1, device=dev, generator=gen)
+            dy, dx = (u[4] * 5).floor() - 2, (u[5] * 5).floor() - 2
+            sigma, amp = 3 + 9 * u[2], 64 + 191 * u[3]
+            img += amp * torch.exp(-((yy - u[0] * H - step * dy) ** 2 + (xx - u[1] * W - step * dx) ** 2) / (2 * sigma ** 2))
+        part.copy_(img.round_().clamp_(0, 255))
+    return out
+
+
+def prepare(case, seed):
+    cfg = _cfg(case)
+    n, T, call = case["rows"], case["steps"], case["call"]
+    A, Hn = cfg["num_actions"], cfg["lstm_units"]
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    rng = np.random.default_rng(seed)
+    net = seedinf.SeedInfer(seedinf.make_arch(cfg, max_batch=n * T if call == "unroll" else n), wl.make_weights(cfg, seed=seed))
+    state = dict(case=case, net=net)
+
+    if call == "batcher":
+        dones = (rng.random(n) < 0.02).astype(np.uint8)
+        args = dict(uniforms=None, epsilon=None, explore_uniforms=None)
+        if cfg["select"] == 1:
+            args["uniforms"] = rng.uniform(1e-7, 1 - 6e-8, (n, A)).astype(np.float32)
+        else:
+            args.update(epsilon=wl.epsilon_schedule(n), explore_uniforms=rng.random((n, 2), dtype=np.float32))
+        state.update(batcher=seedinf.Batcher(net, n), actors=rng.permutation(n).astype(np.int32), frames=_frames(cfg, n, gen).cpu().numpy(),
+                     rewards=rng.standard_normal(n).astype(np.float32), dones=dones, args=args)
+        return state
+
+    # time-major inputs of all steps; a single step is the first of them
+    rand = lambda *shape: torch.rand(*shape, device="cuda", generator=gen)  # noqa: E731
+    x = dict(obs=_frames(cfg, T * n, gen).view(T, n, cfg["obs_h"], cfg["obs_w"], cfg["obs_c"]))
+    if Hn:
+        x["prev_action"] = torch.randint(0, A, (T, n), dtype=torch.int32, device="cuda", generator=gen)
+        x["prev_reward"] = torch.randn(T, n, device="cuda", generator=gen)
+        state["h"], state["c"] = (0.5 * torch.randn(n, Hn, device="cuda", generator=gen) for _ in range(2))
+        if case["flags"]:
+            x["done"] = (rand(T, n) < 0.02).to(torch.uint8)
+    if cfg["select"] == 1:
+        x["uniforms"] = rand(T, n, A).clamp_(1e-7, 1 - 6e-8)
+    elif case["flags"] and call == "step":
+        x["epsilon"] = torch.from_numpy(wl.epsilon_schedule(n)).cuda().view(T, n)
+        x["explore_uniforms"] = rand(T, n, 2)
+    if call == "unroll":
+        state["inputs"] = x
+        return state
+    state["inputs"] = [{k: v[t] for k, v in x.items()} for t in range(T)]
+    # the buffers such a program keeps: the outputs of every step, a step's state being the next one's input
+    out = dict(action=torch.empty(T, n, dtype=torch.int32, device="cuda"), logits=torch.empty(T, n, A, device="cuda"),
+               value=torch.empty(T, n, device="cuda"), probs=torch.empty(T, n, A, device="cuda"))
+    if Hn:
+        out.update(h=torch.empty(T, n, Hn, device="cuda"), c=torch.empty(T, n, Hn, device="cuda"))
+    state["outputs"] = out
+    state["out"] = [{k: v[t] for k, v in out.items()} for t in range(T)]
+    return state
+
+
+def run(state):
+    net, call = state["net"], state["case"]["call"]
+    if call == "batcher":
+        b = state["batcher"]
+        b.add_many(state["actors"], state["frames"], state["rewards"], state["dones"])
+        return b.wait(b.submit(**state["args"]))
+    if call == "unroll":
+        return net.unroll(h0=state["h"], c0=state["c"], **state["inputs"])
+    h, c = state.get("h"), state.get("c")
+    for x, out in zip(state["inputs"], state["out"]):
+        net.step(h_in=h, c_in=c, out=out, **x)
+        h, c = out.get("h"), out.get("c")
+    return state["outputs"]
+
+
+def work(case):
+    """Bytes: the frames and the other inputs of every row, the outputs, the recurrent state in and out once per
+    call (once per step in a loop, whose caller holds every step's state) and every weight once per call or step,
+    two bytes each in bf16.  Flops: two per multiply-accumulate of the network, without any padding."""
+    cfg = _cfg(case)
+    rows = case["rows"] * case["steps"]
+    per_row = wl.hbm_bytes_per_frame(cfg)
+    state = 16 * cfg["lstm_units"]                  # h and c, in and out, fp32
+    calls = case["steps"] if case["call"] == "loop" else 1
+    total = rows * (per_row - state) + calls * case["rows"] * state
+    total += calls * wl.weight_count(cfg) * (2 if cfg["precision"] == "bf16" else 4)
+    return {"bytes": total, "flops": 2.0 * rows * wl.macs_per_frame(cfg)}
+
+
+def tolerance(case):
+    """fp32 (sums in another order): the library against the oracle's sums in double differs by up to 4e-7 (norm) and
+    1e-6 (largest); a drawn batch may be a single row, whose value can be small.  bf16 (activations between the
+    layers rounded at other places; weights are bf16-representable, accumulation is fp32): the bf16 path against the
+    fp32 path differs by 2e-3 .. 8e-3 (norm), 2.6e-2 where a network's values are close to zero, and by up to 8e-2
+    (largest); an action may differ where the two best scores are within that error."""
+    if _cfg(case)["precision"] == "fp32":
+        return {"rel": 1e-5, "max": 4e-5, "differ": 0.01}
+    return {"rel": 2e-2, "max": 0.3, "differ": 0.01}
