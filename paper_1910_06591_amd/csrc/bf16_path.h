@@ -20,6 +20,7 @@
 #include "resnet_firstpool.h"
 #include "resnet_convpool.h"
 #include "resnet_convtile.h"
+#include "resnet_strip.h"
 
 namespace seedinf {
 
@@ -531,6 +532,12 @@ inline seed_status_t bf16_create(const Plan& p, const float* d_w, Bf16State** ou
         set((const void*)conv_pool_kernel<64, 64>, CP_LDS_MAX);
         set((const void*)conv_pool_kernel<64, 128>, CP_LDS_MAX);
         set((const void*)conv_pool_kernel<128, 128>, CP_LDS_MAX);
+        set((const void*)strip_block_kernel<16, true>, RS_LDS_MAX); set((const void*)strip_block_kernel<16, false>, RS_LDS_MAX);
+        set((const void*)strip_block_kernel<32, true>, RS_LDS_MAX); set((const void*)strip_block_kernel<32, false>, RS_LDS_MAX);
+        set((const void*)strip_block_kernel<64, true>, RS_LDS_MAX); set((const void*)strip_block_kernel<64, false>, RS_LDS_MAX);
+        set((const void*)strip_block_kernel<128, true>, RS_LDS_MAX); set((const void*)strip_block_kernel<128, false>, RS_LDS_MAX);
+        set((const void*)strip_pool_kernel<16>, RS_LDS_MAX); set((const void*)strip_pool_kernel<32>, RS_LDS_MAX);
+        set((const void*)strip_pool_kernel<64>, RS_LDS_MAX); set((const void*)strip_pool_kernel<128>, RS_LDS_MAX);
         set((const void*)conv_tile_kernel<128, true>, CT_LDS_MAX);
         set((const void*)conv_tile_kernel<128, false>, CT_LDS_MAX);
         set((const void*)first_pool_kernel<64, 4>, FirstPoolCfg<64, 4>::LDS_MAX);
@@ -841,6 +848,74 @@ inline bool launch_conv_tile(hipStream_t st, const LwLayerDev& d, const bf16x8* 
     }
 }
 
+template <class F>
+inline bool strip_by_width(int C, F go)
+{
+    switch (C) {
+    case 16: return go(std::integral_constant<int, 16>{});
+    case 32: return go(std::integral_constant<int, 32>{});
+    case 64: return go(std::integral_constant<int, 64>{});
+    case 128: return go(std::integral_constant<int, 128>{});
+    default: return false;
+    }
+}
+
+// Whether a section's residual blocks run on the strip kernels.
+inline bool strip_blocks_fit(const Section& sec, int B, int n_cu)
+{
+    const int C = sec.conv0.Cout;
+    return strip_by_width(C, [&](auto cc) {
+        StripBlockPlan<decltype(cc)::value> pl;
+        return pl.choose(B, sec.PH, sec.PW, n_cu);
+    });
+}
+
+// Both residual blocks of a section: xb (bf16, the pooled map) -> y; x is the fp32 stream between them.
+inline void launch_strip_blocks(hipStream_t st, const LwLayerDev* d, const bf16x8* wp_conv, const float* d_w, const Section& sec, int B,
+                                int n_cu, const __bf16* xb, float* x, __bf16* y, int y_relu, int ldy)
+{
+    strip_by_width(sec.conv0.Cout, [&](auto cc) {
+        constexpr int CC = decltype(cc)::value;
+        StripBlockPlan<CC> pl;
+        if (!pl.choose(B, sec.PH, sec.PW, n_cu)) return false;
+        StripBlockArgs a{};
+        a.B = B; a.H = sec.PH; a.W = sec.PW; a.TH = pl.TH; a.strips = pl.strips; a.stack = pl.stack; a.nblk = pl.nblk;
+        a.groups = pl.stack > 1 ? (B + pl.stack - 1) / pl.stack : B * pl.strips;
+        a.x_out = x; a.y_relu = y_relu; a.ldy = ldy;
+        auto weights = [&](int at, int conv) { a.wp[at] = wp_conv + d[conv].wp_off / 8; a.bias[at] = d_w + sec.block[conv].b_off; };
+        for (int i = 0; i < 2 * pl.nblk; ++i) weights(i, i);
+        a.x_in = xb;
+        a.y = pl.nblk == 2 ? y : nullptr;
+        hipLaunchKernelGGL((strip_block_kernel<CC, true>), dim3(a.groups), dim3(RS_THREADS), pl.lds, st, a);
+        if (pl.nblk == 1) {
+            weights(0, 2); weights(1, 3);
+            a.x_in = x; a.x_out = nullptr; a.y = y;
+            hipLaunchKernelGGL((strip_block_kernel<CC, false>), dim3(a.groups), dim3(RS_THREADS), pl.lds, st, a);
+        }
+        return true;
+    });
+}
+
+// conv0 of a later section with its pooling on the strip kernel (bf16 NHWC map -> x as bf16); false when the channel
+// pair has no such kernel or no strip fits, and nothing was launched.
+inline bool launch_strip_pool(hipStream_t st, const LwLayerDev& d, const bf16x8* wp_conv, const float* d_w, const Section& sec, int B,
+                              const __bf16* in, __bf16* x)
+{
+    const ConvLayer& c = sec.conv0;
+    if (c.Cout % c.Cin) return false;
+    return strip_by_width(c.Cin, [&](auto cc) {
+        constexpr int CC = decltype(cc)::value;
+        StripPoolPlan<CC> pl;
+        if (!pl.choose(c.H, c.W, sec.PH, sec.pool_pad_h)) return false;
+        StripPoolArgs a{};
+        a.in = in; a.wp = wp_conv + d.wp_off / 8; a.bias = d_w + c.b_off; a.x = x;
+        a.B = B; a.H = c.H; a.W = c.W; a.PH = sec.PH; a.PW = sec.PW; a.pad_h = sec.pool_pad_h; a.pad_w = sec.pool_pad_w; a.COUT = c.Cout;
+        a.PTH = pl.PTH; a.strips = pl.strips; a.groups = B * pl.strips * (c.Cout / CC);
+        hipLaunchKernelGGL(strip_pool_kernel<CC>, dim3(a.groups), dim3(RS_THREADS), StripCfg<CC>::lds_bytes(pl.rows + 2, c.W), st, a);
+        return true;
+    });
+}
+
 // Torso and linear layer over B rows: leaves the rectified linear-layer output of row r in row r of
 // fc_bf16 / fc_f32.
 inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w, hipStream_t st, int B, const uint8_t* obs,
@@ -869,6 +944,16 @@ inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w
                 const int ft = nft % 4 == 0 ? 4 : (nft % 2 == 0 ? 2 : 1);
                 launch_lw_conv(st, ca, ft, u8);
             };
+            // conv0 + pooling, then both blocks, on the strip kernels where the section's strips fit
+            if (strip_blocks_fit(sec, B, s->n_cu) &&
+                (si == 0 ? launch_first_pool(st, s->lw[li], W.wp_conv, d_w, sec, B, obs, nullptr, s->lw_u)
+                         : launch_strip_pool(st, s->lw[li], W.wp_conv, d_w, sec, B, (const __bf16*)in, s->lw_u))) {
+                launch_strip_blocks(st, &s->lw[li + 1], W.wp_conv, d_w, sec, B, s->n_cu, s->lw_u, s->lw_x, last_sec ? s->feat : s->lw_r,
+                                    last_sec ? 1 : 0, last_sec ? s->ldf : 0);
+                li += 5;
+                in = s->lw_r;
+                continue;
+            }
             // only the layer-by-layer block convolutions read R; a fused block takes ReLU(x) itself
             const bool need_r = !resblock_fusable(sec.block[0], sec.block[1]);
             if (si == 0 && launch_first_pool(st, s->lw[li], W.wp_conv, d_w, sec, B, obs, s->lw_x, need_r ? s->lw_r : nullptr)) {

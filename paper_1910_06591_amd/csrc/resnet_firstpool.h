@@ -25,8 +25,9 @@ struct FirstPoolArgs {
     const bf16x8* wp;                  // [C0 / 16][chunks][64 lanes][8]
     const float* bias;
     float scale;
-    float* x;                          // [B, PH, PW, C0] fp32
-    __bf16* r;                         // [B, PH, PW, C0] ReLU(x) as bf16, or nullptr
+    float* x;                          // [B, PH, PW, C0] fp32, or nullptr
+    __bf16* r;                         // [B, PH, PW, C0] bf16, or nullptr: ReLU(x) next to x; x itself (exact: the maxima
+                                       // are bf16 values) where x is nullptr
     int B, H, W, Cin, PH, PW, pad_h, pad_w;
     int PTH, PTW, tiles_y, tiles_x;
 };
@@ -229,6 +230,10 @@ __global__ __launch_bounds__(FP_THREADS) void first_pool_kernel(FirstPoolArgs p)
             for (int dx = 0; dx < 3; ++dx)
                 if (dy + dx > 0) m = bf16x8_max(m, *(const uint4*)(win + (size_t)(dy * CRW + dx) * K::CSTRIDE));
         const size_t o = (((size_t)b * p.PH + ph0 + ph) * p.PW + pw0 + pw) * C0 + cg * 8;
+        if (!p.x) {
+            *(uint4*)(p.r + o) = m;
+            continue;
+        }
         *(floatx4*)(p.x + o) = floatx4{bf16_lo_f32(m.x), bf16_hi_f32(m.x), bf16_lo_f32(m.y), bf16_hi_f32(m.y)};
         *(floatx4*)(p.x + o + 4) = floatx4{bf16_lo_f32(m.z), bf16_hi_f32(m.z), bf16_lo_f32(m.w), bf16_hi_f32(m.w)};
         if (p.r) {

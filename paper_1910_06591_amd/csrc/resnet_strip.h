@@ -1,0 +1,535 @@
+// Layer-by-layer ResNet path, maps whose full-width strips fit LDS: conv0 + pooling of a section, and its residual
+// blocks (one per launch, or both where a workgroup holds whole images), each in one launch over ONE LDS map that every
+// convolution rewrites in place.
+//
+// A workgroup takes TH rows of an image (all W columns), a whole image or several stacked ones.  The map is planar
+// bf16 [C/8][cells][8 channels]; a row is W + 1 cells, cell 0 of which is zero: it is the left border of its own row
+// and the right border of the row above (SAME padding without a second border column).  The output pixels of a
+// convolution are walked flat over the map, border cells included (computed, and kept zero): a tile is 16
+// consecutive cells, so its fragments are 256 distinct bank bytes - the full LDS rate, where 16 row-major pixels
+// of a narrower region wrap rows and read at about 57 % - and tile i of a wavefront sits at a constant distance
+// from tile 0: one address register for all of them, immediates for the rest.
+//
+// In place: a wavefront keeps its whole output (up to TPW pixel tiles x FTW feature tiles) in accumulators, the
+// workgroup waits until everybody has read the input map, and the output overwrites it.  Half the LDS of an input
+// and an output map, so a tile holds twice the pixels with two workgroups per compute unit, and that is what the
+// layer needs: with FTW = 2 feature tiles a wavefront's weight fragments (global, vector L1: 64 B/clk per compute
+// unit) serve up to 9 pixel tiles instead of 4 or 5, and the halo that neighbouring strips recompute shrinks.
+// Weight packing: A fragments [feature tile][chunk][lane][8], k = tap * C + ci.
+#pragma once
+#include "resnet_blockfused.h"
+
+namespace seedinf {
+
+constexpr int RS_THREADS = 512;
+constexpr size_t RS_LDS_MAX = 80 * 1024;                    // two workgroups per compute unit
+constexpr int RS_MAX_STACK = 4;                             // images a workgroup stacks
+
+template <int C>
+struct StripCfg {
+    static_assert(C == 16 || C == 32 || C == 64 || C == 128, "widths with a strip kernel");
+    static constexpr int NCG = C / 8, NFT = C / 16;
+    static constexpr int FTW = C == 16 ? 1 : 2;             // feature tiles a wavefront multiplies with one map fragment
+    static constexpr int NFG = NFT / FTW;
+    static constexpr int NPG = 8 / NFG;                     // wavefronts (pixel groups) per feature group
+    static constexpr int TPW = C == 16 ? 12 : 9;            // pixel tiles a wavefront's accumulators hold
+    static constexpr int KCH = (9 * C + 31) / 32;
+    static constexpr int MAX_TILES = TPW * NPG;
+    // cells of a plane: `rows` rows and the right border of the last, in whole 256 bytes
+    __host__ __device__ static constexpr int plane(int rows, int W) { return (rows * (W + 1) + 1 + 15) / 16 * 16; }
+    static constexpr size_t lds_bytes(int rows, int W) { return (size_t)NCG * plane(rows, W) * 16; }
+    __host__ __device__ static constexpr int tiles(int rows, int W) { return (rows * (W + 1) - 1 + 15) / 16; }
+    static constexpr bool fits(int rows, int map_rows, int W)
+    {
+        return tiles(rows, W) <= MAX_TILES && lds_bytes(map_rows, W) <= RS_LDS_MAX;
+    }
+};
+
+// logical workgroup of a launch: consecutive workgroups land on the eight XCDs in turn, so each XCD is given one run
+// of consecutive strips, whose shared halo rows then meet in its L2
+__device__ __forceinline__ int xcd_run(int idx, int total)
+{
+    const int per = total >> 3, rem = total & 7, x = idx & 7;
+    return x * per + min(x, rem) + (idx >> 3);
+}
+
+// The lane number, worked out afresh: what follows from it is not hoisted over (and spilled across) the phases.
+__device__ __forceinline__ int fresh_lane(int lane)
+{
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
+// acc[i][j] = convolution of pixel tile pg + NPG * i and feature tile ft0 + j of a region that starts at `src` (tap
+// (0, 0) of its first pixel, plane 0): pixel q has tap (kh, kw) at cell q + kh * P + kw.  `last`: the region's last
+// pixel, which lanes past the end read again.
+template <int C, int NT>
+__device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int pg, int last, const bf16x8* __restrict__ wl, int lane,
+                                           floatx4 (&acc)[NT][StripCfg<C>::FTW])
+{
+    using K = StripCfg<C>;
+    constexpr int FTW = K::FTW, KCH = K::KCH, STEP = K::NPG * 256;
+    // Map fragments travel in a ring of RING registers sets, RING tiles (of this chunk or the next) ahead of their use;
+    // RING divides NT so that a slot serves the same tiles in every chunk.  Weight fragments are requested one
+    // chunk ahead.  The order is pinned: left alone, the compiler saves registers by asking for every fragment
+    // right before its MFMAs, and each then waits out an LDS trip (64 channels on 36 x 48, 1024 images: 361 us).
+    constexpr int RING = NT % 4 == 0 ? 4 : (NT % 3 == 0 ? 3 : (NT % 5 == 0 ? 5 : NT));
+    lane = fresh_lane(lane);
+    const int g = lane >> 4, n = lane & 15;
+    const int q0 = pg * 16 + n, ql = min(q0 + (NT - 1) * K::NPG * 16, last);
+    const int plane = (C == 16 ? (g & 1) : g) * PL;
+    const char* s0 = src + (plane + min(q0, last)) * 16;
+    const char* sl = src + (plane + ql) * 16;
+    // byte offset of chunk kc's tap and channel planes
+    auto off = [&](int kc) {
+        if constexpr (C == 16) {
+            const int t0 = 2 * kc, t1 = min(2 * kc + 1, 8);  // (the tenth tap has zero weights)
+            const int o0 = (t0 / 3) * P + t0 % 3, o1 = (t1 / 3) * P + t1 % 3;
+            return ((g >> 1) ? o1 : o0) * 16;
+        } else {
+            constexpr int CPT = C / 32;
+            const int tap = kc / CPT;
+            return ((kc % CPT) * 4 * PL + (tap / 3) * P + tap % 3) * 16;
+        }
+    };
+    auto frag = [&](int o, int i) { return *(const bf16x8*)((i < NT - 1 ? s0 + i * STEP : sl) + o); };
+    bf16x8 a[2][FTW], b[RING];
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+        for (int j = 0; j < FTW; ++j) a[d][j] = wl[(j * KCH + d) * 64 + lane];
+    int o = off(0);
+#pragma unroll
+    for (int i = 0; i < RING; ++i) b[i] = frag(o, i);
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < FTW; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto chunk = [&](int kc, bf16x8 (&w)[FTW]) {
+        const int on = off(min(kc + 1, KCH - 1));
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+#pragma unroll
+            for (int j = 0; j < FTW; ++j) acc[i][j] = mfma16(w[j], b[i % RING], acc[i][j]);
+            b[i % RING] = i + RING < NT ? frag(o, i + RING) : frag(on, i + RING - NT);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const int kn = min(kc + 2, KCH - 1);
+#pragma unroll
+        for (int j = 0; j < FTW; ++j) w[j] = (wl + (j * KCH + kn) * 64)[lane];
+        __builtin_amdgcn_sched_barrier(0);
+        o = on;
+    };
+    int kc = 0;
+#pragma unroll 1
+    for (; kc + 2 <= KCH; kc += 2) {
+        chunk(kc, a[0]);
+        chunk(kc + 1, a[1]);
+    }
+    if constexpr (KCH % 2) chunk(KCH - 1, a[0]);
+}
+
+// Calls phase(NT) for the number of pixel tiles this wavefront owns (uniform): a convolution and its epilogue with the
+// count a constant.  (Barriers inside: every wavefront passes the same number of them whatever its count.)
+template <int TPW, class F>
+__device__ __forceinline__ void by_tiles(int nt, F phase)
+{
+    auto go = [&](auto ntc) {
+        if constexpr (decltype(ntc)::value <= TPW) phase(ntc);
+    };
+    switch (nt) {
+    case 0: go(std::integral_constant<int, 0>{}); break;
+    case 1: go(std::integral_constant<int, 1>{}); break;
+    case 2: go(std::integral_constant<int, 2>{}); break;
+    case 3: go(std::integral_constant<int, 3>{}); break;
+    case 4: go(std::integral_constant<int, 4>{}); break;
+    case 5: go(std::integral_constant<int, 5>{}); break;
+    case 6: go(std::integral_constant<int, 6>{}); break;
+    case 7: go(std::integral_constant<int, 7>{}); break;
+    case 8: go(std::integral_constant<int, 8>{}); break;
+    case 9: go(std::integral_constant<int, 9>{}); break;
+    case 10: go(std::integral_constant<int, 10>{}); break;
+    case 11: go(std::integral_constant<int, 11>{}); break;
+    case 12: go(std::integral_constant<int, 12>{}); break;
+    case 13: go(std::integral_constant<int, 13>{}); break;
+    case 14: go(std::integral_constant<int, 14>{}); break;
+    case 15: go(std::integral_constant<int, 15>{}); break;
+    default: go(std::integral_constant<int, 16>{}); break;
+    }
+}
+
+// (row, column) of the lane's pixel in a wavefront's successive tiles, P cells to a row, step by step: all tiles'
+// coordinates at once would need the registers the accumulators are in.
+struct TileWalk {
+    int q, r, c, dr, dc, P, step;
+    __device__ __forceinline__ TileWalk(int first, int step_, int P_) : q(first), P(P_), step(step_)
+    {
+        r = q / P; c = q - r * P;
+        dr = step / P; dc = step - dr * P;
+    }
+    __device__ __forceinline__ void next()
+    {
+        q += step; c += dc; r += dr;
+        if (c >= P) { c -= P; ++r; }
+    }
+};
+
+// ---- residual blocks ----------------------------------------------------------
+struct StripBlockArgs {
+    const void* x_in;                  // [B, H, W, C]: bf16 (X_BF16: the pooled map, whose values are bf16 by origin) or fp32
+    const bf16x8* wp[4];               // conv_a, conv_b of the first block (and of the second)
+    const float* bias[4];
+    float* x_out;                      // fp32 x' of the first block [B, H, W, C]; unused by a lone closing block
+    __bf16* y;                         // bf16 output of the closing block, or nullptr
+    int y_relu, ldy;                   // rectify y; ldy > 0: y is the feature matrix [B, ldy], (h, w, c) order
+    int B, H, W, TH, strips;           // strips of TH rows per image; strips == 1 with `stack` images per workgroup
+    int stack, nblk, groups;           // blocks in this launch (2: whole images only); workgroups
+};
+
+template <int C>
+struct StripBlockPlan {
+    using K = StripCfg<C>;
+    int TH = 0, strips = 0, stack = 1, nblk = 1;
+    size_t lds = 0;
+    // Rows per strip: the cut with the least work (tiles per wavefront, both convolutions, the halo row that
+    // conv_a computes on each inner side included) that fits.  Whole images run both blocks in one launch: no
+    // halo, and x' is read back by the lanes that wrote it.  Small images are stacked while there are workgroups
+    // enough for two per compute unit: a lone 9 x 12 map gives a wavefront two to four tiles per weight fragment.
+    bool choose(int B, int H, int W, int n_cu)
+    {
+        long best = -1;
+        for (int ny = 1; ny <= H; ++ny) {
+            const int th = (H + ny - 1) / ny;
+            if ((th - 1) * ny >= H) continue;               // (the same rows with a smaller ny)
+            const int ns = (H + th - 1) / th;
+            const int ra = ns == 1 ? th : (ns == 2 ? th + 1 : th + 2);
+            if (!K::fits(ra, ra + 2, W)) continue;
+            const long cost = (long)ns * (K::tiles(ra, W) + K::tiles(th, W) + 2 * K::NPG);
+            if (best < 0 || cost < best) { best = cost; TH = th; strips = ns; }
+        }
+        if (best < 0) return false;
+        if (strips == 1) {
+            nblk = 2;
+            for (int s = 2; s <= RS_MAX_STACK; ++s) {
+                const int rows = s * (H + 1) - 1;
+                if ((B + s - 1) / s < 2 * n_cu || !K::fits(rows, rows + 2, W)) break;
+                stack = s;
+            }
+        }
+        const int ra = strips == 1 ? stack * (H + 1) - 1 : (strips == 2 ? TH + 1 : TH + 2);
+        lds = K::lds_bytes(ra + 2, W);
+        return true;
+    }
+};
+
+template <int C, bool X_BF16>
+__global__ __launch_bounds__(RS_THREADS, 4) void strip_block_kernel(StripBlockArgs p)
+{
+    using K = StripCfg<C>;
+    constexpr int FTW = K::FTW, TPW = K::TPW;
+    extern __shared__ __attribute__((aligned(16))) char rs_lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wg = xcd_run(blockIdx.x, p.groups);
+    const int P = p.W + 1, Hp = p.H + 1;
+    const bool stacked = p.stack > 1;
+    const int b = stacked ? wg * p.stack : wg / p.strips;
+    const int y0 = stacked ? 0 : (wg % p.strips) * p.TH;
+    const int ye = min(y0 + p.TH, p.H);                      // the strip's rows: y0 .. ye - 1
+    const int nimg = min(p.stack, p.B - b);
+    // map row 0 is image row m0; conv_a covers image rows ya .. yz - 1, conv_b the strip's
+    const int m0 = max(y0 - 2, -1), ya = max(y0 - 1, 0), yz = min(ye + 1, p.H);
+    const int arow = ya - m0, brow = y0 - m0;
+    const int ra = stacked ? nimg * Hp - 1 : yz - ya, rb = stacked ? ra : ye - y0;
+    const int MR = arow + ra + 1;
+    const int PL = K::plane(MR, p.W);
+    const size_t img = (size_t)p.H * p.W * C;
+
+    // (image, row) of a map row; rows between stacked images and outside an image are zero
+    auto image_row = [&](int r, int& im, int& y) {
+        y = m0 + r;
+        im = 0;
+        if (stacked) {
+#pragma unroll
+            for (int k = 1; k < RS_MAX_STACK; ++k)
+                if (y >= Hp) { y -= Hp; ++im; }
+        }
+        return y >= 0 && y < p.H && im < nimg;
+    };
+
+    // ---- R = ReLU(x) as bf16, zeros in the border cells; four items' loads before the first conversion ----
+    {
+        constexpr int UNR = X_BF16 ? 10 : 5, CSTEP = RS_THREADS / K::NCG;
+        static_assert(RS_THREADS % K::NCG == 0, "a thread keeps its channel group");
+        const int cg = tid % K::NCG, cells = MR * P + 1;
+        RowWalk rw(tid / K::NCG, CSTEP, P);
+        for (int cell0 = tid / K::NCG; cell0 < cells; cell0 += UNR * CSTEP) {
+            floatx4 lo[UNR], hi[UNR];
+            bf16x8 v[UNR];
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                int im, y;
+                const bool in = image_row(rw.r, im, y) && rw.c > 0 && cell0 + u * CSTEP < cells;
+                const int o = im * (int)img + (y * p.W + rw.c - 1) * C + cg * 8;      // from image b
+                rw.next();
+                v[u] = bf16x8{};
+                lo[u] = hi[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+                if (in) {
+                    if constexpr (X_BF16) {
+                        v[u] = *(const bf16x8*)((const __bf16*)p.x_in + b * img + o);
+                    } else {
+                        lo[u] = *(const floatx4*)((const float*)p.x_in + b * img + o);
+                        hi[u] = *(const floatx4*)((const float*)p.x_in + b * img + o + 4);
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                if (cell0 + u * CSTEP >= cells) continue;
+                const bf16x8 raw = X_BF16 ? v[u] : to_bf16x8(lo[u], hi[u]);
+                const bf16x4 l = relu_bf16x4(__builtin_shufflevector(raw, raw, 0, 1, 2, 3));
+                const bf16x4 h = relu_bf16x4(__builtin_shufflevector(raw, raw, 4, 5, 6, 7));
+                *(bf16x8*)(rs_lds + (size_t)(cg * PL + cell0 + u * CSTEP) * 16) = __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7);
+            }
+        }
+    }
+    __syncthreads();
+
+    const int fg = wave % K::NFG, pg = wave / K::NFG;
+    const int ft0 = fg * FTW;
+    // where lane group g's four channels of feature tile ft0 go in the map: plane (ft0 * 16 + 4 g) / 8, half g & 1
+    auto out_cell = [&](int g) { return rs_lds + ((ft0 * 2 + (g >> 1)) * PL) * 16 + (g & 1) * 8; };
+
+    auto tiles_of = [&](int npix) { return ((npix + 15) / 16 - pg + K::NPG - 1) / K::NPG; };      // (at most TPW: the host's plan)
+    for (int blk = 0; blk < p.nblk; ++blk) {
+        // ---- U = ReLU(conv_a(R) + bias), in place ----
+        const int npa = ra * P - 1;
+        by_tiles<TPW>(tiles_of(npa), [&](auto ntc) {
+            constexpr int NT = decltype(ntc)::value;
+            if constexpr (NT == 0) {
+                __syncthreads();
+            } else {
+                floatx4 acc[NT][FTW];
+                strip_conv<C, NT>(rs_lds + (arow - 1) * P * 16, PL, P, pg, npa - 1, p.wp[2 * blk] + ft0 * K::KCH * 64, lane, acc);
+                const int ln = fresh_lane(lane), g = ln >> 4;
+                floatx4 bv[FTW];
+#pragma unroll
+                for (int j = 0; j < FTW; ++j) bv[j] = *(const floatx4*)(p.bias[2 * blk] + (ft0 + j) * 16 + g * 4);
+                __syncthreads();                             // everybody has read R
+                TileWalk w(pg * 16 + (ln & 15), K::NPG * 16, P);
+                char* cell = out_cell(g) + (arow * P + 1 + w.q) * 16;
+#pragma unroll
+                for (int i = 0; i < NT; ++i, w.next(), cell += K::NPG * 256) {
+                    int im, y;
+                    const bool in = w.c < p.W && image_row(arow + w.r, im, y);
+                    if (i < NT - 1 || w.q < npa) {
+#pragma unroll
+                        for (int j = 0; j < FTW; ++j) {
+                            bf16x4 o = {};
+                            if (in) o = relu_bf16x4(to_bf16x4(acc[i][j] + bv[j]));
+                            *(bf16x4*)(cell + j * 2 * PL * 16) = o;
+                        }
+                    }
+                }
+            }
+        });
+        __syncthreads();
+        // ---- x' = x + conv_b(U) + bias ----
+        const int npb = rb * P - 1;
+        const bool closing = blk + 1 == p.nblk;
+        by_tiles<TPW>(tiles_of(npb), [&](auto ntc) {
+            constexpr int NT = decltype(ntc)::value;
+            if constexpr (NT == 0) {
+                if (!closing) __syncthreads();
+            } else {
+                floatx4 acc[NT][FTW];
+                strip_conv<C, NT>(rs_lds + (brow - 1) * P * 16, PL, P, pg, npb - 1, p.wp[2 * blk + 1] + ft0 * K::KCH * 64, lane, acc);
+                const int ln = fresh_lane(lane), g = ln >> 4;
+                floatx4 bv[FTW];
+#pragma unroll
+                for (int j = 0; j < FTW; ++j) bv[j] = *(const floatx4*)(p.bias[2 * blk + 1] + (ft0 + j) * 16 + g * 4);
+                if (!closing) __syncthreads();               // everybody has read U: the next R overwrites it
+                TileWalk w(pg * 16 + (ln & 15), K::NPG * 16, P);
+                char* cell = out_cell(g) + (brow * P + 1 + w.q) * 16;
+                const int f0 = ft0 * 16 + g * 4;
+                // XB tiles' residuals are requested before the first of them is added (stores may alias later loads as
+                // far as the compiler knows: one tile at a time, each waits out a trip to memory)
+                constexpr int XB = C == 16 ? 4 : 2;
+#pragma unroll
+                for (int i0 = 0; i0 < NT; i0 += XB) {
+                    floatx4 r[XB][FTW];
+                    int at[XB], yo[XB];                      // element offsets from image b; -1: no pixel
+#pragma unroll
+                    for (int u = 0; u < XB; ++u) {
+                        if (i0 + u >= NT) break;
+                        int im, y;
+                        const bool in = w.c < p.W && image_row(brow + w.r, im, y) && (i0 + u < NT - 1 || w.q < npb);
+                        const int pl = (y * p.W + w.c) * C + f0;
+                        at[u] = in ? im * (int)img + pl : -1;
+                        yo[u] = p.ldy > 0 ? im * p.ldy + pl : at[u];
+                        w.next();
+                        const int from = max(at[u], 0);
+#pragma unroll
+                        for (int j = 0; j < FTW; ++j) {
+                            if (blk == 0) {
+                                if constexpr (X_BF16) r[u][j] = to_floatx4(*(const bf16x4*)((const __bf16*)p.x_in + b * img + from + j * 16));
+                                else r[u][j] = *(const floatx4*)((const float*)p.x_in + b * img + from + j * 16);
+                            } else {
+                                r[u][j] = *(const floatx4*)(p.x_out + b * img + from + j * 16);     // this lane's own x' of the first block
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < XB; ++u) {
+                        if (i0 + u >= NT) break;
+                        if (at[u] >= 0) {
+#pragma unroll
+                            for (int j = 0; j < FTW; ++j) {
+                                const floatx4 v = acc[i0 + u][j] + bv[j] + r[u][j];
+                                if (!closing) *(bf16x4*)(cell + j * 2 * PL * 16) = relu_bf16x4(to_bf16x4(v));
+                                if (!closing || !p.y) {
+                                    *(floatx4*)(p.x_out + b * img + at[u] + j * 16) = v;
+                                } else {
+                                    const bf16x4 t = to_bf16x4(v);
+                                    *(bf16x4*)(p.y + (p.ldy > 0 ? (size_t)b * p.ldy : b * img) + yo[u] + j * 16) = p.y_relu ? relu_bf16x4(t) : t;
+                                }
+                            }
+                        }
+                        cell += K::NPG * 256;
+                    }
+                }
+            }
+        });
+        if (!closing) __syncthreads();
+    }
+}
+
+// ---- conv0 of a later section with its pooling --------------------------------
+// bf16 NHWC input of C channels -> 3x3 SAME convolution -> 3x3 / stride-2 max-pool -> the section's x as bf16 (the
+// maxima of values that were rounded to bf16 before they were compared: no rounding of its own).  A workgroup
+// computes C of the layer's output channels (blockIdx.y: which), so that its output fits over its input, for the
+// convolution rows under PTH pooled rows; window cells outside the map are clamped onto it.
+struct StripPoolArgs {
+    const __bf16* in;                  // [B, H, W, C]
+    const bf16x8* wp;                  // [COUT / 16][chunks][64 lanes][8], k = tap * C + ci
+    const float* bias;
+    __bf16* x;                         // [B, PH, PW, COUT]
+    int B, H, W, PH, PW, pad_h, pad_w, COUT, PTH, strips, groups;
+};
+
+template <int C>
+struct StripPoolPlan {
+    using K = StripCfg<C>;
+    int PTH = 0, strips = 0, rows = 0;
+    bool choose(int H, int W, int PH, int pad_h)
+    {
+        long best = -1;
+        for (int pth = 1; pth <= PH; ++pth) {
+            const int ns = (PH + pth - 1) / pth;
+            int r = 0;                                       // the most convolution rows a strip covers
+            long work = 0;
+            for (int s = 0; s < ns; ++s) {
+                const int p0 = s * pth, p1 = std::min(p0 + pth, PH);
+                const int n = std::min(2 * (p1 - 1) - pad_h + 2, H - 1) - std::max(2 * p0 - pad_h, 0) + 1;
+                r = std::max(r, n);
+                work += K::tiles(n, W) + 2 * K::NPG;
+            }
+            if (!K::fits(r, r + 2, W)) continue;
+            if (best < 0 || work < best) { best = work; PTH = pth; strips = ns; rows = r; }
+        }
+        return best >= 0;
+    }
+};
+
+template <int C>
+__global__ __launch_bounds__(RS_THREADS, 4) void strip_pool_kernel(StripPoolArgs p)
+{
+    using K = StripCfg<C>;
+    constexpr int FTW = K::FTW, TPW = K::TPW;
+    extern __shared__ __attribute__((aligned(16))) char rs_lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, n = lane & 15;
+    // the feature groups of a strip are neighbours: they read the same input
+    const int nf = p.COUT / C;
+    const int wg = xcd_run(blockIdx.x, p.groups);
+    const int fbase = (wg % nf) * K::NFT, strip = wg / nf;
+    const int b = strip / p.strips, ph0 = (strip % p.strips) * p.PTH, ph1 = min(ph0 + p.PTH, p.PH);
+    const int P = p.W + 1;
+    const int yc = max(2 * ph0 - p.pad_h, 0), yz = min(2 * (ph1 - 1) - p.pad_h + 3, p.H);      // convolution rows yc .. yz - 1
+    const int m0 = yc - 1, rows = yz - yc, MR = rows + 2;
+    const int PL = K::plane(MR, p.W);
+    const __bf16* img = p.in + (size_t)b * p.H * p.W * C;
+
+    {
+        constexpr int UNR = 10, CSTEP = RS_THREADS / K::NCG;
+        const int cg = tid % K::NCG, cells = MR * P + 1;
+        RowWalk rw(tid / K::NCG, CSTEP, P);
+        for (int cell0 = tid / K::NCG; cell0 < cells; cell0 += UNR * CSTEP) {
+            bf16x8 v[UNR];
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                const int y = m0 + rw.r, x = rw.c - 1;
+                rw.next();
+                v[u] = bf16x8{};
+                if (cell0 + u * CSTEP < cells && y >= 0 && y < p.H && x >= 0) v[u] = *(const bf16x8*)(img + ((size_t)y * p.W + x) * C + cg * 8);
+            }
+#pragma unroll
+            for (int u = 0; u < UNR; ++u)
+                if (cell0 + u * CSTEP < cells) *(bf16x8*)(rs_lds + (size_t)(cg * PL + cell0 + u * CSTEP) * 16) = v[u];
+        }
+    }
+    __syncthreads();
+
+    {
+        const int fg = wave % K::NFG, pg = wave / K::NFG;
+        const int ft0 = fg * FTW;
+        const int npix = rows * P - 1;
+        by_tiles<TPW>(((npix + 15) / 16 - pg + K::NPG - 1) / K::NPG, [&](auto ntc) {
+            constexpr int NT = decltype(ntc)::value;
+            if constexpr (NT == 0) {
+                __syncthreads();
+            } else {
+                floatx4 acc[NT][FTW];
+                strip_conv<C, NT>(rs_lds, PL, P, pg, npix - 1, p.wp + (size_t)(fbase + ft0) * K::KCH * 64, lane, acc);
+                floatx4 bv[FTW];
+#pragma unroll
+                for (int j = 0; j < FTW; ++j) bv[j] = *(const floatx4*)(p.bias + (fbase + ft0 + j) * 16 + g * 4);
+                __syncthreads();                             // everybody has read the input
+                char* cell = rs_lds + ((ft0 * 2 + (g >> 1)) * PL + P + 1 + pg * 16 + n) * 16 + (g & 1) * 8;
+#pragma unroll
+                for (int i = 0; i < NT; ++i, cell += K::NPG * 256) {
+                    if (i == NT - 1 && (pg + K::NPG * i) * 16 + n >= npix) continue;
+#pragma unroll
+                    for (int j = 0; j < FTW; ++j) *(bf16x4*)(cell + j * 2 * PL * 16) = to_bf16x4(acc[i][j] + bv[j]);
+                }
+            }
+        });
+    }
+    __syncthreads();
+
+    // a wavefront pools PXW consecutive pixels x CGW channel groups at a time: reads of one plane are two cells apart
+    constexpr int CGW = K::NCG < 8 ? K::NCG : 8, PXW = 64 / CGW, NCB = K::NCG / CGW;
+    const int pxl = lane % PXW, cgl = lane / PXW;
+    const int npool = (ph1 - ph0) * p.PW;
+    for (int it = wave; it < (npool + PXW - 1) / PXW * NCB; it += RS_THREADS / 64) {
+        const int px = (it / NCB) * PXW + pxl, cg = (it % NCB) * CGW + cgl;
+        if (px >= npool) continue;
+        const int ph = px / p.PW, pw = px - ph * p.PW;
+        const int y = 2 * (ph0 + ph) - p.pad_h, x = 2 * pw - p.pad_w;
+        const char* pl = rs_lds + (size_t)(cg * PL + 1) * 16;
+        uint4 m;
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy) {
+            const char* row = pl + (size_t)((min(max(y + dy, yc), yz - 1) - m0) * P) * 16;
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) {
+                const uint4 v = *(const uint4*)(row + min(max(x + dx, 0), p.W - 1) * 16);
+                m = dy + dx == 0 ? v : bf16x8_max(m, v);
+            }
+        }
+        *(uint4*)(p.x + (((size_t)b * p.PH + ph0 + ph) * p.PW + pw) * p.COUT + fbase * 16 + cg * 8) = m;
+    }
+}
+
+}  // namespace seedinf
