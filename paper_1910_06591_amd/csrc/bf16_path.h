@@ -902,7 +902,7 @@ inline bool launch_strip_pool(hipStream_t st, const LwLayerDev& d, const bf16x8*
                               const __bf16* in, __bf16* x)
 {
     const ConvLayer& c = sec.conv0;
-    if (c.Cout % c.Cin) return false;
+    if (c.Cout != c.Cin && c.Cout != 2 * c.Cin) return false;      // (a workgroup per Cin output channels, each staging the input)
     return strip_by_width(c.Cin, [&](auto cc) {
         constexpr int CC = decltype(cc)::value;
         StripPoolPlan<CC> pl;

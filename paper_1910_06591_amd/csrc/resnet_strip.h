@@ -16,6 +16,15 @@
 // layer needs: with FTW = 2 feature tiles a wavefront's weight fragments (global, vector L1: 64 B/clk per compute
 // unit) serve up to 9 pixel tiles instead of 4 or 5, and the halo that neighbouring strips recompute shrinks.
 // Weight packing: A fragments [feature tile][chunk][lane][8], k = tap * C + ci.
+//
+// Measured, 1024 images, us per launch, against the kernels that keep an input and an output map (resnet_blockfused.h,
+// resnet_convpool.h, resnet_convtile.h), a section's two blocks together: 64 channels on 36 x 48 915 -> 655, on 18 x 24
+// 222 -> 135, on 9 x 12 82 -> 45; 128 channels on 18 x 24 680 -> 475, on 9 x 12 199 -> 123; 32 channels on 36 x 48 333 ->
+// 246, on 27 x 36 174 -> 111; 16 channels on 54 x 72 273 -> 253.  conv0 + pooling: 64 -> 128 on 36 x 48 339 -> 292, 128 ->
+// 128 on 18 x 24 212 -> 126, 32 -> 64 on 36 x 48 120 -> 85, 16 -> 32 on 54 x 72 107 -> 77.
+// What bounds them now (64 channels on 36 x 48, cycles of a workgroup's 90 K): staging 25 K and the epilogue 23 K of
+// memory, the two convolutions 36 K for 18 K of MFMAs (two workgroups share the matrix cores); 0.9 GB of HBM traffic is
+// 150 us at the copy rate, the MFMAs 119 us.
 #pragma once
 #include "resnet_blockfused.h"
 
@@ -70,8 +79,7 @@ __device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int p
     using K = StripCfg<C>;
     constexpr int FTW = K::FTW, KCH = K::KCH, STEP = K::NPG * 256;
     // Map fragments travel in a ring of RING registers sets, RING tiles (of this chunk or the next) ahead of their use;
-    // RING divides NT so that a slot serves the same tiles in every chunk.  Weight fragments are requested one
-    // chunk ahead.  The order is pinned: left alone, the compiler saves registers by asking for every fragment
+    // RING divides NT so that a slot serves the same tiles in every chunk.  The order is pinned: left alone, the compiler saves registers by asking for every fragment
     // right before its MFMAs, and each then waits out an LDS trip (64 channels on 36 x 48, 1024 images: 361 us).
     constexpr int RING = NT % 4 == 0 ? 4 : (NT % 3 == 0 ? 3 : (NT % 5 == 0 ? 5 : NT));
     lane = fresh_lane(lane);
@@ -93,9 +101,13 @@ __device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int p
         }
     };
     auto frag = [&](int o, int i) { return *(const bf16x8*)((i < NT - 1 ? s0 + i * STEP : sl) + o); };
-    bf16x8 a[2][FTW], b[RING];
+    // Weight fragments: WS slots, requested WS - 1 chunks ahead.  Three where two feature groups or more pull 36 KiB
+    // and up per convolution through the vector L1 (64 channels on 36 x 48 370 -> 362 us, 128 on 18 x 24 257 -> 244); at
+    // 32 channels the registers they take cost more (129 -> 147 us), and so at 16.
+    constexpr int WS = C >= 64 ? 3 : 2;
+    bf16x8 a[WS][FTW], b[RING];
 #pragma unroll
-    for (int d = 0; d < 2; ++d)
+    for (int d = 0; d < WS - 1; ++d)
 #pragma unroll
         for (int j = 0; j < FTW; ++j) a[d][j] = wl[(j * KCH + d) * 64 + lane];
     int o = off(0);
@@ -105,28 +117,32 @@ __device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int p
     for (int i = 0; i < NT; ++i)
 #pragma unroll
         for (int j = 0; j < FTW; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    auto chunk = [&](int kc, bf16x8 (&w)[FTW]) {
+    auto chunk = [&](int kc, auto dc) {
+        constexpr int D = decltype(dc)::value;
         const int on = off(min(kc + 1, KCH - 1));
+        const int kn = min(kc + WS - 1, KCH - 1);
+#pragma unroll
+        for (int j = 0; j < FTW; ++j) a[(D + WS - 1) % WS][j] = (wl + (j * KCH + kn) * 64)[lane];
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
 #pragma unroll
-            for (int j = 0; j < FTW; ++j) acc[i][j] = mfma16(w[j], b[i % RING], acc[i][j]);
+            for (int j = 0; j < FTW; ++j) acc[i][j] = mfma16(a[D][j], b[i % RING], acc[i][j]);
             b[i % RING] = i + RING < NT ? frag(o, i + RING) : frag(on, i + RING - NT);
             __builtin_amdgcn_sched_barrier(0);
         }
-        const int kn = min(kc + 2, KCH - 1);
-#pragma unroll
-        for (int j = 0; j < FTW; ++j) w[j] = (wl + (j * KCH + kn) * 64)[lane];
-        __builtin_amdgcn_sched_barrier(0);
         o = on;
     };
+    using D0 = std::integral_constant<int, 0>; using D1 = std::integral_constant<int, 1>; using D2 = std::integral_constant<int, 2>;
     int kc = 0;
 #pragma unroll 1
-    for (; kc + 2 <= KCH; kc += 2) {
-        chunk(kc, a[0]);
-        chunk(kc + 1, a[1]);
+    for (; kc + WS <= KCH; kc += WS) {
+        chunk(kc, D0{});
+        chunk(kc + 1, D1{});
+        if constexpr (WS == 3) chunk(kc + 2, D2{});
     }
-    if constexpr (KCH % 2) chunk(KCH - 1, a[0]);
+    static_assert(KCH % WS <= 1, "at most one chunk is left over");
+    if constexpr (KCH % WS == 1) chunk(KCH - 1, D0{});
 }
 
 // Calls phase(NT) for the number of pixel tiles this wavefront owns (uniform): a convolution and its epilogue with the
@@ -352,51 +368,47 @@ __global__ __launch_bounds__(RS_THREADS, 4) void strip_block_kernel(StripBlockAr
                 TileWalk w(pg * 16 + (ln & 15), K::NPG * 16, P);
                 char* cell = out_cell(g) + (brow * P + 1 + w.q) * 16;
                 const int f0 = ft0 * 16 + g * 4;
-                // XB tiles' residuals are requested before the first of them is added (stores may alias later loads as
-                // far as the compiler knows: one tile at a time, each waits out a trip to memory)
+                // residuals are requested XB tiles ahead of their use: one tile at a time, each waits out a trip to memory
                 constexpr int XB = C == 16 ? 4 : 2;
+                floatx4 r[XB][FTW];
+                int at[XB], yo[XB];                          // element offsets from image b; -1: no pixel
+                auto request = [&](int i) {
+                    int im, y;
+                    const bool in = w.c < p.W && image_row(brow + w.r, im, y) && (i < NT - 1 || w.q < npb);
+                    const int pl = (y * p.W + w.c) * C + f0;
+                    at[i % XB] = in ? im * (int)img + pl : -1;
+                    yo[i % XB] = p.ldy > 0 ? im * p.ldy + pl : at[i % XB];
+                    w.next();
+                    const int from = max(at[i % XB], 0);
 #pragma unroll
-                for (int i0 = 0; i0 < NT; i0 += XB) {
-                    floatx4 r[XB][FTW];
-                    int at[XB], yo[XB];                      // element offsets from image b; -1: no pixel
+                    for (int j = 0; j < FTW; ++j) {
+                        if (blk == 0) {
+                            if constexpr (X_BF16) r[i % XB][j] = to_floatx4(*(const bf16x4*)((const __bf16*)p.x_in + b * img + from + j * 16));
+                            else r[i % XB][j] = *(const floatx4*)((const float*)p.x_in + b * img + from + j * 16);
+                        } else {
+                            r[i % XB][j] = *(const floatx4*)(p.x_out + b * img + from + j * 16);     // this lane's own x' of the first block
+                        }
+                    }
+                };
 #pragma unroll
-                    for (int u = 0; u < XB; ++u) {
-                        if (i0 + u >= NT) break;
-                        int im, y;
-                        const bool in = w.c < p.W && image_row(brow + w.r, im, y) && (i0 + u < NT - 1 || w.q < npb);
-                        const int pl = (y * p.W + w.c) * C + f0;
-                        at[u] = in ? im * (int)img + pl : -1;
-                        yo[u] = p.ldy > 0 ? im * p.ldy + pl : at[u];
-                        w.next();
-                        const int from = max(at[u], 0);
+                for (int i = 0; i < XB && i < NT; ++i) request(i);
+#pragma unroll
+                for (int i = 0; i < NT; ++i, cell += K::NPG * 256) {
+                    const int u = i % XB;
+                    if (at[u] >= 0) {
 #pragma unroll
                         for (int j = 0; j < FTW; ++j) {
-                            if (blk == 0) {
-                                if constexpr (X_BF16) r[u][j] = to_floatx4(*(const bf16x4*)((const __bf16*)p.x_in + b * img + from + j * 16));
-                                else r[u][j] = *(const floatx4*)((const float*)p.x_in + b * img + from + j * 16);
+                            const floatx4 v = acc[i][j] + bv[j] + r[u][j];
+                            if (!closing) *(bf16x4*)(cell + j * 2 * PL * 16) = relu_bf16x4(to_bf16x4(v));
+                            if (!closing || !p.y) {
+                                *(floatx4*)(p.x_out + b * img + at[u] + j * 16) = v;
                             } else {
-                                r[u][j] = *(const floatx4*)(p.x_out + b * img + from + j * 16);     // this lane's own x' of the first block
+                                const bf16x4 t = to_bf16x4(v);
+                                *(bf16x4*)(p.y + (p.ldy > 0 ? (size_t)b * p.ldy : b * img) + yo[u] + j * 16) = p.y_relu ? relu_bf16x4(t) : t;
                             }
                         }
                     }
-#pragma unroll
-                    for (int u = 0; u < XB; ++u) {
-                        if (i0 + u >= NT) break;
-                        if (at[u] >= 0) {
-#pragma unroll
-                            for (int j = 0; j < FTW; ++j) {
-                                const floatx4 v = acc[i0 + u][j] + bv[j] + r[u][j];
-                                if (!closing) *(bf16x4*)(cell + j * 2 * PL * 16) = relu_bf16x4(to_bf16x4(v));
-                                if (!closing || !p.y) {
-                                    *(floatx4*)(p.x_out + b * img + at[u] + j * 16) = v;
-                                } else {
-                                    const bf16x4 t = to_bf16x4(v);
-                                    *(bf16x4*)(p.y + (p.ldy > 0 ? (size_t)b * p.ldy : b * img) + yo[u] + j * 16) = p.y_relu ? relu_bf16x4(t) : t;
-                                }
-                            }
-                        }
-                        cell += K::NPG * 256;
-                    }
+                    if (i + XB < NT) request(i + XB);
                 }
             }
         });

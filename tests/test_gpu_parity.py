@@ -512,3 +512,40 @@ def test_largest_batch_the_interface_allows(orc, precision):
                    lstm_units=16, num_actions=5, head=1, head_hidden=16, select=0, precision="bf16", obs_kind="uniform",
                    index=121)
     run_full(orc, cfg, B, sample=64)
+
+
+@pytest.mark.parametrize("label,over", [
+    # 34 x 22 frames: maps of 17 x 11 and 9 x 6, whole images, stacked from 1024 rows on; every width
+    ("16/32/64", dict(obs_h=34, obs_w=22, sections=[16, 32, 64])),
+    ("32/64/128", dict(obs_h=34, obs_w=22, sections=[32, 64, 128])),
+    ("64/128/128", dict(obs_h=33, obs_w=21, sections=[64, 128, 128])),
+])
+def test_bf16_strip_kernels_stack_small_images(orc, label, over):
+    """A batch large enough to stack images (a ragged last stack included) gives the same bits as the same rows in
+    a batch too small for it, and those match the oracle."""
+    cfg = dict(wl.CONFIGS["C3"], label=f"stacked strips {label}", index=120, **over)
+    B, few = 1029 + 512, 5
+    weights, batch = wl.make_weights(cfg), wl.make_batch(cfg, B)
+    net = seedinf.SeedInfer(seedinf.make_arch(cfg, max_batch=B), weights)
+    net.step(**to_device(batch))
+    big = net.read_intermediate(0, B).cpu().numpy()
+    rows = [0, 1, 2, B - 2, B - 1]
+    part = {k: None if v is None else np.ascontiguousarray(v[rows]) for k, v in batch.items()}
+    net.step(**to_device(part))
+    small = net.read_intermediate(0, few).cpu().numpy()
+    net.close()
+    np.testing.assert_array_equal(big[rows], small)
+    run_case(orc, cfg, few, "bf16")
+
+
+@pytest.mark.parametrize("label,over,B", [
+    # strips of one section that end in a shorter one, two strips (one halo side each) and many; rows of one pixel column
+    ("64 channels, 58 x 50 maps", dict(obs_h=116, obs_w=100, obs_c=3, sections=[64]), 2),
+    ("128 channels, 31 x 30 maps", dict(obs_h=124, obs_w=119, obs_c=1, sections=[64, 128]), 2),
+    ("128 channels, too wide for a strip", dict(obs_h=18, obs_w=520, obs_c=1, sections=[64, 128, 128]), 2),
+    ("16 channels, 70 x 61 maps", dict(obs_h=139, obs_w=121, obs_c=4, sections=[16, 16]), 2),
+    ("one column", dict(obs_h=40, obs_w=2, obs_c=4, sections=[32, 64]), 3),
+])
+def test_bf16_strip_kernels_at_the_edges_of_their_plans(orc, label, over, B):
+    cfg = dict(wl.CONFIGS["C3"], label=f"strips: {label}", index=121, fc_units=32, **over)
+    run_case(orc, cfg, B, "bf16")
