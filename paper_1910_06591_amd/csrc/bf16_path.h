@@ -569,6 +569,7 @@ inline bool launch_gemm_lds(hipStream_t st, const GemmArgs& g, int tile_groups, 
 {
     if (g.rows < GL_MIN_ROWS || (g.kc1 & 1)) return false;
     const int kct = g.kc1 + (g.k2 + 31) / 32;
+    auto rounds = [&](long row_tiles, long feature_tiles) { return (row_tiles * feature_tiles + n_cu - 1) / n_cu; };
     if constexpr (EPI == EPI_RELU) {
         // 64 x 64 tiles with K over the eight wavefronts where wider tiles would be too few for the chip: long K
         // (the linear layer after the torso) with fewer 128 x 256 tiles than compute units, and shorter K with
@@ -577,13 +578,21 @@ inline bool launch_gemm_lds(hipStream_t st, const GemmArgs& g, int tile_groups, 
         const long wide = (long)((g.rows + 127) / 128) * ((tile_groups + 3) / 4);
         const long mid = (long)((g.rows + 63) / 64) * ((tile_groups + 3) / 4);
         if (g.k2 == 0 && ((kct >= 64 && wide < n_cu) || (kct >= 16 && kct < 64 && mid < n_cu / 2))) {
-            hipLaunchKernelGGL((gemm_bf16_k8_kernel<EPI>), dim3((g.rows + 63) / 64, tile_groups), dim3(GL_THREADS), GL_K8_LDS_BYTES, st, g);
+            // A workgroup fills a compute unit, so time goes in whole rounds of n_cu tiles: 96-row tiles where that
+            // saves a round (K = 3136, 512 features, 3001 rows: two rounds of 64-row tiles 35 us, one of 96 rows 20 us;
+            // with 2 against 3 rounds the two would cost about the same)
+            if (2 * rounds((g.rows + 63) / 64, tile_groups) > 3 * rounds((g.rows + 95) / 96, tile_groups))
+                hipLaunchKernelGGL((gemm_bf16_k8_kernel<EPI, 6>), dim3((g.rows + 95) / 96, tile_groups), dim3(GL_THREADS), GL_K8_LDS_BYTES, st, g);
+            else
+                hipLaunchKernelGGL((gemm_bf16_k8_kernel<EPI>), dim3((g.rows + 63) / 64, tile_groups), dim3(GL_THREADS), GL_K8_LDS_BYTES, st, g);
             return true;
         }
     }
     const int by = (tile_groups + 3) / 4;
     constexpr int LDS42 = GemmXwCfg<4, 2, 1, true>::LDS_BYTES, LDS41 = GemmXwCfg<4, 1, 2, true>::LDS_BYTES;
-    if ((long)((g.rows + 127) / 128) * by >= n_cu)
+    // 128-row tiles where their rounds over the compute units cost no more: one takes about 1.5 rounds of 64-row tiles
+    // (512-unit core: 38 us against 25), so 3001 rows run as one round of 192 tiles, 39 us, instead of two of 376, 50 us
+    if (3 * rounds((g.rows + 127) / 128, by) <= 2 * rounds((g.rows + 63) / 64, by))
         hipLaunchKernelGGL((gemm_bf16_xw_kernel<4, 2, 1, EPI, true>), dim3((g.rows + 127) / 128, by), dim3(GL_THREADS), LDS42, st, g);
     else
         hipLaunchKernelGGL((gemm_bf16_xw_kernel<4, 1, 2, EPI, true>), dim3((g.rows + 63) / 64, by), dim3(GL_THREADS), LDS41, st, g);

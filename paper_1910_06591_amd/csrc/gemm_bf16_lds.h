@@ -16,8 +16,8 @@
 //     KG = 2 a wavefront takes every second K chunk of its sub-tile and the two partial sums meet in LDS at the
 //     end.  Activations go through a four-slot LDS ring with one barrier per stage of two chunks; a wavefront's
 //     weight fragments go straight into its registers.
-//   gemm_bf16_k8_kernel<EPI> (long K, few output tiles: the linear layer after the torso): the eight wavefronts
-//     share one 64 x 64 tile and each takes every eighth chunk.  Nothing is shared between them, so each runs
+//   gemm_bf16_k8_kernel<EPI, RT> (long K, few output tiles: the linear layer after the torso): the eight wavefronts
+//     share one 64 x 64 (RT = 4) or 96 x 64 (RT = 6) tile and each takes every eighth chunk.  Nothing is shared between them, so each runs
 //     private rings in its own 20 KiB of LDS (three slots of activation fragments, two of weight fragments)
 //     with no barrier inside the K loop.  The eight partial tiles meet in LDS and four wavefronts finish one
 //     row tile each.  (Splitting K over workgroups instead costs more than it saves here: partial sums that
@@ -41,88 +41,115 @@ __device__ __forceinline__ void wait_outstanding()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-template <int EPI>
-__global__ __launch_bounds__(GL_THREADS) void gemm_bf16_k8_kernel(GemmArgs p)
+// RT: row tiles of the workgroup's output tile, 4 (64 rows) or 6 (96 rows: two activation slots instead of three, and
+// the partial tiles meet in two steps).
+template <int EPI, int RT = 4>
+__global__ __launch_bounds__(GL_THREADS, 2) void gemm_bf16_k8_kernel(GemmArgs p)
 {
     static_assert(EPI == EPI_RELU, "the K-split tile has the plain epilogue only");
+    static_assert(RT == 4 || RT == 6, "row tiles whose rings fit 20 KiB");
+    constexpr int NX = RT == 4 ? 3 : 2, XSLOT = RT * 1024, WBASE = NX * XSLOT;
+    static_assert(WBASE + 2 * 4096 <= GL_K8_LDS_BYTES / 8, "private rings");
     extern __shared__ __attribute__((aligned(16))) char gl_lds[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)gl_lds;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, n = lane & 15;
-    const int r0 = blockIdx.x * 64;
+    const int r0 = blockIdx.x * (RT * 16);
     const int wt = blockIdx.y;                           // the workgroup's tile group along features
     const int kct = p.kc1;
 
-    floatx4 acc[4][4];
+    floatx4 acc[RT][4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < RT; ++r)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[r][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    // wavefront w owns chunks w, w + 8, ...; 20 KiB of LDS each: three slots of 4 activation fragments (those
+    // wavefront w owns chunks w, w + 8, ...; 20 KiB of LDS each: NX slots of RT activation fragments (those
     // come from HBM, the longer wait) and two slots of 4 weight fragments
     const int ni = (kct - wave + 7) / 8;
     const int cell_b = 4 * n + ((g + (n >> 2)) & 3);     // where this lane's operand piece sits in a fragment's LDS image
     const int piece = (lane - (lane >> 4)) & 3;          // lane L fetches row L / 4, 16-byte piece (L % 4 - L / 16) mod 4
     auto issue_x = [&](int i) {
         const int kc = wave + 8 * i;
-        const uint32_t sb = lds0 + wave * 20480 + (i % 3) * 4096;
+        const uint32_t sb = lds0 + wave * 20480 + (i % NX) * XSLOT;
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
+        for (int rt = 0; rt < RT; ++rt) {
             const int row = min(r0 + rt * 16 + (lane >> 2), p.rows - 1);
             g2lds16(p.x1 + (size_t)row * p.ld1 + kc * 32 + piece * 8, sb + rt * 1024);
         }
     };
     auto issue_w = [&](int i) {
         const int kc = wave + 8 * i;
-        const uint32_t sb = lds0 + wave * 20480 + 12288 + (i & 1) * 4096;
+        const uint32_t sb = lds0 + wave * 20480 + WBASE + (i & 1) * 4096;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int ft = min(wt * 4 + j, p.n_ftiles - 1);
             g2lds16(p.wp + ((size_t)ft * kct + kc) * 64 + lane, sb + j * 1024);
         }
     };
-    // issue order: x(0) x(1) w(0) | x(2) w(1) | x(3) w(2) | ...: when chunk i is due, x(i + 2) and w(i + 1)
-    // (8 loads) are the only ones issued after its own, and loads complete in the order issued
-    if (ni > 0) issue_x(0);
-    if (ni > 1) issue_x(1);
+    // issue order with three slots: x(0) x(1) w(0) | x(2) w(1) | x(3) w(2) | ...: when chunk i is due, x(i + 2) and
+    // w(i + 1) (8 loads) are the only ones issued after its own, and loads complete in the order issued.  With two: x(0)
+    // w(0) | x(1) w(1) | ...: the RT + 4 loads of chunk i + 1.
+    constexpr int AX = NX - 1;                           // chunks the activations run ahead
+#pragma unroll
+    for (int i = 0; i < AX; ++i)
+        if (i < ni) issue_x(i);
     if (ni > 0) issue_w(0);
     for (int i = 0; i < ni; ++i) {
         // (the slots written now were last read for chunk i - 1, whose MFMAs have been issued)
-        if (i + 2 < ni) issue_x(i + 2);
+        if (i + AX < ni) issue_x(i + AX);
         if (i + 1 < ni) issue_w(i + 1);
-        if (i + 2 < ni) wait_outstanding<8>();
+        if (i + AX < ni) wait_outstanding<RT + 4>();
         else if (i + 1 < ni) wait_outstanding<4>();
         else stage_wait();
-        const char* xb = gl_lds + wave * 20480 + (i % 3) * 4096;
-        const char* wb = gl_lds + wave * 20480 + 12288 + (i & 1) * 4096;
-        bf16x8 a[4], b[4];
+        const char* xb = gl_lds + wave * 20480 + (i % NX) * XSLOT;
+        const char* wb = gl_lds + wave * 20480 + WBASE + (i & 1) * 4096;
+        bf16x8 a[4], b[RT];
 #pragma unroll
         for (int j = 0; j < 4; ++j) a[j] = *(const bf16x8*)(wb + (j * 64 + lane) * 16);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) b[r] = *(const bf16x8*)(xb + (r * 64 + cell_b) * 16);
+        for (int r = 0; r < RT; ++r) b[r] = *(const bf16x8*)(xb + (r * 64 + cell_b) * 16);
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+        for (int r = 0; r < RT; ++r)
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[r][j] = mfma16(a[j], b[r], acc[r][j]);
     }
     __syncthreads();                                     // LDS is free
 
-    // eight partial tiles: everybody writes all 16 of its accumulators, wavefront r < 4 sums row tile r
-    floatx4* ex = (floatx4*)gl_lds;                      // [wave][4][4][64]
+    floatx4* ex = (floatx4*)gl_lds;                      // [wave][RT][4][64]
+    constexpr int PARTS = RT == 4 ? 8 : 4;
+    if constexpr (RT == 4) {
+        // eight partial tiles: everybody writes all 16 of its accumulators, wavefront r < 4 sums row tile r
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+        for (int r = 0; r < RT; ++r)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) ex[((wave * 4 + r) * 4 + j) * 64 + lane] = acc[r][j];
+            for (int j = 0; j < 4; ++j) ex[((wave * RT + r) * 4 + j) * 64 + lane] = acc[r][j];
+    } else {
+        // eight partial tiles of 24 KiB do not fit at once: the upper four wavefronts hand theirs to the lower four
+        if (wave >= 4) {
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) ex[(((wave - 4) * RT + r) * 4 + j) * 64 + lane] = acc[r][j];
+        }
+        __syncthreads();
+        if (wave < 4) {
+            // (read and rewritten by the same lanes)
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) ex[((wave * RT + r) * 4 + j) * 64 + lane] += acc[r][j];
+        }
+    }
     __syncthreads();
-    if (wave >= 4) return;
+    if (wave >= RT) return;
     floatx4 fin[1][4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        floatx4 t = ex[((0 * 4 + wave) * 4 + j) * 64 + lane];
+        floatx4 t = ex[((0 * RT + wave) * 4 + j) * 64 + lane];
 #pragma unroll
-        for (int w2 = 1; w2 < 8; ++w2) t += ex[((w2 * 4 + wave) * 4 + j) * 64 + lane];
+        for (int w2 = 1; w2 < PARTS; ++w2) t += ex[((w2 * RT + wave) * 4 + j) * 64 + lane];
         fin[0][j] = t;
     }
     gemm_epilogue<1, EPI>(p, fin, -1, wt, r0 + wave * 16, lane);
@@ -318,7 +345,10 @@ inline hipError_t gemm_lds_set_attributes()
     auto set = [&](const void* f, int bytes) {
         if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     };
-    if constexpr (EPI == EPI_RELU) set((const void*)gemm_bf16_k8_kernel<EPI>, GL_K8_LDS_BYTES);
+    if constexpr (EPI == EPI_RELU) {
+        set((const void*)gemm_bf16_k8_kernel<EPI>, GL_K8_LDS_BYTES);
+        set((const void*)gemm_bf16_k8_kernel<EPI, 6>, GL_K8_LDS_BYTES);
+    }
     set((const void*)gemm_bf16_xw_kernel<4, 1, 2, EPI, true>, GemmXwCfg<4, 1, 2, true>::LDS_BYTES);
     set((const void*)gemm_bf16_xw_kernel<4, 2, 1, EPI, true>, GemmXwCfg<4, 2, 1, true>::LDS_BYTES);
     return e;
