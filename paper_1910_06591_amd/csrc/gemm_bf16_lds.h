@@ -17,10 +17,10 @@
 //     end.  Activations go through a four-slot LDS ring with one barrier per stage of two chunks; a wavefront's
 //     weight fragments go straight into its registers.
 //   gemm_bf16_k8_kernel<EPI, RT> (long K, few output tiles: the linear layer after the torso): the eight wavefronts
-//     share one 64 x 64 (RT = 4) or 96 x 64 (RT = 6) tile and each takes every eighth chunk.  Nothing is shared between them, so each runs
-//     private rings in its own 20 KiB of LDS (three slots of activation fragments, two of weight fragments)
-//     with no barrier inside the K loop.  The eight partial tiles meet in LDS and four wavefronts finish one
-//     row tile each.  (Splitting K over workgroups instead costs more than it saves here: partial sums that
+//     share one 64 x 64 (RT = 4) or 96 x 64 (RT = 6) tile and each takes every eighth chunk.  Nothing is shared
+//     between them, so each runs private rings in its own 20 KiB of LDS (three slots of activation fragments, or two
+//     at 96 rows, and two of weight fragments) with no barrier inside the K loop.  The eight partial tiles meet in
+//     LDS and RT wavefronts finish one row tile each.  (Splitting K over workgroups instead costs more than it saves here: partial sums that
 //     cross the chip's L2 slices need device-scope fences, each of which writes back and invalidates a whole
 //     slice.)
 #pragma once

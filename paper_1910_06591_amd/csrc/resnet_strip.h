@@ -18,11 +18,11 @@
 // Weight packing: A fragments [feature tile][chunk][lane][8], k = tap * C + ci.
 //
 // Measured, 1024 images, us per launch, against the kernels that keep an input and an output map (resnet_blockfused.h,
-// resnet_convpool.h, resnet_convtile.h), a section's two blocks together: 64 channels on 36 x 48 915 -> 655, on 18 x 24
+// resnet_convpool.h, resnet_convtile.h), a section's two blocks together: 64 channels on 36 x 48 915 -> 635, on 18 x 24
 // 222 -> 135, on 9 x 12 82 -> 45; 128 channels on 18 x 24 680 -> 475, on 9 x 12 199 -> 123; 32 channels on 36 x 48 333 ->
-// 246, on 27 x 36 174 -> 111; 16 channels on 54 x 72 273 -> 253.  conv0 + pooling: 64 -> 128 on 36 x 48 339 -> 292, 128 ->
+// 240, on 27 x 36 174 -> 111; 16 channels on 54 x 72 273 -> 253.  conv0 + pooling: 64 -> 128 on 36 x 48 339 -> 292, 128 ->
 // 128 on 18 x 24 212 -> 126, 32 -> 64 on 36 x 48 120 -> 85, 16 -> 32 on 54 x 72 107 -> 77.
-// What bounds them now (64 channels on 36 x 48, cycles of a workgroup's 90 K): staging 25 K and the epilogue 23 K of
+// What bounds them now (64 channels on 36 x 48, cycles of a workgroup's 78 K): staging 15 K and the epilogue 22 K of
 // memory, the two convolutions 36 K for 18 K of MFMAs (two workgroups share the matrix cores); 0.9 GB of HBM traffic is
 // 150 us at the copy rate, the MFMAs 119 us.
 #pragma once
@@ -60,6 +60,23 @@ __device__ __forceinline__ int xcd_run(int idx, int total)
 {
     const int per = total >> 3, rem = total & 7, x = idx & 7;
     return x * per + min(x, rem) + (idx >> 3);
+}
+
+// Zeroes a map's border cells: cell 0 of every row and the one behind the last row, the first and the last row where
+// they lie outside the image, and (period > 0) every row between stacked images.
+template <int C>
+__device__ __forceinline__ void zero_borders(char* map, int PL, int P, int rows, bool top, bool bottom, int period, int tid)
+{
+    constexpr int NCG = C / 8, STEP = RS_THREADS / NCG;
+    const bf16x8 z = {};
+    char* plane = map + (tid % NCG) * PL * 16;
+    for (int r = tid / NCG; r <= rows; r += STEP) *(bf16x8*)(plane + r * P * 16) = z;
+    for (int c = tid / NCG; c < P; c += STEP) {
+        if (top) *(bf16x8*)(plane + c * 16) = z;
+        if (bottom) *(bf16x8*)(plane + ((rows - 1) * P + c) * 16) = z;
+        if (period > 0)
+            for (int r = period; r < rows - 1; r += period) *(bf16x8*)(plane + (r * P + c) * 16) = z;
+    }
 }
 
 // The lane number, worked out afresh: what follows from it is not hoisted over (and spilled across) the phases.
@@ -273,39 +290,50 @@ __global__ __launch_bounds__(RS_THREADS, 4) void strip_block_kernel(StripBlockAr
         return y >= 0 && y < p.H && im < nimg;
     };
 
-    // ---- R = ReLU(x) as bf16, zeros in the border cells; four items' loads before the first conversion ----
+    // ---- R = ReLU(x) as bf16 ----
+    // The strip's pixels (of all stacked images) are one run of memory, so an item's address is a running offset and
+    // only its cell needs a (row, column) walk; the border cells are zeroed apart (walked cell by cell with the border in
+    // it, the loop spent 25 K cycles of a workgroup against 15 K: 64 channels on 36 x 48, 334 -> 310 us).  All of a
+    // thread's loads, or half of them in fp32, are requested before the first conversion.
     {
         constexpr int UNR = X_BF16 ? 10 : 5, CSTEP = RS_THREADS / K::NCG;
         static_assert(RS_THREADS % K::NCG == 0, "a thread keeps its channel group");
-        const int cg = tid % K::NCG, cells = MR * P + 1;
-        RowWalk rw(tid / K::NCG, CSTEP, P);
-        for (int cell0 = tid / K::NCG; cell0 < cells; cell0 += UNR * CSTEP) {
+        const int cg = tid % K::NCG;
+        const int t0 = max(m0, 0), t1 = min(m0 + MR, p.H);      // image rows in the map (one image)
+        const int npx = stacked ? nimg * p.H * p.W : (t1 - t0) * p.W;
+        const char* src = (const char*)p.x_in + (b * img + (size_t)t0 * p.W * C) * (X_BF16 ? 2 : 4);
+        zero_borders<C>(rs_lds, PL, P, MR, m0 < 0, m0 + MR > p.H, stacked ? Hp : 0, tid);
+        RowWalk rw(tid / K::NCG, CSTEP, p.W);
+        int px = tid / K::NCG;
+        uint32_t from = (uint32_t)(px * C + cg * 8) * (X_BF16 ? 2 : 4);
+        char* const plane = rs_lds + (cg * PL + (t0 - m0) * P + 1) * 16;
+        for (; px < npx; px += UNR * CSTEP) {
             floatx4 lo[UNR], hi[UNR];
             bf16x8 v[UNR];
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                int im, y;
-                const bool in = image_row(rw.r, im, y) && rw.c > 0 && cell0 + u * CSTEP < cells;
-                const int o = im * (int)img + (y * p.W + rw.c - 1) * C + cg * 8;      // from image b
-                rw.next();
-                v[u] = bf16x8{};
-                lo[u] = hi[u] = floatx4{0.f, 0.f, 0.f, 0.f};
-                if (in) {
-                    if constexpr (X_BF16) {
-                        v[u] = *(const bf16x8*)((const __bf16*)p.x_in + b * img + o);
-                    } else {
-                        lo[u] = *(const floatx4*)((const float*)p.x_in + b * img + o);
-                        hi[u] = *(const floatx4*)((const float*)p.x_in + b * img + o + 4);
-                    }
+            for (int u = 0; u < UNR; ++u, from += CSTEP * C * (X_BF16 ? 2 : 4)) {
+                if (px + u * CSTEP >= npx) continue;
+                if constexpr (X_BF16) {
+                    v[u] = *(const bf16x8*)(src + from);
+                } else {
+                    lo[u] = *(const floatx4*)(src + from);
+                    hi[u] = *(const floatx4*)(src + from + 16);
                 }
             }
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
-                if (cell0 + u * CSTEP >= cells) continue;
+                int r = rw.r;
+                if (stacked) {                                   // a zero row between images
+#pragma unroll
+                    for (int k = 1; k < RS_MAX_STACK; ++k) r += rw.r >= k * p.H;
+                }
+                char* cell = plane + (r * P + rw.c) * 16;
+                rw.next();
+                if (px + u * CSTEP >= npx) continue;
                 const bf16x8 raw = X_BF16 ? v[u] : to_bf16x8(lo[u], hi[u]);
                 const bf16x4 l = relu_bf16x4(__builtin_shufflevector(raw, raw, 0, 1, 2, 3));
                 const bf16x4 h = relu_bf16x4(__builtin_shufflevector(raw, raw, 4, 5, 6, 7));
-                *(bf16x8*)(rs_lds + (size_t)(cg * PL + cell0 + u * CSTEP) * 16) = __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7);
+                *(bf16x8*)cell = __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7);
             }
         }
     }
@@ -471,24 +499,27 @@ __global__ __launch_bounds__(RS_THREADS, 4) void strip_pool_kernel(StripPoolArgs
     const int yc = max(2 * ph0 - p.pad_h, 0), yz = min(2 * (ph1 - 1) - p.pad_h + 3, p.H);      // convolution rows yc .. yz - 1
     const int m0 = yc - 1, rows = yz - yc, MR = rows + 2;
     const int PL = K::plane(MR, p.W);
-    const __bf16* img = p.in + (size_t)b * p.H * p.W * C;
-
     {
         constexpr int UNR = 10, CSTEP = RS_THREADS / K::NCG;
-        const int cg = tid % K::NCG, cells = MR * P + 1;
-        RowWalk rw(tid / K::NCG, CSTEP, P);
-        for (int cell0 = tid / K::NCG; cell0 < cells; cell0 += UNR * CSTEP) {
+        const int cg = tid % K::NCG;
+        const int t0 = max(m0, 0), t1 = min(m0 + MR, p.H), npx = (t1 - t0) * p.W;
+        const char* src = (const char*)(p.in + ((size_t)b * p.H + t0) * p.W * C);
+        zero_borders<C>(rs_lds, PL, P, MR, m0 < 0, m0 + MR > p.H, 0, tid);
+        RowWalk rw(tid / K::NCG, CSTEP, p.W);
+        int px = tid / K::NCG;
+        uint32_t from = (uint32_t)(px * C + cg * 8) * 2;
+        char* const plane = rs_lds + (cg * PL + (t0 - m0) * P + 1) * 16;
+        for (; px < npx; px += UNR * CSTEP) {
             bf16x8 v[UNR];
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                const int y = m0 + rw.r, x = rw.c - 1;
-                rw.next();
-                v[u] = bf16x8{};
-                if (cell0 + u * CSTEP < cells && y >= 0 && y < p.H && x >= 0) v[u] = *(const bf16x8*)(img + ((size_t)y * p.W + x) * C + cg * 8);
-            }
+            for (int u = 0; u < UNR; ++u, from += CSTEP * C * 2)
+                if (px + u * CSTEP < npx) v[u] = *(const bf16x8*)(src + from);
 #pragma unroll
-            for (int u = 0; u < UNR; ++u)
-                if (cell0 + u * CSTEP < cells) *(bf16x8*)(rs_lds + (size_t)(cg * PL + cell0 + u * CSTEP) * 16) = v[u];
+            for (int u = 0; u < UNR; ++u) {
+                char* cell = plane + (rw.r * P + rw.c) * 16;
+                rw.next();
+                if (px + u * CSTEP < npx) *(bf16x8*)cell = v[u];
+            }
         }
     }
     __syncthreads();
