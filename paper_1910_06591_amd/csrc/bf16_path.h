@@ -428,6 +428,27 @@ inline void bf16_repack(Bf16State* s, const float* d_w, int set, hipStream_t st)
                        (uint16_t*)(s->arena + s->o_pk[set]), s->tab_fb, n_fb, (float*)(s->arena + s->o_fb[set]));
 }
 
+// Workspace of the layer-by-layer ResNet for `rows` rows: byte offsets of the conv0 map (bf16), the pooled maps U and R
+// (bf16) and the residual stream x (fp32), and the bytes they take.  Between a section's fused blocks x lies over the
+// conv0 map and U, which are dead by then: the conv0 map alone is too small for it where a frame is one row or
+// column, because a pooled map is a quarter of it only up to the rounding of odd extents (1 x 5 -> 1 x 3).
+struct LwLayout { size_t c0 = 0, u = 0, r = 0, x = 0, end = 0; };
+inline LwLayout lw_layout(const Plan& p, size_t rows)
+{
+    size_t m0 = 0, m1 = 0;
+    for (const Section& sec : p.sections) {
+        m0 = std::max(m0, (size_t)sec.conv0.OH * sec.conv0.OW * sec.conv0.Cout);
+        m1 = std::max(m1, (size_t)sec.PH * sec.PW * sec.conv0.Cout);
+    }
+    auto al = [](size_t v) { return (v + 255) / 256 * 256; };
+    LwLayout l;
+    l.u = l.c0 + al(rows * m0 * 2);
+    l.r = l.u + al(rows * m1 * 2);
+    l.x = l.r + al(rows * m1 * 2);
+    l.end = l.x + al(rows * m1 * 4);
+    return l;
+}
+
 // d_w: the canonical weights, already on the device (set 0 is packed from them here).
 inline seed_status_t bf16_create(const Plan& p, const float* d_w, Bf16State** out, std::string& err)
 {
@@ -475,17 +496,11 @@ inline seed_status_t bf16_create(const Plan& p, const float* d_w, Bf16State** ou
         o_act[0] = off; off += al(mb * m * 2);
         o_act[1] = off; off += al(mb * m * 2);
     }
-    size_t o_lw[4] = {0, 0, 0, 0};
+    const size_t o_lw = off;
+    LwLayout lw_at;
     if (a.torso == SEED_TORSO_RESNET && s->torso_kind == TORSO_NONE) {
-        size_t m0 = 0, m1 = 0;
-        for (const Section& sec : p.sections) {
-            m0 = std::max(m0, (size_t)sec.conv0.OH * sec.conv0.OW * sec.conv0.Cout);
-            m1 = std::max(m1, (size_t)sec.PH * sec.PW * sec.conv0.Cout);
-        }
-        o_lw[0] = off; off += al(mb * m0 * 2);
-        o_lw[1] = off; off += al(mb * m1 * 2);
-        o_lw[2] = off; off += al(mb * m1 * 2);
-        o_lw[3] = off; off += al(mb * m1 * 4);
+        lw_at = lw_layout(p, mb);
+        off += lw_at.end;
     }
     const size_t o_feat = off; off += al(mb * s->ldf * 2);
     const size_t o_fcb = off; off += al(mb * s->ldfc * 2);
@@ -505,10 +520,10 @@ inline seed_status_t bf16_create(const Plan& p, const float* d_w, Bf16State** ou
     s->koff = (const int*)(s->arena + o_ko);
     s->act[0] = (__bf16*)(s->arena + o_act[0]);
     s->act[1] = (__bf16*)(s->arena + o_act[1]);
-    s->lw_c0 = (__bf16*)(s->arena + o_lw[0]);
-    s->lw_r = (__bf16*)(s->arena + o_lw[1]);
-    s->lw_u = (__bf16*)(s->arena + o_lw[2]);
-    s->lw_x = (float*)(s->arena + o_lw[3]);
+    s->lw_c0 = (__bf16*)(s->arena + o_lw + lw_at.c0);
+    s->lw_u = (__bf16*)(s->arena + o_lw + lw_at.u);
+    s->lw_r = (__bf16*)(s->arena + o_lw + lw_at.r);
+    s->lw_x = (float*)(s->arena + o_lw + lw_at.x);
     s->feat = (__bf16*)(s->arena + o_feat);
     s->fc_bf16 = (__bf16*)(s->arena + o_fcb);
     s->fc_f32 = (float*)(s->arena + o_fcf);
@@ -978,7 +993,7 @@ inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w
                                    need_r ? s->lw_r : nullptr, B, sec.conv0.OH, sec.conv0.OW, C, sec.PH, sec.PW, sec.pool_pad_h, sec.pool_pad_w);
             }
             // a residual block in one launch where the width has a fused kernel and a tile fits; x ping-pongs between
-            // lw_x and the (by now dead) conv0 map, since tiles read their neighbours' halos of the block's input
+            // lw_x and the (by now dead) conv0 map with U behind it, since tiles read their neighbours' halos of the block's input
             float* x_cur = s->lw_x;
             float* x_alt = (float*)s->lw_c0;
             for (int blk = 0; blk < 2; ++blk) {

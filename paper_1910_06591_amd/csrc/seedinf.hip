@@ -488,15 +488,13 @@ static size_t workspace_carve(const seed_infer* h, int B, char* base, WorkspaceP
         w.bact[1] = (__bf16*)take(rows * m * 2);
     }
     if (a.torso == SEED_TORSO_RESNET && b->torso_kind == TORSO_NONE) {
-        size_t m0 = 0, m1 = 0;
-        for (const Section& sec : p.sections) {
-            m0 = std::max(m0, (size_t)sec.conv0.OH * sec.conv0.OW * sec.conv0.Cout);
-            m1 = std::max(m1, (size_t)sec.PH * sec.PW * sec.conv0.Cout);
+        const LwLayout l = lw_layout(p, rows);
+        if (char* at = take(l.end)) {
+            w.lw_c0 = (__bf16*)(at + l.c0);
+            w.lw_u = (__bf16*)(at + l.u);
+            w.lw_r = (__bf16*)(at + l.r);
+            w.lw_x = (float*)(at + l.x);
         }
-        w.lw_c0 = (__bf16*)take(rows * m0 * 2);
-        w.lw_r = (__bf16*)take(rows * m1 * 2);
-        w.lw_u = (__bf16*)take(rows * m1 * 2);
-        w.lw_x = (float*)take(rows * m1 * 4);
     }
     w.feat = (__bf16*)take(rows * b->ldf * 2);
     w.fc_bf16 = (__bf16*)take(rows * b->ldfc * 2);

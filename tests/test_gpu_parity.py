@@ -549,3 +549,20 @@ def test_bf16_strip_kernels_stack_small_images(orc, label, over):
 def test_bf16_strip_kernels_at_the_edges_of_their_plans(orc, label, over, B):
     cfg = dict(wl.CONFIGS["C3"], label=f"strips: {label}", index=121, fc_units=32, **over)
     run_case(orc, cfg, B, "bf16")
+
+
+def test_bf16_one_row_frames_wider_than_a_strip(orc):
+    """Frames of one row: the residual stream between a section's blocks is larger than the conv0 map it lies over, so
+    the last rows of a large batch would meet the first rows' outputs if anything live lay behind it.  Every row sampled
+    equals the same row in a batch of its own, and the oracle."""
+    cfg = dict(wl.CONFIGS["C3"], label="one row of 1199 pixels", index=123, obs_h=1, obs_w=1199, sections=[16, 16], fc_units=32)
+    B, rows = 2048, [0, 1, 2, 3, 2044, 2045, 2046, 2047]
+    weights, batch = wl.make_weights(cfg), wl.make_batch(cfg, B)
+    net = seedinf.SeedInfer(seedinf.make_arch(cfg, max_batch=B), weights)
+    net.step(**to_device(batch))
+    big = net.read_intermediate(0, B).cpu().numpy()
+    net.step(**to_device({k: None if v is None else np.ascontiguousarray(v[rows]) for k, v in batch.items()}))
+    small = net.read_intermediate(0, len(rows)).cpu().numpy()
+    net.close()
+    np.testing.assert_array_equal(big[rows], small)
+    run_case(orc, cfg, len(rows), "bf16")
