@@ -114,6 +114,19 @@ struct ConvStackLayerDev { size_t wp_off; size_t koff_off; int kchunks; };
 // convolution + pooling kernel as well (LW_NONE: not packed that way)
 constexpr size_t LW_NONE = (size_t)-1;
 struct LwLayerDev { size_t wp_off; size_t ktab_off; int kchunks; size_t first_off = LW_NONE; };
+
+// layer-by-layer ResNet, the kernels a section may run on: fixed by the network, so searched for once per handle (a
+// search walks every cut of a map: with the tile kernels' searches in each step, one image of the 120x90 minimap took 209
+// us for 83 us of kernels, of 135 x 240 pooled pixels at 16 channels 779 for 126)
+struct TileCut { int h = 0, w = 0; };          // tile extents; 0: the layer has no such kernel, or no tile fits
+struct LwSectionPlan {
+    TileCut first, pool;                       // first_pool_kernel (pooled pixels), conv_pool_kernel (pooled pixels)
+    TileCut block, conv;                       // resblock_fused_kernel, conv_tile_kernel
+    int tiles = 0; long tile_cells = 0;        // the tile kernels': workgroups an image, cells a block's convolutions walk
+    StripBlockPlan strip_block;
+    StripPoolPlan strip_pool;
+    bool strips = false;                       // the strip kernels cover conv0 + pooling and the blocks
+};
 inline bool first_pool_supported(const ConvLayer& c)
 {
     return (c.Cin <= 4 || c.Cin == 8 || c.Cin == 16) && (c.Cout == 16 || c.Cout == 32 || c.Cout == 64);
@@ -154,6 +167,7 @@ struct Bf16State {
     int kc_fc = 0, ft_fc = 0, kc1_lstm = 0, ft_hid = 0;
     std::vector<ConvStackLayerDev> stack;
     std::vector<LwLayerDev> lw;
+    std::vector<LwSectionPlan> lw_plan;        // per section
     const int* koff = nullptr;
     // layer-by-layer ResNet workspace: conv0 output at input resolution; R / U conv inputs; x residual stream
     __bf16* lw_c0 = nullptr; __bf16* lw_r = nullptr; __bf16* lw_u = nullptr; float* lw_x = nullptr;
@@ -428,6 +442,8 @@ inline void bf16_repack(Bf16State* s, const float* d_w, int set, hipStream_t st)
                        (uint16_t*)(s->arena + s->o_pk[set]), s->tab_fb, n_fb, (float*)(s->arena + s->o_fb[set]));
 }
 
+inline LwSectionPlan plan_lw_section(const Section& sec, const LwLayerDev* d, bool first);
+
 // Workspace of the layer-by-layer ResNet for `rows` rows: byte offsets of the conv0 map (bf16), the pooled maps U and R
 // (bf16) and the residual stream x (fp32), and the bytes they take.  Between a section's fused blocks x lies over the
 // conv0 map and U, which are dead by then: the conv0 map alone is too small for it where a frame is one row or
@@ -471,6 +487,8 @@ inline seed_status_t bf16_create(const Plan& p, const float* d_w, Bf16State** ou
     s->kc_fc = o.kc_fc; s->ft_fc = o.ft_fc; s->kc1_lstm = o.kc1_lstm; s->ft_hid = o.ft_hid;
     s->stack = o.stack;
     s->lw = o.lw;
+    if (a.torso == SEED_TORSO_RESNET && s->torso_kind == TORSO_NONE)
+        for (size_t si = 0; si < p.sections.size(); ++si) s->lw_plan.push_back(plan_lw_section(p.sections[si], &s->lw[5 * si], si == 0));
     s->pk_bytes = o.pk.size() * 2;                // (one 16-bit element per table entry)
     s->fb_bytes = o.fb.size() * 4;
     const int F = a.fc_units;
@@ -715,27 +733,11 @@ inline void launch_lw_conv(hipStream_t st, const LwConvArgs& c, int ft, bool u8)
     else by_ft(std::false_type{});
 }
 
-// The first layer with its pooling as one launch (uint8 frame -> fp32 x and, if r is given, ReLU(x) as bf16);
-// false when the layer has no fused kernel, and nothing was launched.
-inline bool launch_first_pool(hipStream_t st, const LwLayerDev& d, const bf16x8* wp_conv, const float* d_w, const Section& sec, int B,
-                              const uint8_t* obs, float* x, __bf16* r)
+// Calls go(output channels, planes per frame cell) for the first layer's fused kernel; false where it has none.
+template <class F>
+inline bool first_pool_by_layer(const LwLayerDev& d, const ConvLayer& c, F go)
 {
-    const ConvLayer& c = sec.conv0;
     if (d.first_off == LW_NONE) return false;
-    auto go = [&](auto cc, auto cellc) -> bool {
-        constexpr int CC = decltype(cc)::value, CELL = decltype(cellc)::value;
-        using K = FirstPoolCfg<CC, CELL>;
-        FirstPoolArgs a{};
-        if (!K::choose(sec.PH, sec.PW, a.PTH, a.PTW)) return false;
-        if (CELL != 4 && d.kchunks != K::KCH) return false;
-        a.obs = obs; a.wp = wp_conv + d.first_off / 8; a.bias = d_w + c.b_off; a.scale = 1.0f / 255.0f;
-        a.x = x; a.r = r;
-        a.B = B; a.H = c.H; a.W = c.W; a.Cin = c.Cin; a.PH = sec.PH; a.PW = sec.PW; a.pad_h = sec.pool_pad_h; a.pad_w = sec.pool_pad_w;
-        a.tiles_y = (sec.PH + a.PTH - 1) / a.PTH; a.tiles_x = (sec.PW + a.PTW - 1) / a.PTW;
-        hipLaunchKernelGGL((first_pool_kernel<CC, CELL>), dim3((unsigned)((long)B * a.tiles_y * a.tiles_x)), dim3(FP_THREADS),
-                           K::lds_bytes(a.PTH, a.PTW), st, a);
-        return true;
-    };
     auto by_cell = [&](auto cc) -> bool {
         if (c.Cin <= 4) return go(cc, std::integral_constant<int, 4>{});
         if (c.Cin == 8) return go(cc, std::integral_constant<int, 8>{});
@@ -750,8 +752,30 @@ inline bool launch_first_pool(hipStream_t st, const LwLayerDev& d, const bf16x8*
     }
 }
 
+// The first layer with its pooling as one launch (uint8 frame -> fp32 x and, if r is given, ReLU(x) as bf16; x as bf16
+// in r where x is nullptr); false when the layer has no fused kernel, and nothing was launched.
+inline bool launch_first_pool(hipStream_t st, const LwLayerDev& d, const bf16x8* wp_conv, const float* d_w, const Section& sec,
+                              const TileCut& cut, int B, const uint8_t* obs, float* x, __bf16* r)
+{
+    const ConvLayer& c = sec.conv0;
+    if (!cut.h) return false;
+    return first_pool_by_layer(d, c, [&](auto cc, auto cellc) -> bool {
+        constexpr int CC = decltype(cc)::value, CELL = decltype(cellc)::value;
+        using K = FirstPoolCfg<CC, CELL>;
+        FirstPoolArgs a{};
+        a.PTH = cut.h; a.PTW = cut.w;
+        a.obs = obs; a.wp = wp_conv + d.first_off / 8; a.bias = d_w + c.b_off; a.scale = 1.0f / 255.0f;
+        a.x = x; a.r = r;
+        a.B = B; a.H = c.H; a.W = c.W; a.Cin = c.Cin; a.PH = sec.PH; a.PW = sec.PW; a.pad_h = sec.pool_pad_h; a.pad_w = sec.pool_pad_w;
+        a.tiles_y = (sec.PH + a.PTH - 1) / a.PTH; a.tiles_x = (sec.PW + a.PTW - 1) / a.PTW;
+        hipLaunchKernelGGL((first_pool_kernel<CC, CELL>), dim3((unsigned)((long)B * a.tiles_y * a.tiles_x)), dim3(FP_THREADS),
+                           K::lds_bytes(a.PTH, a.PTW), st, a);
+        return true;
+    });
+}
+
 // conv0 of a later section with its pooling as one launch (bf16 NHWC map -> fp32 x and, if r is given, ReLU(x) as
-// bf16); false when the channel pair has no fused kernel or no tile fits, and nothing was launched.
+// bf16); false when the channel pair has no fused kernel, and nothing was launched.
 template <class F>
 inline bool conv_pool_by_channels(int cin, int cout, F go)
 {
@@ -770,15 +794,16 @@ inline bool conv_pool_by_channels(int cin, int cout, F go)
     }
 }
 
-inline bool launch_conv_pool(hipStream_t st, const LwLayerDev& d, const bf16x8* wp_conv, const float* d_w, const Section& sec, int B,
-                             const __bf16* in, float* x, __bf16* r)
+inline bool launch_conv_pool(hipStream_t st, const LwLayerDev& d, const bf16x8* wp_conv, const float* d_w, const Section& sec,
+                             const TileCut& cut, int B, const __bf16* in, float* x, __bf16* r)
 {
     const ConvLayer& c = sec.conv0;
+    if (!cut.h) return false;
     return conv_pool_by_channels(c.Cin, c.Cout, [&](auto ci, auto co) -> bool {
         constexpr int CIN = decltype(ci)::value, COUT = decltype(co)::value;
         using CP = ConvPoolCfg<CIN, COUT>;
         ConvPoolArgs a{};
-        if (!CP::choose(sec.PH, sec.PW, a.PTH, a.PTW)) return false;
+        a.PTH = cut.h; a.PTW = cut.w;
         a.in = in; a.wp = wp_conv + d.wp_off / 8; a.bias = d_w + c.b_off; a.x = x; a.r = r;
         a.B = B; a.H = c.H; a.W = c.W; a.PH = sec.PH; a.PW = sec.PW; a.pad_h = sec.pool_pad_h; a.pad_w = sec.pool_pad_w;
         a.tiles_y = (sec.PH + a.PTH - 1) / a.PTH; a.tiles_x = (sec.PW + a.PTW - 1) / a.PTW; a.kchunks = d.kchunks;
@@ -808,33 +833,24 @@ inline bool conv_tile_preferred(const ConvLayer& c) { return c.Cin == c.Cout && 
 // pitch-wide regions (conflict-free map fragments) where measured faster: 64 channels on maps larger than 18 x 24
 inline bool resblock_flat(const ConvLayer& c) { return c.Cin == 64 && c.H * c.W > 18 * 24; }
 
-// Whether launch_resblock takes this block: every width with a kernel whose tile fits.  Measured at 1024 images
+// launch_resblock takes every width with a kernel whose tile fits.  Measured at 1024 images
 // against the two-launch form (LDS-tiled convolution kernel twice): 16 ch 54 x 72 149 vs 308 us; 32 ch 36 x 48 175
 // vs 284, 27 x 36 and smaller 52 vs 70; 64 ch 36 x 48 552 vs 640, 18 x 24 and 9 x 12 84 vs 124; 128 ch (18 x 24 and
 // 9 x 12, mean) 305 vs 412.
-inline bool resblock_fusable(const ConvLayer& ca, const ConvLayer& cb)
-{
-    const int C = ca.Cin;
-    if (ca.Cout != C || cb.Cin != C || cb.Cout != C || ca.H != cb.H || ca.W != cb.W) return false;
-    return resblock_by_width(C, [&](auto cc) {
-        int th, tw;
-        return ResBlockCfg<decltype(cc)::value>::choose(ca.H, ca.W, resblock_flat(ca), th, tw);
-    });
-}
 
 // One residual block (two 3x3 convolutions C -> C over an H x W map) as a single launch; false when the width has
-// no fused kernel or no tile fits, and nothing was launched.
+// no fused kernel, and nothing was launched.
 inline bool launch_resblock(hipStream_t st, const LwLayerDev& da, const LwLayerDev& db, const bf16x8* wp_conv, const float* d_w,
-                            const ConvLayer& ca, const ConvLayer& cb, int B, const float* x_in, float* x_out, __bf16* y, int y_relu,
-                            int ldy)
+                            const ConvLayer& ca, const ConvLayer& cb, const TileCut& cut, int B, const float* x_in, float* x_out,
+                            __bf16* y, int y_relu, int ldy)
 {
-    if (!resblock_fusable(ca, cb)) return false;
+    if (!cut.h) return false;
     return resblock_by_width(ca.Cin, [&](auto cc) -> bool {
         constexpr int CC = decltype(cc)::value;
         using K = ResBlockCfg<CC>;
         ResBlockArgs r{};
         r.flat = resblock_flat(ca);
-        if (!K::choose(ca.H, ca.W, r.flat != 0, r.TH, r.TW)) return false;
+        r.TH = cut.h; r.TW = cut.w;
         r.x_in = x_in; r.wpa = wp_conv + da.wp_off / 8; r.wpb = wp_conv + db.wp_off / 8;
         r.bias_a = d_w + ca.b_off; r.bias_b = d_w + cb.b_off;
         r.x_out = x_out; r.y = y; r.y_relu = y_relu; r.ldy = ldy;
@@ -847,16 +863,17 @@ inline bool launch_resblock(hipStream_t st, const LwLayerDev& da, const LwLayerD
 }
 
 // One convolution of a residual block as a launch of its own over large LDS tiles (conv_tile_kernel); false when
-// the width has no such kernel or no tile fits, and nothing was launched.
-inline bool launch_conv_tile(hipStream_t st, const LwLayerDev& d, const bf16x8* wp_conv, const float* d_w, const ConvLayer& c, int B,
-                             const void* in, bool in_f32, const float* resid, float* x_out, __bf16* y, int y_relu, int ldy)
+// the width has no such kernel, and nothing was launched.
+inline bool launch_conv_tile(hipStream_t st, const LwLayerDev& d, const bf16x8* wp_conv, const float* d_w, const ConvLayer& c,
+                             const TileCut& cut, int B, const void* in, bool in_f32, const float* resid, float* x_out, __bf16* y,
+                             int y_relu, int ldy)
 {
-    if (c.Cin != c.Cout) return false;
+    if (!cut.h) return false;
     auto go = [&](auto cc) -> bool {
         constexpr int CC = decltype(cc)::value;
         using CT = ConvTileCfg<CC>;
         ConvTileArgs a{};
-        if (d.kchunks != (9 * CC + 31) / 32 || !CT::choose(c.H, c.W, a.TH, a.TW)) return false;
+        a.TH = cut.h; a.TW = cut.w;
         a.in = in; a.wp = wp_conv + d.wp_off / 8; a.bias = d_w + c.b_off; a.resid = resid; a.x_out = x_out; a.y = y;
         a.y_relu = y_relu; a.ldy = ldy;
         a.B = B; a.H = c.H; a.W = c.W; a.kchunks = d.kchunks;
@@ -884,53 +901,110 @@ inline bool strip_by_width(int C, F go)
     }
 }
 
-// Whether a section's residual blocks run on the strip kernels.
-inline bool strip_blocks_fit(const Section& sec, int B, int n_cu)
+// The kernels that cover a section, d: its five convolutions.
+inline LwSectionPlan plan_lw_section(const Section& sec, const LwLayerDev* d, bool first)
 {
-    const int C = sec.conv0.Cout;
-    return strip_by_width(C, [&](auto cc) {
-        StripBlockPlan<decltype(cc)::value> pl;
-        return pl.choose(B, sec.PH, sec.PW, n_cu);
+    LwSectionPlan pl;
+    const ConvLayer& c = sec.conv0;
+    const ConvLayer& ba = sec.block[0];
+    auto cut = [](TileCut& t, auto choose) {
+        int h, w;
+        if (choose(h, w)) t = {h, w};
+        return true;
+    };
+    if (first)
+        first_pool_by_layer(d[0], c, [&](auto cc, auto cellc) {
+            using K = FirstPoolCfg<decltype(cc)::value, decltype(cellc)::value>;
+            if (decltype(cellc)::value != 4 && d[0].kchunks != K::KCH) return false;
+            return cut(pl.first, [&](int& h, int& w) { return K::choose(sec.PH, sec.PW, h, w); });
+        });
+    else
+        conv_pool_by_channels(c.Cin, c.Cout, [&](auto ci, auto co) {
+            return cut(pl.pool, [&](int& h, int& w) { return ConvPoolCfg<decltype(ci)::value, decltype(co)::value>::choose(sec.PH, sec.PW, h, w); });
+        });
+    resblock_by_width(ba.Cin, [&](auto cc) {
+        using K = ResBlockCfg<decltype(cc)::value>;
+        const bool flat = resblock_flat(ba);
+        cut(pl.block, [&](int& h, int& w) { return K::choose(ba.H, ba.W, flat, h, w); });
+        if (!pl.block.h) return false;
+        pl.tiles = ((ba.H + pl.block.h - 1) / pl.block.h) * ((ba.W + pl.block.w - 1) / pl.block.w);
+        pl.tile_cells = (long)pl.tiles * K::tile_cells(pl.block.h, pl.block.w, flat);
+        return true;
     });
+    if (conv_tile_preferred(ba) && d[1].kchunks == (9 * 128 + 31) / 32) {
+        cut(pl.conv, [&](int& h, int& w) { return ConvTileCfg<128>::choose(ba.H, ba.W, h, w); });
+        if (pl.conv.h) {
+            pl.tiles = ((ba.H + pl.conv.h - 1) / pl.conv.h) * ((ba.W + pl.conv.w - 1) / pl.conv.w);
+            pl.tile_cells = (long)pl.tiles * 2 * ((pl.conv.h * pl.conv.w + 15) / 16 * 16);
+        }
+    }
+    const bool blocks = strip_by_width(ba.Cin, [&](auto cc) { return pl.strip_block.choose<decltype(cc)::value>(ba.H, ba.W); });
+    // (conv0 on strips: a workgroup per Cin output channels, each staging the input)
+    const bool conv0 = first ? pl.first.h > 0 : (c.Cout == c.Cin || c.Cout == 2 * c.Cin) && strip_by_width(c.Cin, [&](auto cc) {
+        return pl.strip_pool.choose<decltype(cc)::value>(c.H, c.W, sec.PH, sec.pool_pad_h);
+    });
+    pl.strips = blocks && conv0;
+    return pl;
+}
+
+// Whether a section's batch runs on the strip kernels; else on the tile kernels, with the same results.  Measured at 1 to
+// 256 images, the two blocks, tiles -> strips, us:
+// * Full-width strips get thin on wide maps and recompute their halo rows: where they walk more than 1.3 times the
+//   tiles' cells tiles win (256 images: 64 channels on 81 x 108, one row a strip, 1.6 times, 1107 -> 1605; 32 on 90 x 200,
+//   1.38, 774 -> 843; below the line 64 channels on 72 x 96, 1.23, 888 -> 901, on 63 x 84, 1.05, 662 -> 583), or at 128
+//   channels, whose tiles recompute nothing but carry U through memory, 1.5 times (36 x 48, 1.61, 678 -> 718; 27 x 36,
+//   1.31, 355 -> 324); except at 64 channels and up while every strip has a compute unit of its own (1 image: 64
+//   channels on 81 x 108 35 -> 30, 128 on 40 x 54 95 -> 44).
+// * A strip mostly holds two or more tiles, so with few images tiles use more of the chip (16 images: 64 channels on 36
+//   x 48 36 -> 47, 32 on 72 x 96 31 -> 38) and strips win from about 3/4 of the compute units on (32 channels on 27 x 36,
+//   192 strips: 42 -> 37; 64 on 36 x 48, 256: 84 -> 58); with less than two tiles to a strip at 16 and 32 channels, where
+//   a strip is mostly staging and epilogue, from two strips per unit on (32 on 54 x 72, 320 strips: 49 -> 53, 1280: 173 ->
+//   145).
+// * One strip for one tile, and 128 channels (two launches instead of four), are faster at any batch (1 image: 64 channels on
+//   9 x 12 23 -> 18, 128 on 18 x 24 82 -> 61).
+inline bool strips_preferred(const LwSectionPlan& pl, int C, int B, int n_cu)
+{
+    if (!pl.strips || !pl.block.h) return pl.strips;
+    const long strips = pl.strip_block.strips, groups = B * strips;
+    if (10 * pl.strip_block.cells > (pl.conv.h ? 15 : 13) * pl.tile_cells) return C >= 64 && groups <= n_cu;
+    if (C == 128 || strips >= pl.tiles) return true;
+    return groups >= (C == 64 || 2 * strips <= pl.tiles ? n_cu * 3 / 4 : 2 * n_cu);
 }
 
 // Both residual blocks of a section: xb (bf16, the pooled map) -> y; x is the fp32 stream between them.
-inline void launch_strip_blocks(hipStream_t st, const LwLayerDev* d, const bf16x8* wp_conv, const float* d_w, const Section& sec, int B,
-                                int n_cu, const __bf16* xb, float* x, __bf16* y, int y_relu, int ldy)
+inline void launch_strip_blocks(hipStream_t st, const LwLayerDev* d, const bf16x8* wp_conv, const float* d_w, const Section& sec,
+                                const StripBlockPlan& pl, int B, int n_cu, const __bf16* xb, float* x, __bf16* y, int y_relu, int ldy)
 {
     strip_by_width(sec.conv0.Cout, [&](auto cc) {
         constexpr int CC = decltype(cc)::value;
-        StripBlockPlan<CC> pl;
-        if (!pl.choose(B, sec.PH, sec.PW, n_cu)) return false;
         StripBlockArgs a{};
-        a.B = B; a.H = sec.PH; a.W = sec.PW; a.TH = pl.TH; a.strips = pl.strips; a.stack = pl.stack; a.nblk = pl.nblk;
-        a.groups = pl.stack > 1 ? (B + pl.stack - 1) / pl.stack : B * pl.strips;
+        a.B = B; a.H = sec.PH; a.W = sec.PW; a.TH = pl.TH; a.strips = pl.strips; a.nblk = pl.blocks();
+        a.stack = pl.stack<CC>(B, sec.PH, sec.PW, n_cu);
+        a.groups = a.stack > 1 ? (B + a.stack - 1) / a.stack : B * pl.strips;
         a.x_out = x; a.y_relu = y_relu; a.ldy = ldy;
+        const int rows = a.stack > 1 ? a.stack * (sec.PH + 1) - 1 : pl.conv_a_rows(pl.TH, pl.strips);
+        const size_t lds = StripCfg<CC>::lds_bytes(rows + 2, sec.PW);
         auto weights = [&](int at, int conv) { a.wp[at] = wp_conv + d[conv].wp_off / 8; a.bias[at] = d_w + sec.block[conv].b_off; };
-        for (int i = 0; i < 2 * pl.nblk; ++i) weights(i, i);
+        for (int i = 0; i < 2 * a.nblk; ++i) weights(i, i);
         a.x_in = xb;
-        a.y = pl.nblk == 2 ? y : nullptr;
-        hipLaunchKernelGGL((strip_block_kernel<CC, true>), dim3(a.groups), dim3(RS_THREADS), pl.lds, st, a);
-        if (pl.nblk == 1) {
+        a.y = a.nblk == 2 ? y : nullptr;
+        hipLaunchKernelGGL((strip_block_kernel<CC, true>), dim3(a.groups), dim3(RS_THREADS), lds, st, a);
+        if (a.nblk == 1) {
             weights(0, 2); weights(1, 3);
             a.x_in = x; a.x_out = nullptr; a.y = y;
-            hipLaunchKernelGGL((strip_block_kernel<CC, false>), dim3(a.groups), dim3(RS_THREADS), pl.lds, st, a);
+            hipLaunchKernelGGL((strip_block_kernel<CC, false>), dim3(a.groups), dim3(RS_THREADS), lds, st, a);
         }
         return true;
     });
 }
 
-// conv0 of a later section with its pooling on the strip kernel (bf16 NHWC map -> x as bf16); false when the channel
-// pair has no such kernel or no strip fits, and nothing was launched.
-inline bool launch_strip_pool(hipStream_t st, const LwLayerDev& d, const bf16x8* wp_conv, const float* d_w, const Section& sec, int B,
-                              const __bf16* in, __bf16* x)
+// conv0 of a later section with its pooling on the strip kernel (bf16 NHWC map -> x as bf16).
+inline void launch_strip_pool(hipStream_t st, const LwLayerDev& d, const bf16x8* wp_conv, const float* d_w, const Section& sec,
+                              const StripPoolPlan& pl, int B, const __bf16* in, __bf16* x)
 {
     const ConvLayer& c = sec.conv0;
-    if (c.Cout != c.Cin && c.Cout != 2 * c.Cin) return false;      // (a workgroup per Cin output channels, each staging the input)
-    return strip_by_width(c.Cin, [&](auto cc) {
+    strip_by_width(c.Cin, [&](auto cc) {
         constexpr int CC = decltype(cc)::value;
-        StripPoolPlan<CC> pl;
-        if (!pl.choose(c.H, c.W, sec.PH, sec.pool_pad_h)) return false;
         StripPoolArgs a{};
         a.in = in; a.wp = wp_conv + d.wp_off / 8; a.bias = d_w + c.b_off; a.x = x;
         a.B = B; a.H = c.H; a.W = c.W; a.PH = sec.PH; a.PW = sec.PW; a.pad_h = sec.pool_pad_h; a.pad_w = sec.pool_pad_w; a.COUT = c.Cout;
@@ -968,21 +1042,22 @@ inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w
                 const int ft = nft % 4 == 0 ? 4 : (nft % 2 == 0 ? 2 : 1);
                 launch_lw_conv(st, ca, ft, u8);
             };
-            // conv0 + pooling, then both blocks, on the strip kernels where the section's strips fit
-            if (strip_blocks_fit(sec, B, s->n_cu) &&
-                (si == 0 ? launch_first_pool(st, s->lw[li], W.wp_conv, d_w, sec, B, obs, nullptr, s->lw_u)
-                         : launch_strip_pool(st, s->lw[li], W.wp_conv, d_w, sec, B, (const __bf16*)in, s->lw_u))) {
-                launch_strip_blocks(st, &s->lw[li + 1], W.wp_conv, d_w, sec, B, s->n_cu, s->lw_u, s->lw_x, last_sec ? s->feat : s->lw_r,
-                                    last_sec ? 1 : 0, last_sec ? s->ldf : 0);
+            const LwSectionPlan& pl = s->lw_plan[si];
+            // conv0 + pooling, then both blocks, on the strip kernels
+            if (strips_preferred(pl, sec.conv0.Cout, B, s->n_cu)) {
+                if (si == 0) launch_first_pool(st, s->lw[li], W.wp_conv, d_w, sec, pl.first, B, obs, nullptr, s->lw_u);
+                else launch_strip_pool(st, s->lw[li], W.wp_conv, d_w, sec, pl.strip_pool, B, (const __bf16*)in, s->lw_u);
+                launch_strip_blocks(st, &s->lw[li + 1], W.wp_conv, d_w, sec, pl.strip_block, B, s->n_cu, s->lw_u, s->lw_x,
+                                    last_sec ? s->feat : s->lw_r, last_sec ? 1 : 0, last_sec ? s->ldf : 0);
                 li += 5;
                 in = s->lw_r;
                 continue;
             }
             // only the layer-by-layer block convolutions read R; a fused block takes ReLU(x) itself
-            const bool need_r = !resblock_fusable(sec.block[0], sec.block[1]);
-            if (si == 0 && launch_first_pool(st, s->lw[li], W.wp_conv, d_w, sec, B, obs, s->lw_x, need_r ? s->lw_r : nullptr)) {
+            const bool need_r = !pl.block.h;
+            if (si == 0 && launch_first_pool(st, s->lw[li], W.wp_conv, d_w, sec, pl.first, B, obs, s->lw_x, need_r ? s->lw_r : nullptr)) {
                 ++li;
-            } else if (si > 0 && !need_r && launch_conv_pool(st, s->lw[li], W.wp_conv, d_w, sec, B, (const __bf16*)in, s->lw_x, nullptr)) {
+            } else if (si > 0 && !need_r && launch_conv_pool(st, s->lw[li], W.wp_conv, d_w, sec, pl.pool, B, (const __bf16*)in, s->lw_x, nullptr)) {
                 // (not when R is wanted: it would land in lw_r, which is this layer's input)
                 ++li;
             } else {
@@ -1003,25 +1078,18 @@ inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w
                 const int y_relu = to_next ? 0 : 1, ldy = closing ? s->ldf : 0;
                 // (two launches over larger tiles where the one-launch block is bound by operand delivery; conv_b adds
                 // and writes x in place: it reads no pixel of x but its own)
-                if (conv_tile_preferred(sec.block[2 * blk]) &&
-                    launch_conv_tile(st, s->lw[li], W.wp_conv, d_w, sec.block[2 * blk], B, x_cur, true, nullptr, nullptr, s->lw_u, 1, 0)) {
-                    if (!launch_conv_tile(st, s->lw[li + 1], W.wp_conv, d_w, sec.block[2 * blk + 1], B, s->lw_u, false, x_cur,
-                                          blk == 0 ? x_cur : nullptr, blk == 0 ? nullptr : y, y_relu, ldy)) {
-                        err = "residual block: second convolution has no tile kernel";
-                        return SEED_ERR_DEVICE;
-                    }
+                if (launch_conv_tile(st, s->lw[li], W.wp_conv, d_w, sec.block[2 * blk], pl.conv, B, x_cur, true, nullptr, nullptr, s->lw_u,
+                                     1, 0)) {
+                    launch_conv_tile(st, s->lw[li + 1], W.wp_conv, d_w, sec.block[2 * blk + 1], pl.conv, B, s->lw_u, false, x_cur,
+                                     blk == 0 ? x_cur : nullptr, blk == 0 ? nullptr : y, y_relu, ldy);
                     li += 2;
                     continue;
                 }
-                if (launch_resblock(st, s->lw[li], s->lw[li + 1], W.wp_conv, d_w, sec.block[2 * blk], sec.block[2 * blk + 1], B, x_cur,
+                if (launch_resblock(st, s->lw[li], s->lw[li + 1], W.wp_conv, d_w, sec.block[2 * blk], sec.block[2 * blk + 1], pl.block, B, x_cur,
                                     blk == 0 ? x_alt : nullptr, blk == 0 ? nullptr : y, y_relu, ldy)) {
                     li += 2;
                     if (blk == 0) std::swap(x_cur, x_alt);
                     continue;
-                }
-                if (x_cur != s->lw_x) {                             // unreachable: both blocks of a section have one shape
-                    err = "residual blocks of one section differ in shape";
-                    return SEED_ERR_DEVICE;
                 }
                 conv(sec.block[2 * blk], s->lw_r, false, nullptr, nullptr, s->lw_u, 1, 0);
                 conv(sec.block[2 * blk + 1], s->lw_u, false, s->lw_x, s->lw_x, y, y_relu, ldy);

@@ -53,6 +53,11 @@ struct ResBlockCfg {
     // cells of a map plane, in whole 256 bytes; walked flat, the last tile's taps reach two cells past the map
     __host__ __device__ static constexpr int plane(int rows, int pitch, bool flat) { return (rows * pitch + (flat ? 2 : 0) + 15) / 16 * 16; }
     static size_t lds_bytes(int TH, int TW, bool flat) { return (size_t)NCG * (plane(TH + 4, TW + 4, flat) + plane(TH + 2, TW + 2, flat)) * 16; }
+    // cells of whole pixel tiles that both convolutions of a workgroup's tile walk
+    static constexpr int tile_cells(int th, int tw, bool flat)
+    {
+        return ((th + 2) * (tw + (flat ? 4 : 2)) + 15) / 16 * 16 + (th * (tw + (flat ? 2 : 0)) + 15) / 16 * 16;
+    }
     // tile extents for an H x W map: the cheapest cut whose conv_a region fits a workgroup and whose maps fit LDS
     static bool choose(int H, int W, bool flat, int& TH, int& TW)
     {

@@ -219,39 +219,41 @@ struct StripBlockArgs {
     int stack, nblk, groups;           // blocks in this launch (2: whole images only); workgroups
 };
 
-template <int C>
 struct StripBlockPlan {
-    using K = StripCfg<C>;
-    int TH = 0, strips = 0, stack = 1, nblk = 1;
-    size_t lds = 0;
+    int TH = 0, strips = 0;            // TH == 0: no strip fits
+    long cells = 0;                    // map cells the two convolutions of a block walk over all strips
     // Rows per strip: the cut with the least work (tiles per wavefront, both convolutions, the halo row that
-    // conv_a computes on each inner side included) that fits.  Whole images run both blocks in one launch: no
-    // halo, and x' is read back by the lanes that wrote it.  Small images are stacked while there are workgroups
-    // enough for two per compute unit: a lone 9 x 12 map gives a wavefront two to four tiles per weight fragment.
-    bool choose(int B, int H, int W, int n_cu)
+    // conv_a computes on each inner side included) that fits.
+    template <int C>
+    bool choose(int H, int W)
     {
+        using K = StripCfg<C>;
         long best = -1;
         for (int ny = 1; ny <= H; ++ny) {
-            const int th = (H + ny - 1) / ny;
-            if ((th - 1) * ny >= H) continue;               // (the same rows with a smaller ny)
-            const int ns = (H + th - 1) / th;
-            const int ra = ns == 1 ? th : (ns == 2 ? th + 1 : th + 2);
+            const int th = (H + ny - 1) / ny, ns = (H + th - 1) / th;
+            const int ra = conv_a_rows(th, ns);
             if (!K::fits(ra, ra + 2, W)) continue;
-            const long cost = (long)ns * (K::tiles(ra, W) + K::tiles(th, W) + 2 * K::NPG);
-            if (best < 0 || cost < best) { best = cost; TH = th; strips = ns; }
+            const long tiles = (long)ns * (K::tiles(ra, W) + K::tiles(th, W)), cost = tiles + (long)ns * 2 * K::NPG;
+            if (best < 0 || cost < best) { best = cost; TH = th; strips = ns; cells = tiles * 16; }
         }
-        if (best < 0) return false;
-        if (strips == 1) {
-            nblk = 2;
-            for (int s = 2; s <= RS_MAX_STACK; ++s) {
-                const int rows = s * (H + 1) - 1;
-                if ((B + s - 1) / s < 2 * n_cu || !K::fits(rows, rows + 2, W)) break;
-                stack = s;
-            }
+        return best >= 0;
+    }
+    static int conv_a_rows(int th, int ns) { return ns == 1 ? th : (ns == 2 ? th + 1 : th + 2); }
+    // Whole images run both blocks in one launch: no halo, and x' is read back by the lanes that wrote it.
+    int blocks() const { return strips == 1 ? 2 : 1; }
+    // Small images are stacked while there are workgroups enough for two per compute unit: a lone 9 x 12 map gives a
+    // wavefront two to four tiles per weight fragment.
+    template <int C>
+    int stack(int B, int H, int W, int n_cu) const
+    {
+        if (strips != 1) return 1;
+        int images = 1;
+        for (int s = 2; s <= RS_MAX_STACK; ++s) {
+            const int rows = s * (H + 1) - 1;
+            if ((B + s - 1) / s < 2 * n_cu || !StripCfg<C>::fits(rows, rows + 2, W)) break;
+            images = s;
         }
-        const int ra = strips == 1 ? stack * (H + 1) - 1 : (strips == 2 ? TH + 1 : TH + 2);
-        lds = K::lds_bytes(ra + 2, W);
-        return true;
+        return images;
     }
 };
 
@@ -457,16 +459,16 @@ struct StripPoolArgs {
     int B, H, W, PH, PW, pad_h, pad_w, COUT, PTH, strips, groups;
 };
 
-template <int C>
 struct StripPoolPlan {
-    using K = StripCfg<C>;
-    int PTH = 0, strips = 0, rows = 0;
+    int PTH = 0, strips = 0, rows = 0; // PTH == 0: no strip fits; rows: the most convolution rows a strip covers
+    template <int C>
     bool choose(int H, int W, int PH, int pad_h)
     {
+        using K = StripCfg<C>;
         long best = -1;
         for (int pth = 1; pth <= PH; ++pth) {
             const int ns = (PH + pth - 1) / pth;
-            int r = 0;                                       // the most convolution rows a strip covers
+            int r = 0;
             long work = 0;
             for (int s = 0; s < ns; ++s) {
                 const int p0 = s * pth, p1 = std::min(p0 + pth, PH);

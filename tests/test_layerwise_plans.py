@@ -1,4 +1,4 @@
-"""Host side of the layer-by-layer ResNet path: workspace."""
+"""Host side of the layer-by-layer ResNet path: workspace and the choice of kernels."""
 import itertools
 import random
 
@@ -9,15 +9,53 @@ from tests import host_program
 MAIN = r"""
 int main()
 {
+    char what[8];
     int h, w, c, rows, n;
-    while (scanf("%d %d %d %d %d", &h, &w, &c, &rows, &n) == 5) {
+    while (scanf("%7s %d %d %d %d %d", what, &h, &w, &c, &rows, &n) == 6) {
         std::vector<int> sections(n);
         for (int& s : sections) if (scanf("%d", &s) != 1) return 1;
-        const LwLayout l = lw_layout(resnet(h, w, c, sections), rows);
-        printf("%zu %zu %zu %zu %zu\n", l.c0, l.u, l.r, l.x, l.end);
+        const Plan p = resnet(h, w, c, sections);
+        if (what[0] == 'b') {
+            const LwLayout l = lw_layout(p, rows);
+            printf("%zu %zu %zu %zu %zu\n", l.c0, l.u, l.r, l.x, l.end);
+        } else {
+            // a letter per section: strips, tiles, or neither; 256 compute units
+            Bf16Packed o;
+            bf16_pack(p, TORSO_NONE, (int)(p.flat + 31) / 32 * 32, 32, o);
+            std::string route;
+            for (int i = 0; i < n; ++i) {
+                const LwSectionPlan pl = plan_lw_section(p.sections[i], &o.lw[5 * i], i == 0);
+                route += strips_preferred(pl, sections[i], rows, 256) ? 'S' : pl.block.h ? 'T' : '-';
+            }
+            printf("%s\n", route.c_str());
+        }
     }
 }
 """
+
+# frames (h, w, planes), sections, {rows: kernels of each section}: S strips, T tiles
+ROUTES = [
+    # the model-size variants
+    ((72, 96, 3), (32, 64, 64), {1: "TTS", 64: "TTS", 256: "SSS", 4096: "SSS"}),
+    ((72, 96, 3), (64, 128, 128), {1: "TSS", 32: "TSS", 64: "SSS", 1024: "SSS"}),
+    ((90, 120, 16), (16, 32, 32, 32), {1: "TTSS", 256: "SSSS"}),
+    ((108, 144, 16), (16, 32, 32, 32), {1: "TTSS", 256: "SSSS"}),
+    # maps so wide that a strip is one or two rows: tiles, unless every strip has a compute unit of its own
+    ((162, 216, 3), (64,), {1: "S", 16: "T", 256: "T"}),
+    ((144, 192, 1), (64, 128), {2: "SS", 64: "ST", 256: "ST"}),
+    ((160, 216, 3), (64, 128), {1: "SS", 64: "TT", 256: "TT"}),
+    ((180, 400, 3), (32, 32), {1: "TT", 256: "TS"}),
+    ((120, 800, 4), (16, 16), {1: "TT", 256: "TS"}),
+    # strips of one section that end in a shorter one, two strips (one halo side each) and many
+    ((116, 100, 3), (64,), {2: "T", 60: "S"}),
+    ((124, 119, 1), (64, 128), {2: "TS", 60: "SS"}),
+    ((139, 121, 4), (16, 16), {2: "TT", 200: "SS"}),
+    # one map, one strip, one tile; too wide for a strip
+    ((40, 2, 4), (32, 64), {1: "SS", 500: "SS"}),
+    ((18, 520, 1), (64, 128, 128), {2: "TTT", 300: "TTT"}),
+    # no fused block at 48 channels
+    ((50, 70, 3), (16, 48), {1: "T-", 300: "S-"}),
+]
 
 
 @pytest.fixture(scope="module")
@@ -34,7 +72,7 @@ def test_maps_that_live_together_do_not_overlap(program):
     frames += [(rng.randint(1, 40), rng.randint(1, 40)) for _ in range(100)]
     cases = [(h, w, rng.choice([1, 3, 64, 2048]), s)
              for (h, w), s in itertools.product(frames, ([16], [16, 16], [16, 32, 64, 128], [64, 32, 16]))]
-    out = program([f"{h} {w} 3 {rows} {len(s)} {' '.join(map(str, s))}" for h, w, rows, s in cases])
+    out = program([f"buffers {h} {w} 3 {rows} {len(s)} {' '.join(map(str, s))}" for h, w, rows, s in cases])
     assert len(out) == len(cases)
     up = lambda n: -(-n // 256) * 256  # noqa: E731
     for (h, w, rows, sections), line in zip(cases, out):
@@ -48,3 +86,11 @@ def test_maps_that_live_together_do_not_overlap(program):
         assert 2 * max(pooled) <= r
         assert c0 == 0 and u >= max(conv) and r - u >= max(pooled) and x - r >= max(pooled) and end - x >= 2 * max(pooled)
         assert end == up(max(conv)) + 2 * up(max(pooled)) + up(2 * max(pooled))     # no more memory than the maps
+
+
+def test_strips_are_chosen_where_they_are_faster(program):
+    """Strips against tiles by the work of either plan and the workgroups a batch gives (both sides' times stand at
+    strips_preferred)."""
+    cases = [(*frame, rows, sections, route) for frame, sections, by_rows in ROUTES for rows, route in by_rows.items()]
+    out = program([f"route {h} {w} {c} {rows} {len(s)} {' '.join(map(str, s))}" for h, w, c, rows, s, _ in cases])
+    assert out == [c[-1] for c in cases], [(c, o) for c, o in zip(cases, out) if c[-1] != o]
