@@ -949,7 +949,7 @@ inline LwSectionPlan plan_lw_section(const Section& sec, const LwLayerDev* d, bo
 
 // Whether a section's batch runs on the strip kernels; else on the tile kernels, with the same results.  Measured at 1 to
 // 256 images, the two blocks, tiles -> strips, us:
-// * Full-width strips get thin on wide maps and recompute their halo rows: where they walk more than 1.3 times the
+// * Full-width strips get thin on wide maps and recompute their halo rows (a whole image has none): where they walk more than 1.3 times the
 //   tiles' cells tiles win (256 images: 64 channels on 81 x 108, one row a strip, 1.6 times, 1107 -> 1605; 32 on 90 x 200,
 //   1.38, 774 -> 843; below the line 64 channels on 72 x 96, 1.23, 888 -> 901, on 63 x 84, 1.05, 662 -> 583), or at 128
 //   channels, whose tiles recompute nothing but carry U through memory, 1.5 times (36 x 48, 1.61, 678 -> 718; 27 x 36,
@@ -966,7 +966,7 @@ inline bool strips_preferred(const LwSectionPlan& pl, int C, int B, int n_cu)
 {
     if (!pl.strips || !pl.block.h) return pl.strips;
     const long strips = pl.strip_block.strips, groups = B * strips;
-    if (10 * pl.strip_block.cells > (pl.conv.h ? 15 : 13) * pl.tile_cells) return C >= 64 && groups <= n_cu;
+    if (strips > 1 && 10 * pl.strip_block.cells > (pl.conv.h ? 15 : 13) * pl.tile_cells) return C >= 64 && groups <= n_cu;
     if (C == 128 || strips >= pl.tiles) return true;
     return groups >= (C == 64 || 2 * strips <= pl.tiles ? n_cu * 3 / 4 : 2 * n_cu);
 }

@@ -50,6 +50,8 @@ ROUTES = [
     ((116, 100, 3), (64,), {2: "T", 60: "S"}),
     ((124, 119, 1), (64, 128), {2: "TS", 60: "SS"}),
     ((139, 121, 4), (16, 16), {2: "TT", 200: "SS"}),
+    # small whole images (5 x 3 pixels fill half of their pixel tiles)
+    ((34, 22, 3), (32, 64, 128), {5: "SSS", 1541: "SSS"}),
     # one map, one strip, one tile; too wide for a strip
     ((40, 2, 4), (32, 64), {1: "SS", 500: "SS"}),
     ((18, 520, 1), (64, 128, 128), {2: "TTT", 300: "TTT"}),
