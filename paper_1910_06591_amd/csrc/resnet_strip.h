@@ -163,14 +163,16 @@ __device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int p
 }
 
 // Calls phase(NT) for the number of pixel tiles this wavefront owns (uniform): a convolution and its epilogue with the
-// count a constant.  (Barriers inside: every wavefront passes the same number of them whatever its count.)
+// count a constant.  (Barriers inside: every wavefront passes the same number of them whatever its count.  The plans give
+// at most TPW; the clamp keeps a count beyond it from passing none.)
 template <int TPW, class F>
 __device__ __forceinline__ void by_tiles(int nt, F phase)
 {
+    static_assert(TPW <= 12, "a case for every count");
     auto go = [&](auto ntc) {
         if constexpr (decltype(ntc)::value <= TPW) phase(ntc);
     };
-    switch (nt) {
+    switch (min(nt, TPW)) {
     case 0: go(std::integral_constant<int, 0>{}); break;
     case 1: go(std::integral_constant<int, 1>{}); break;
     case 2: go(std::integral_constant<int, 2>{}); break;
@@ -184,10 +186,6 @@ __device__ __forceinline__ void by_tiles(int nt, F phase)
     case 10: go(std::integral_constant<int, 10>{}); break;
     case 11: go(std::integral_constant<int, 11>{}); break;
     case 12: go(std::integral_constant<int, 12>{}); break;
-    case 13: go(std::integral_constant<int, 13>{}); break;
-    case 14: go(std::integral_constant<int, 14>{}); break;
-    case 15: go(std::integral_constant<int, 15>{}); break;
-    default: go(std::integral_constant<int, 16>{}); break;
     }
 }
 

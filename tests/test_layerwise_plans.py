@@ -7,6 +7,45 @@ import pytest
 from tests import host_program
 
 MAIN = r"""
+// the strip plans of a section: per plan LDS bytes of its largest map and of the launch, the most pixel tiles of a wavefront
+// and the accumulators' limit, and whether the strips cover every row once
+static void strips(const Section& sec, int rows)
+{
+    const int H = sec.PH, W = sec.PW, C = sec.conv0.Cout;
+    strip_by_width(C, [&](auto cc) {
+        using K = StripCfg<decltype(cc)::value>;
+        auto tiles = [&](int r, int w) { return (K::tiles(r, w) + K::NPG - 1) / K::NPG; };
+        StripBlockPlan b;
+        if (b.choose<decltype(cc)::value>(H, W)) {
+            const int stack = b.stack<decltype(cc)::value>(rows, H, W, 256);
+            int lds_rows = 0, most = 0;
+            for (int s = 0; s < b.strips; ++s) {
+                const int y0 = s * b.TH, ye = std::min(y0 + b.TH, H);
+                const int ra = stack > 1 ? stack * (H + 1) - 1 : std::min(ye + 1, H) - std::max(y0 - 1, 0);
+                lds_rows = std::max(lds_rows, ra + 2);
+                most = std::max(most, tiles(ra, W));
+            }
+            const bool cover = (long)b.TH * b.strips >= H && (long)b.TH * (b.strips - 1) < H && (stack == 1 || b.strips == 1);
+            const size_t asked = K::lds_bytes((stack > 1 ? stack * (H + 1) - 1 : b.conv_a_rows(b.TH, b.strips)) + 2, W);
+            printf("%zu %zu %d %d %d ", K::lds_bytes(lds_rows, W), asked, most, K::TPW, cover && asked <= RS_LDS_MAX);
+        }
+        const ConvLayer& c = sec.conv0;
+        StripPoolPlan q;
+        if (q.choose<decltype(cc)::value>(c.H, c.W, sec.PH, sec.pool_pad_h)) {
+            int most = 0;
+            for (int s = 0; s < q.strips; ++s) {
+                const int p0 = s * q.PTH, p1 = std::min(p0 + q.PTH, sec.PH);
+                const int n = std::min(2 * (p1 - 1) - sec.pool_pad_h + 3, c.H) - std::max(2 * p0 - sec.pool_pad_h, 0);
+                most = std::max(most, n);
+            }
+            const bool cover = (long)q.PTH * q.strips >= sec.PH && (long)q.PTH * (q.strips - 1) < sec.PH && most <= q.rows;
+            printf("%zu %zu %d %d %d", K::lds_bytes(q.rows + 2, c.W), RS_LDS_MAX, tiles(most, c.W), K::TPW, cover);
+        }
+        printf("\n");
+        return true;
+    });
+}
+
 int main()
 {
     char what[8];
@@ -15,7 +54,9 @@ int main()
         std::vector<int> sections(n);
         for (int& s : sections) if (scanf("%d", &s) != 1) return 1;
         const Plan p = resnet(h, w, c, sections);
-        if (what[0] == 'b') {
+        if (what[0] == 's') {
+            strips(p.sections[0], rows);
+        } else if (what[0] == 'b') {
             const LwLayout l = lw_layout(p, rows);
             printf("%zu %zu %zu %zu %zu\n", l.c0, l.u, l.r, l.x, l.end);
         } else {
@@ -96,3 +137,21 @@ def test_strips_are_chosen_where_they_are_faster(program):
     cases = [(*frame, rows, sections, route) for frame, sections, by_rows in ROUTES for rows, route in by_rows.items()]
     out = program([f"route {h} {w} {c} {rows} {len(s)} {' '.join(map(str, s))}" for h, w, c, rows, s, _ in cases])
     assert out == [c[-1] for c in cases], [(c, o) for c, o in zip(cases, out) if c[-1] != o]
+
+
+def test_strips_fit_lds_and_the_accumulators(program):
+    """A strip's map fits the LDS a workgroup asks for and its pixel tiles the accumulators (a wavefront with more would
+    drop them), for every map, ragged strips and stacks of images, as the kernels work their rows out."""
+    rng = random.Random(2)
+    maps = [(1, 1), (2, 3), (9, 12), (17, 11), (36, 48), (54, 72), (2048, 2), (2, 500), (1, 1020), (300, 250)]
+    maps += [(rng.randint(1, 200), rng.randint(1, 300)) for _ in range(300)]
+    # (the pooling plan looks at conv0 as a layer of C input channels: planes do not matter)
+    cases = [(2 * h - rng.randint(0, 1), 2 * w - rng.randint(0, 1), ch, rng.choice([1, 600, 1100, 1700, 2051, 5000]))
+             for h, w in maps for ch in (16, 32, 64, 128)]
+    out = program([f"strips {h} {w} 3 {rows} 1 {ch}" for h, w, ch, rows in cases])
+    assert len(out) == len(cases)
+    for case, line in zip(cases, out):
+        v = list(map(int, line.split()))
+        for lds, lds_max, tiles, tiles_max, cover in zip(*[iter(v)] * 5):
+            assert lds <= lds_max and 1 <= tiles <= tiles_max and cover, (case, line)
+    assert sum(len(line.split()) >= 5 for line in out) > len(out) // 2
