@@ -292,8 +292,8 @@ def test_bf16_head_and_core_variants(orc):
     ("odd frame 50x70x3, two sections, 48 channels", dict(obs_h=50, obs_w=70, sections=[16, 48]), 7),
     ("4-plane minimap 72x96x4", dict(obs_c=4, sections=[16, 32, 32, 32]), 6),
     ("odd frame 46x62x3, 32 then 96 channels", dict(obs_h=46, obs_w=62, sections=[32, 96]), 5),
-    # the per-section fused kernels (first layer + pool, conv0 + pool, residual block) on maps that leave ragged
-    # tiles and odd pooled sizes, at every channel pair they are built for
+    # the per-section kernels (first layer + pool, conv0 + pool, residual blocks) on maps that leave ragged tiles and odd
+    # pooled sizes; with so few rows on tiles or, for small maps and at 128 channels, on strips
     ("odd frame 45x61x3, sections 64/128/128", dict(obs_h=45, obs_w=61, sections=[64, 128, 128]), 3),
     ("odd frame 37x53x1, sections 16/16/32/64", dict(obs_h=37, obs_w=53, obs_c=1, sections=[16, 16, 32, 64]), 4),
     ("frame 67x41x8, sections 32/32/64/64", dict(obs_h=67, obs_w=41, obs_c=8, sections=[32, 32, 64, 64]), 3),
@@ -539,6 +539,26 @@ def test_bf16_strip_kernels_stack_small_images(orc, label, over):
     run_case(orc, cfg, few, "bf16")
 
 
+@pytest.mark.parametrize("label,over", [
+    ("16/32/64", dict(obs_h=34, obs_w=22, sections=[16, 32, 64])),
+    ("64/128/128", dict(obs_h=21, obs_w=33, sections=[64, 128, 128])),
+])
+def test_bf16_stacks_of_four_images(orc, label, over):
+    """The largest stacks (two workgroups per compute unit left over, so from 2045 rows on): all four places of a
+    stack and a ragged last one of three images."""
+    cfg = dict(wl.CONFIGS["C3"], label=f"stacks of four {label}", index=125, **over)
+    B, rows = 4 * 512 + 3, [0, 1, 2, 3, 2048, 2049, 2050]
+    weights, batch = wl.make_weights(cfg), wl.make_batch(cfg, B)
+    net = seedinf.SeedInfer(seedinf.make_arch(cfg, max_batch=B), weights)
+    net.step(**to_device(batch))
+    big = net.read_intermediate(0, B).cpu().numpy()
+    net.step(**to_device({k: None if v is None else np.ascontiguousarray(v[rows]) for k, v in batch.items()}))
+    small = net.read_intermediate(0, len(rows)).cpu().numpy()
+    net.close()
+    np.testing.assert_array_equal(big[rows], small)
+    run_case(orc, cfg, len(rows), "bf16")
+
+
 @pytest.mark.parametrize("label,over,B", [
     # strips of one section that end in a shorter one, two strips (one halo side each) and many; rows of one pixel column
     ("64 channels, 58 x 50 maps", dict(obs_h=116, obs_w=100, obs_c=3, sections=[64]), 2),
@@ -550,6 +570,18 @@ def test_bf16_strip_kernels_stack_small_images(orc, label, over):
 def test_bf16_strip_kernels_at_the_edges_of_their_plans(orc, label, over, B):
     cfg = dict(wl.CONFIGS["C3"], label=f"strips: {label}", index=121, fc_units=32, **over)
     run_case(orc, cfg, B, "bf16")
+
+
+@pytest.mark.parametrize("label,over", [
+    ("16/16/32", dict(obs_h=8, obs_w=2060, sections=[16, 16, 32])),
+    ("32/32/64/64", dict(obs_h=6, obs_w=2060, sections=[32, 32, 64, 64])),
+    ("64/64/128/128", dict(obs_h=9, obs_w=1030, sections=[64, 64, 128, 128])),
+])
+def test_bf16_maps_wider_than_any_strip(orc, label, over):
+    """Frames whose maps fit no strip (more than 510 / 254 / 126 / 62 columns at 16 / 32 / 64 / 128 channels): the tile
+    kernels' first layer, conv0 + pooling and blocks at every channel pair they are built for, whatever the batch."""
+    cfg = dict(wl.CONFIGS["C3"], label=f"wide maps {label}", index=126, obs_c=3, fc_units=32, **over)
+    run_case(orc, cfg, 2, "bf16")
 
 
 @pytest.mark.parametrize("frame,sections,routes", ROUTES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else "")
