@@ -20,9 +20,9 @@
 //     share one 64 x 64 (RT = 4) or 96 x 64 (RT = 6) tile and each takes every eighth chunk.  Nothing is shared
 //     between them, so each runs private rings in its own 20 KiB of LDS (three slots of activation fragments, or two
 //     at 96 rows, and two of weight fragments) with no barrier inside the K loop.  The eight partial tiles meet in
-//     LDS and RT wavefronts finish one row tile each.  (Splitting K over workgroups instead costs more than it saves here: partial sums that
-//     cross the chip's L2 slices need device-scope fences, each of which writes back and invalidates a whole
-//     slice.)
+//     LDS and RT wavefronts finish one row tile each.  (Splitting K over workgroups instead costs more than it saves
+//     here: partial sums that cross the chip's L2 slices need device-scope fences, each of which writes back and
+//     invalidates a whole slice.)
 #pragma once
 #include "gemm_bf16.h"
 

@@ -1,6 +1,6 @@
-// Layer-by-layer ResNet path, maps whose full-width strips fit LDS: conv0 + pooling of a section, and its residual
-// blocks (one per launch, or both where a workgroup holds whole images), each in one launch over ONE LDS map that every
-// convolution rewrites in place.
+// Layer-by-layer ResNet path, maps whose full-width strips fit LDS and are the faster cut (strips_preferred in
+// bf16_path.h): conv0 + pooling of a section, and its residual blocks (one per launch, or both where a workgroup holds whole
+// images), each in one launch over ONE LDS map that every convolution rewrites in place.
 //
 // A workgroup takes TH rows of an image (all W columns), a whole image or several stacked ones.  The map is planar
 // bf16 [C/8][cells][8 channels]; a row is W + 1 cells, cell 0 of which is zero: it is the left border of its own row
@@ -8,7 +8,8 @@
 // convolution are walked flat over the map, border cells included (computed, and kept zero): a tile is 16
 // consecutive cells, so its fragments are 256 distinct bank bytes - the full LDS rate, where 16 row-major pixels
 // of a narrower region wrap rows and read at about 57 % - and tile i of a wavefront sits at a constant distance
-// from tile 0: one address register for all of them, immediates for the rest.
+// from tile 0: one address register for all of them, immediates for the rest.  (The staging writes are not free of
+// conflicts: the lanes of a pixel hold its channel groups, whose planes lie whole 256 bytes apart.)
 //
 // In place: a wavefront keeps its whole output (up to TPW pixel tiles x FTW feature tiles) in accumulators, the
 // workgroup waits until everybody has read the input map, and the output overwrites it.  Half the LDS of an input
@@ -22,9 +23,10 @@
 // 222 -> 135, on 9 x 12 82 -> 45; 128 channels on 18 x 24 680 -> 475, on 9 x 12 199 -> 123; 32 channels on 36 x 48 333 ->
 // 240, on 27 x 36 174 -> 111; 16 channels on 54 x 72 273 -> 253.  conv0 + pooling: 64 -> 128 on 36 x 48 339 -> 292, 128 ->
 // 128 on 18 x 24 212 -> 126, 32 -> 64 on 36 x 48 120 -> 85, 16 -> 32 on 54 x 72 107 -> 77.
-// What bounds them now (64 channels on 36 x 48, cycles of a workgroup's 78 K): staging 15 K and the epilogue 22 K of
-// memory, the two convolutions 36 K for 18 K of MFMAs (two workgroups share the matrix cores); 0.9 GB of HBM traffic is
-// 150 us at the copy rate, the MFMAs 119 us.
+// What bounds them now (64 channels on 36 x 48, cycles of a workgroup's 78 K): staging 15 K, about 5 K of it bank conflicts
+// of its writes (33 % of the kernel's LDS cycles, 46 % in the pooling kernel), the epilogue 22 K of memory, the two
+// convolutions 36 K for 18 K of MFMAs (two workgroups share the matrix cores).  HBM traffic by counters: 0.96 GB in the first
+// block, 1.21 in the second (fp32 in), 155 and 190 us at the copy rate; the MFMAs take 119 us.
 #pragma once
 #include "resnet_blockfused.h"
 
@@ -96,8 +98,9 @@ __device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int p
     using K = StripCfg<C>;
     constexpr int FTW = K::FTW, KCH = K::KCH, STEP = K::NPG * 256;
     // Map fragments travel in a ring of RING registers sets, RING tiles (of this chunk or the next) ahead of their use;
-    // RING divides NT so that a slot serves the same tiles in every chunk.  The order is pinned: left alone, the compiler saves registers by asking for every fragment
-    // right before its MFMAs, and each then waits out an LDS trip (64 channels on 36 x 48, 1024 images: 361 us).
+    // RING divides NT so that a slot serves the same tiles in every chunk.  The order is pinned: left alone, the compiler
+    // saves registers by asking for every fragment right before its MFMAs, and each then waits out an LDS trip (64 channels
+    // on 36 x 48, 1024 images: 361 us).
     constexpr int RING = NT % 4 == 0 ? 4 : (NT % 3 == 0 ? 3 : (NT % 5 == 0 ? 5 : NT));
     lane = fresh_lane(lane);
     const int g = lane >> 4, n = lane & 15;
@@ -447,7 +450,7 @@ __global__ __launch_bounds__(RS_THREADS, 4) void strip_block_kernel(StripBlockAr
 // ---- conv0 of a later section with its pooling --------------------------------
 // bf16 NHWC input of C channels -> 3x3 SAME convolution -> 3x3 / stride-2 max-pool -> the section's x as bf16 (the
 // maxima of values that were rounded to bf16 before they were compared: no rounding of its own).  A workgroup
-// computes C of the layer's output channels (blockIdx.y: which), so that its output fits over its input, for the
+// computes C of the layer's output channels (neighbouring workgroups: the others), so that its output fits over its input, for the
 // convolution rows under PTH pooled rows; window cells outside the map are clamped onto it.
 struct StripPoolArgs {
     const __bf16* in;                  // [B, H, W, C]
