@@ -21,6 +21,7 @@
 #include "resnet_convpool.h"
 #include "resnet_convtile.h"
 #include "resnet_strip.h"
+#include "resnet_pair.h"
 
 namespace seedinf {
 
@@ -125,6 +126,7 @@ struct LwSectionPlan {
     int tiles = 0; long tile_cells = 0;        // the tile kernels': workgroups an image, cells a block's convolutions walk
     StripBlockPlan strip_block;
     StripPoolPlan strip_pool;
+    PairPlan pair;                             // both blocks in one launch with x in registers, where that is the faster cut
     bool strips = false;                       // the strip kernels cover conv0 + pooling and the blocks
 };
 inline bool first_pool_supported(const ConvLayer& c)
@@ -569,6 +571,8 @@ inline seed_status_t bf16_create(const Plan& p, const float* d_w, Bf16State** ou
         set((const void*)strip_block_kernel<32, true>, RS_LDS_MAX); set((const void*)strip_block_kernel<32, false>, RS_LDS_MAX);
         set((const void*)strip_block_kernel<64, true>, RS_LDS_MAX); set((const void*)strip_block_kernel<64, false>, RS_LDS_MAX);
         set((const void*)strip_block_kernel<128, true>, RS_LDS_MAX); set((const void*)strip_block_kernel<128, false>, RS_LDS_MAX);
+        set((const void*)resblock_pair_kernel<16>, RP_LDS_MAX); set((const void*)resblock_pair_kernel<32>, RP_LDS_MAX);
+        set((const void*)resblock_pair_kernel<64>, RP_LDS_MAX); set((const void*)resblock_pair_kernel<128>, RP_LDS_MAX);
         set((const void*)strip_pool_kernel<16>, RS_LDS_MAX); set((const void*)strip_pool_kernel<32>, RS_LDS_MAX);
         set((const void*)strip_pool_kernel<64>, RS_LDS_MAX); set((const void*)strip_pool_kernel<128>, RS_LDS_MAX);
         set((const void*)conv_tile_kernel<128, true>, CT_LDS_MAX);
@@ -901,6 +905,18 @@ inline bool strip_by_width(int C, F go)
     }
 }
 
+// Whether both blocks in one launch (resnet_pair.h) beat a launch of strips per block: by the map cells walked, which the
+// longer halo of the one launch multiplies.  Measured at 256 images, us, strips -> one launch at so many times the cells:
+// 16 channels on 54 x 72 69 -> 42 (1.1), 60 x 96 92 -> 61 (1.29), 80 x 108 146 -> 122 (1.36), 50 x 150 142 -> 137 (1.62), 40 x 240
+// 186 -> 332; 32 on 36 x 48 65 -> 46 (1.13), 54 x 72 160 -> 140 (1.49), 45 x 60 107 -> 84 (1.5), 40 x 100 164 -> 206 (2.2); 64,
+// where matrix cores weigh more, on 18 x 24 50 -> 37 (1), 20 x 30 70 -> 58 (1.24), 12 x 60 81 -> 86 (1.4), 27 x 36 104 -> 122
+// (1.54); 128 on 14 x 18 83 -> 68 (1), 10 x 30 108 -> 132 (1.45).  Below the line at 1 to 1024 images alike (1 image: 32
+// channels on 36 x 48 34 -> 20, 64 on 18 x 24 38 -> 27).
+inline bool pair_preferred(const PairPlan& pair, const StripBlockPlan& strip, int C)
+{
+    return 20 * pair.cells <= (C >= 64 ? 26 : 31) * 2 * strip.cells;
+}
+
 // The kernels that cover a section, d: its five convolutions.
 inline LwSectionPlan plan_lw_section(const Section& sec, const LwLayerDev* d, bool first)
 {
@@ -944,6 +960,12 @@ inline LwSectionPlan plan_lw_section(const Section& sec, const LwLayerDev* d, bo
         return pl.strip_pool.choose<decltype(cc)::value>(c.H, c.W, sec.PH, sec.pool_pad_h);
     });
     pl.strips = blocks && conv0;
+    if (pl.strips)
+        strip_by_width(ba.Cin, [&](auto cc) {
+            PairPlan pair;
+            if (pair.choose<decltype(cc)::value>(ba.H, ba.W) && pair_preferred(pair, pl.strip_block, ba.Cin)) pl.pair = pair;
+            return true;
+        });
     return pl;
 }
 
@@ -998,6 +1020,25 @@ inline void launch_strip_blocks(hipStream_t st, const LwLayerDev* d, const bf16x
     });
 }
 
+// The same in one launch.
+inline void launch_pair(hipStream_t st, const LwLayerDev* d, const bf16x8* wp_conv, const float* d_w, const Section& sec,
+                        const PairPlan& pl, int B, int n_cu, const __bf16* xb, __bf16* y, int y_relu, int ldy)
+{
+    strip_by_width(sec.conv0.Cout, [&](auto cc) {
+        constexpr int CC = decltype(cc)::value;
+        PairArgs a{};
+        a.x_in = xb; a.y = y; a.y_relu = y_relu; a.ldy = ldy;
+        for (int i = 0; i < 4; ++i) { a.wp[i] = wp_conv + d[i].wp_off / 8; a.bias[i] = d_w + sec.block[i].b_off; }
+        a.B = B; a.H = sec.PH; a.W = sec.PW; a.TH = pl.TH; a.strips = pl.strips;
+        a.stack = pl.stack<CC>(B, sec.PH, sec.PW, n_cu);
+        a.rows = pl.rows(sec.PH, a.stack);
+        a.items = a.stack > 1 ? (B + a.stack - 1) / a.stack : B * pl.strips;
+        hipLaunchKernelGGL(resblock_pair_kernel<CC>, dim3(std::min(a.items, n_cu)), dim3(RP_THREADS),
+                           PairCfg<CC>::lds_bytes(a.rows, pl.pixels(sec.PH, sec.PW, a.stack), sec.PW), st, a);
+        return true;
+    });
+}
+
 // conv0 of a later section with its pooling on the strip kernel (bf16 NHWC map -> x as bf16).
 inline void launch_strip_pool(hipStream_t st, const LwLayerDev& d, const bf16x8* wp_conv, const float* d_w, const Section& sec,
                               const StripPoolPlan& pl, int B, const __bf16* in, __bf16* x)
@@ -1047,8 +1088,10 @@ inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w
             if (strips_preferred(pl, sec.conv0.Cout, B, s->n_cu)) {
                 if (si == 0) launch_first_pool(st, s->lw[li], W.wp_conv, d_w, sec, pl.first, B, obs, nullptr, s->lw_u);
                 else launch_strip_pool(st, s->lw[li], W.wp_conv, d_w, sec, pl.strip_pool, B, (const __bf16*)in, s->lw_u);
-                launch_strip_blocks(st, &s->lw[li + 1], W.wp_conv, d_w, sec, pl.strip_block, B, s->n_cu, s->lw_u, s->lw_x,
-                                    last_sec ? s->feat : s->lw_r, last_sec ? 1 : 0, last_sec ? s->ldf : 0);
+                __bf16* const y = last_sec ? s->feat : s->lw_r;
+                const int y_relu = last_sec ? 1 : 0, ldy = last_sec ? s->ldf : 0;
+                if (pl.pair.TH) launch_pair(st, &s->lw[li + 1], W.wp_conv, d_w, sec, pl.pair, B, s->n_cu, s->lw_u, y, y_relu, ldy);
+                else launch_strip_blocks(st, &s->lw[li + 1], W.wp_conv, d_w, sec, pl.strip_block, B, s->n_cu, s->lw_u, s->lw_x, y, y_relu, ldy);
                 li += 5;
                 in = s->lw_r;
                 continue;

@@ -1,6 +1,6 @@
 // Layer-by-layer ResNet path, maps whose full-width strips fit LDS and are the faster cut (strips_preferred in
-// bf16_path.h): conv0 + pooling of a section, and its residual blocks (one per launch, or both where a workgroup holds whole
-// images), each in one launch over ONE LDS map that every convolution rewrites in place.
+// bf16_path.h): conv0 + pooling of a section, and its residual blocks, each in one launch over ONE LDS map that every
+// convolution rewrites in place.  (Both blocks in one launch where their halo allows it: resnet_pair.h.)
 //
 // A workgroup takes TH rows of an image (all W columns), a whole image or several stacked ones.  The map is planar
 // bf16 [C/8][cells][8 channels]; a row is W + 1 cells, cell 0 of which is zero: it is the left border of its own row
@@ -88,20 +88,51 @@ __device__ __forceinline__ int fresh_lane(int lane)
     return lane;
 }
 
+// Pixel tiles whose map fragments strip_conv keeps requested ahead: divides NT so that a slot serves the same tiles in every chunk.
+constexpr int strip_ring(int NT) { return NT % 4 == 0 ? 4 : (NT % 3 == 0 ? 3 : (NT % 5 == 0 ? 5 : NT)); }
+
+// A wavefront's weight fragments: WS slots, requested WS - 1 chunks ahead.  Three where two feature groups or more pull 36
+// KiB and up per convolution through the vector L1 (64 channels on 36 x 48 370 -> 362 us, 128 on 18 x 24 257 -> 244); at
+// 32 channels the registers they take cost more (129 -> 147 us), and so at 16.
+// WIDE (FTW = 2): the two fragments together hold, for lane group g of the result, the eight consecutive channels 8 g ..
+// 8 g + 7 of the pair's 32 instead of four of each tile (the lanes fetch the rows of the packed weights in that order).
+template <int C, bool WIDE>
+struct StripWeights {
+    using K = StripCfg<C>;
+    static constexpr int FTW = K::FTW, KCH = K::KCH, WS = C >= 64 ? 3 : 2, WJ = WIDE ? 4 : KCH * 64;
+    static_assert(!WIDE || FTW == 2, "feature tile pairs");
+    bf16x8 a[WS][FTW];
+    __device__ static __forceinline__ int first(int lane)
+    {
+        return WIDE ? ((lane & 8) >> 3) * KCH * 64 + (lane & 48) + (lane & 4) * 2 + (lane & 3) : lane;
+    }
+    __device__ __forceinline__ void request(const bf16x8* __restrict__ wl, int kc, int slot, int lane)
+    {
+#pragma unroll
+        for (int j = 0; j < FTW; ++j) a[slot][j] = (wl + j * WJ + kc * 64)[first(lane)];
+    }
+    // the first WS - 1 chunks
+    __device__ __forceinline__ void start(const bf16x8* __restrict__ wl, int lane)
+    {
+#pragma unroll
+        for (int d = 0; d < WS - 1; ++d) request(wl, d, d, lane);
+    }
+};
+
 // acc[i][j] = convolution of pixel tile pg + NPG * i and feature tile ft0 + j of a region that starts at `src` (tap
 // (0, 0) of its first pixel, plane 0): pixel q has tap (kh, kw) at cell q + kh * P + kw.  `last`: the region's last
-// pixel, which lanes past the end read again.
-template <int C, int NT>
+// pixel, which lanes past the end read again.  The weights' first chunks have been requested (start); tail() runs
+// behind the request of the last ones.
+template <int C, int NT, int RING = strip_ring(NT), bool WIDE = false, class Tail>
 __device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int pg, int last, const bf16x8* __restrict__ wl, int lane,
-                                           floatx4 (&acc)[NT][StripCfg<C>::FTW])
+                                           StripWeights<C, WIDE>& w, floatx4 (&acc)[NT][StripCfg<C>::FTW], Tail tail)
 {
     using K = StripCfg<C>;
-    constexpr int FTW = K::FTW, KCH = K::KCH, STEP = K::NPG * 256;
-    // Map fragments travel in a ring of RING registers sets, RING tiles (of this chunk or the next) ahead of their use;
-    // RING divides NT so that a slot serves the same tiles in every chunk.  The order is pinned: left alone, the compiler
-    // saves registers by asking for every fragment right before its MFMAs, and each then waits out an LDS trip (64 channels
-    // on 36 x 48, 1024 images: 361 us).
-    constexpr int RING = NT % 4 == 0 ? 4 : (NT % 3 == 0 ? 3 : (NT % 5 == 0 ? 5 : NT));
+    constexpr int FTW = K::FTW, KCH = K::KCH, STEP = K::NPG * 256, WS = StripWeights<C, WIDE>::WS;
+    static_assert(NT % RING == 0, "a ring slot's tiles");
+    // Map fragments travel in a ring of RING registers sets, RING tiles (of this chunk or the next) ahead of their use.
+    // The order is pinned: left alone, the compiler saves registers by asking for every fragment right before its MFMAs,
+    // and each then waits out an LDS trip (64 channels on 36 x 48, 1024 images: 361 us).
     lane = fresh_lane(lane);
     const int g = lane >> 4, n = lane & 15;
     const int q0 = pg * 16 + n, ql = min(q0 + (NT - 1) * K::NPG * 16, last);
@@ -121,15 +152,7 @@ __device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int p
         }
     };
     auto frag = [&](int o, int i) { return *(const bf16x8*)((i < NT - 1 ? s0 + i * STEP : sl) + o); };
-    // Weight fragments: WS slots, requested WS - 1 chunks ahead.  Three where two feature groups or more pull 36 KiB
-    // and up per convolution through the vector L1 (64 channels on 36 x 48 370 -> 362 us, 128 on 18 x 24 257 -> 244); at
-    // 32 channels the registers they take cost more (129 -> 147 us), and so at 16.
-    constexpr int WS = C >= 64 ? 3 : 2;
-    bf16x8 a[WS][FTW], b[RING];
-#pragma unroll
-    for (int d = 0; d < WS - 1; ++d)
-#pragma unroll
-        for (int j = 0; j < FTW; ++j) a[d][j] = wl[(j * KCH + d) * 64 + lane];
+    bf16x8 b[RING];
     int o = off(0);
 #pragma unroll
     for (int i = 0; i < RING; ++i) b[i] = frag(o, i);
@@ -137,32 +160,50 @@ __device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int p
     for (int i = 0; i < NT; ++i)
 #pragma unroll
         for (int j = 0; j < FTW; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    auto chunk = [&](int kc, auto dc) {
+    // chunk kc, its weights in slot D; MORE: weights are left to request, NEXT: another chunk follows
+    auto chunk = [&](int kc, auto dc, auto more, auto next) {
         constexpr int D = decltype(dc)::value;
-        const int on = off(min(kc + 1, KCH - 1));
-        const int kn = min(kc + WS - 1, KCH - 1);
-#pragma unroll
-        for (int j = 0; j < FTW; ++j) a[(D + WS - 1) % WS][j] = (wl + (j * KCH + kn) * 64)[lane];
+        constexpr bool MORE = decltype(more)::value, NEXT = decltype(next)::value;
+        const int on = NEXT ? off(kc + 1) : 0;
+        if constexpr (MORE) w.request(wl, kc + WS - 1, (D + WS - 1) % WS, lane);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
 #pragma unroll
-            for (int j = 0; j < FTW; ++j) acc[i][j] = mfma16(a[D][j], b[i % RING], acc[i][j]);
-            b[i % RING] = i + RING < NT ? frag(o, i + RING) : frag(on, i + RING - NT);
+            for (int j = 0; j < FTW; ++j) acc[i][j] = mfma16(w.a[D][j], b[i % RING], acc[i][j]);
+            if (i + RING < NT) b[i % RING] = frag(o, i + RING);
+            else if constexpr (NEXT) b[i % RING] = frag(on, i + RING - NT);
             __builtin_amdgcn_sched_barrier(0);
         }
         o = on;
     };
     using D0 = std::integral_constant<int, 0>; using D1 = std::integral_constant<int, 1>; using D2 = std::integral_constant<int, 2>;
-    int kc = 0;
+    using T = std::true_type; using F = std::false_type;
+    constexpr int LEFT = KCH % WS == 0 ? WS : KCH % WS;      // chunks behind the loop
+    static_assert(KCH % WS <= 1 && (KCH % WS == 1 ? WS == 2 : WS == 3), "the last groups below");
 #pragma unroll 1
-    for (; kc + WS <= KCH; kc += WS) {
-        chunk(kc, D0{});
-        chunk(kc + 1, D1{});
-        if constexpr (WS == 3) chunk(kc + 2, D2{});
+    for (int kc = 0; kc < KCH - LEFT; kc += WS) {
+        chunk(kc, D0{}, T{}, T{});
+        chunk(kc + 1, D1{}, T{}, T{});
+        if constexpr (WS == 3) chunk(kc + 2, D2{}, T{}, T{});
     }
-    static_assert(KCH % WS <= 1, "at most one chunk is left over");
-    if constexpr (KCH % WS == 1) chunk(KCH - 1, D0{});
+    if constexpr (LEFT == 3) {
+        chunk(KCH - 3, D0{}, T{}, T{});
+        tail();
+        chunk(KCH - 2, D1{}, F{}, T{});
+        chunk(KCH - 1, D2{}, F{}, F{});
+    } else {
+        tail();
+        chunk(KCH - 1, D0{}, F{}, F{});
+    }
+}
+template <int C, int NT>
+__device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int pg, int last, const bf16x8* __restrict__ wl, int lane,
+                                           floatx4 (&acc)[NT][StripCfg<C>::FTW])
+{
+    StripWeights<C, false> w;
+    w.start(wl, fresh_lane(lane));
+    strip_conv<C, NT>(src, PL, P, pg, last, wl, lane, w, acc, [] {});
 }
 
 // Calls phase(NT) for the number of pixel tiles this wavefront owns (uniform): a convolution and its epilogue with the

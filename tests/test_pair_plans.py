@@ -1,0 +1,86 @@
+"""Both residual blocks of a section in one launch: its strips on the CPU, its kernel against the oracle and the other kernels."""
+import random
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1910_06591_amd import seedinf, workloads as wl
+from tests import host_program
+from tests.parity import check_against_oracle, to_device
+
+MAIN = r"""
+// per map: LDS bytes, the most pixel tiles of a wavefront and its limit, pixels of the incoming map asked for and needed, and
+// whether the strips cover every row once with their halos inside the map
+int main()
+{
+    int H, W, C, B;
+    while (scanf("%d %d %d %d", &H, &W, &C, &B) == 4) {
+        strip_by_width(C, [&](auto cc) {
+            constexpr int CC = decltype(cc)::value;
+            using K = PairCfg<CC>;
+            PairPlan p;
+            if (!p.choose<CC>(H, W)) { printf("-\n"); return true; }
+            const int stack = p.stack<CC>(B, H, W, 256), rows = p.rows(H, stack), pixels = p.pixels(H, W, stack);
+            int need = stack > 1 ? stack * H * W : 0, most = stack > 1 ? stack * (H + 1) - 1 : 0, covered = 0;
+            for (int s = 0; s < p.strips; ++s) {
+                const int y0 = s * p.TH, ye = std::min(y0 + p.TH, H);
+                covered += std::max(ye - y0, 0);
+                if (stack > 1) continue;
+                need = std::max(need, (std::min(ye + 4, H) - std::max(y0 - 4, 0)) * W);
+                most = std::max(most, std::min(ye + 3, H) - std::max(y0 - 3, 0));
+            }
+            const int tiles = (K::S::tiles(rows, W) + K::S::NPG - 1) / K::S::NPG;
+            printf("%zu %d %d %d %d %d\n", K::lds_bytes(rows, pixels, W), tiles, K::TPW, pixels, need, covered == H && most <= rows && (stack == 1 || p.strips == 1));
+            return true;
+        });
+    }
+}
+"""
+
+
+def test_strips_fit_lds_and_the_registers(tmp_path):
+    """The map and the incoming pixels fit LDS, the pixel tiles the registers, and the rows of the launch those of its
+    longest strip, for whole images, stacks and up to many strips."""
+    rng = random.Random(3)
+    maps = [(1, 1), (1, 300), (200, 1), (9, 12), (18, 24), (36, 48), (54, 72), (45, 60), (5, 3)]
+    maps += [(rng.randint(1, 150), rng.randint(1, 250)) for _ in range(300)]
+    cases = [(h, w, c, rng.choice([1, 300, 600, 1100, 2051])) for h, w in maps for c in (16, 32, 64, 128)]
+    out = host_program.build(tmp_path, MAIN)([" ".join(map(str, c)) for c in cases])
+    assert len(out) == len(cases)
+    for case, line in zip(cases, out):
+        if line != "-":
+            lds, tiles, limit, pixels, need, cover = map(int, line.split())
+            assert lds <= 160 * 1024 and 1 <= tiles <= limit and need <= pixels and cover, (case, line)
+    assert sum(line != "-" for line in out) > len(out) // 2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("frame,sections,batch", [
+    ((120, 192, 3), (16,), 300),          # four strips, inner ones with halos on both sides
+    ((107, 144, 4), (32,), 130),          # six, the last one shorter
+    ((59, 37, 3), (64,), 200),            # two of 15 rows
+    ((9, 13, 1), (16,), 1100),            # stacks of four, feature rows padded to whole chunks, a last stack of fewer images
+    ((9, 13, 16), (16, 32), 1025),
+], ids=str)
+def test_one_launch_gives_the_bits_of_two(orc, frame, sections, batch):
+    """Rows of a large batch, whose blocks run in one launch, equal the same rows in a batch of one on the tile kernels,
+    and the oracle."""
+    import torch
+    h, w, c = frame
+    cfg = dict(wl.CONFIGS["C3"], label=f"{h}x{w}x{c}, sections {sections}", index=131, obs_h=h, obs_w=w, obs_c=c, sections=list(sections), fc_units=16)
+    weights, batch_in = wl.make_weights(cfg), wl.make_batch(cfg, batch)
+    net = seedinf.SeedInfer(seedinf.make_arch(cfg, max_batch=batch), weights)
+    out = net.step(**to_device(batch_in))
+    torch.cuda.synchronize()
+    big = net.read_intermediate(0, batch).cpu().numpy()
+    got = {k: v.cpu().numpy() for k, v in out.items()}
+    for row in (0, 1, batch // 2, batch - 2, batch - 1):
+        part = {k: None if v is None else np.ascontiguousarray(v[[row]]) for k, v in batch_in.items()}
+        net.step(**to_device(part))
+        np.testing.assert_array_equal(net.read_intermediate(0, 1).cpu().numpy()[0], big[row])
+    net.close()
+    rows = [0, batch - 1]
+    pick = lambda v: None if v is None else np.ascontiguousarray(v[rows])  # noqa: E731
+    ref = orc.forward(oracle.make_arch(cfg), weights, pick(batch_in["obs"]), **{k: pick(batch_in[k]) for k in ("prev_action", "prev_reward", "h_in", "c_in", "uniforms")})
+    check_against_oracle({k: v[rows] for k, v in got.items()}, ref, 2e-2, pick(batch_in["uniforms"]))
