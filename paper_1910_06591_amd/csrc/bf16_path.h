@@ -22,6 +22,7 @@
 #include "resnet_convtile.h"
 #include "resnet_strip.h"
 #include "resnet_pair.h"
+#include "resnet_rows.h"
 
 namespace seedinf {
 
@@ -126,6 +127,7 @@ struct LwSectionPlan {
     int tiles = 0; long tile_cells = 0;        // the tile kernels': workgroups an image, cells a block's convolutions walk
     StripBlockPlan strip_block;
     StripPoolPlan strip_pool;
+    TileCut first_rows;                        // first layer pooled down the rows: h pooled rows to a strip, w strips
     PairPlan pair;                             // both blocks in one launch with x in registers, where that is the faster cut
     bool strips = false;                       // the strip kernels cover conv0 + pooling and the blocks
 };
@@ -571,6 +573,10 @@ inline seed_status_t bf16_create(const Plan& p, const float* d_w, Bf16State** ou
         set((const void*)strip_block_kernel<32, true>, RS_LDS_MAX); set((const void*)strip_block_kernel<32, false>, RS_LDS_MAX);
         set((const void*)strip_block_kernel<64, true>, RS_LDS_MAX); set((const void*)strip_block_kernel<64, false>, RS_LDS_MAX);
         set((const void*)strip_block_kernel<128, true>, RS_LDS_MAX); set((const void*)strip_block_kernel<128, false>, RS_LDS_MAX);
+        set((const void*)first_rows_kernel<1, 16>, FR_LDS_MAX); set((const void*)first_rows_kernel<1, 32>, FR_LDS_MAX); set((const void*)first_rows_kernel<1, 64>, FR_LDS_MAX);
+        set((const void*)first_rows_kernel<3, 16>, FR_LDS_MAX); set((const void*)first_rows_kernel<3, 32>, FR_LDS_MAX); set((const void*)first_rows_kernel<3, 64>, FR_LDS_MAX);
+        set((const void*)first_rows_kernel<4, 16>, FR_LDS_MAX); set((const void*)first_rows_kernel<4, 32>, FR_LDS_MAX); set((const void*)first_rows_kernel<4, 64>, FR_LDS_MAX);
+        set((const void*)first_rows_kernel<16, 16>, FR_LDS_MAX); set((const void*)first_rows_kernel<16, 32>, FR_LDS_MAX); set((const void*)first_rows_kernel<16, 64>, FR_LDS_MAX);
         set((const void*)resblock_pair_kernel<16>, RP_LDS_MAX); set((const void*)resblock_pair_kernel<32>, RP_LDS_MAX);
         set((const void*)resblock_pair_kernel<64>, RP_LDS_MAX); set((const void*)resblock_pair_kernel<128>, RP_LDS_MAX);
         set((const void*)strip_pool_kernel<16>, RS_LDS_MAX); set((const void*)strip_pool_kernel<32>, RS_LDS_MAX);
@@ -778,6 +784,50 @@ inline bool launch_first_pool(hipStream_t st, const LwLayerDev& d, const bf16x8*
     });
 }
 
+// Calls go(planes, output channels) where the first layer can be pooled down its rows; false elsewhere.
+template <class F>
+inline bool first_rows_by_layer(const LwLayerDev& d, const ConvLayer& c, F go)
+{
+    if (d.first_off == LW_NONE) return false;
+    auto by_cout = [&](auto cin) {
+        switch (c.Cout) {
+        case 16: return go(cin, std::integral_constant<int, 16>{});
+        case 32: return go(cin, std::integral_constant<int, 32>{});
+        case 64: return go(cin, std::integral_constant<int, 64>{});
+        default: return false;
+        }
+    };
+    switch (c.Cin) {
+    case 1: return by_cout(std::integral_constant<int, 1>{});
+    case 3: return by_cout(std::integral_constant<int, 3>{});
+    case 4: return by_cout(std::integral_constant<int, 4>{});
+    case 16: return by_cout(std::integral_constant<int, 16>{});
+    default: return false;
+    }
+}
+
+// The first layer with its pooling to x as bf16, pooled down the rows (resnet_rows.h): false, and nothing launched, where
+// first_pool_kernel is the faster one.  With strips of one pooled row a third of the convolution rows are computed twice (16
+// planes on 20 x 300, 256 frames: 24 -> 28 us against 40 x 400 x 3, two rows, 68 -> 55); and a strip is a compute unit's half, so with few of
+// them the tiles use more of the chip (72 x 96 x 3 -> 64 channels, 288 strips: 9.0 -> 10.5, 576: 16.2 -> 14.3; -> 32, 256: 10.6 ->
+// 8.6, 128: 6.8 -> 7.8; 144 x 192 x 4 -> 64, 288: 8.7 -> 10.5).
+inline bool launch_first_rows(hipStream_t st, const LwLayerDev& d, const bf16x8* wp_conv, const float* d_w, const Section& sec,
+                              const TileCut& cut, int B, int n_cu, const uint8_t* obs, __bf16* x)
+{
+    const ConvLayer& c = sec.conv0;
+    if (cut.h < 2 || (long)B * cut.w < 2L * n_cu) return false;
+    return first_rows_by_layer(d, c, [&](auto cin, auto cout) {
+        constexpr int CIN = decltype(cin)::value, COUT = decltype(cout)::value;
+        FirstRowsArgs a{};
+        a.in = obs; a.wp = wp_conv + d.first_off / 8; a.bias = d_w + c.b_off; a.scale = 1.0f / 255.0f; a.x = x;
+        a.B = B; a.H = c.H; a.W = c.W; a.PH = sec.PH; a.PW = sec.PW; a.pad_h = sec.pool_pad_h; a.pad_w = sec.pool_pad_w;
+        a.PTH = cut.h; a.strips = cut.w; a.groups = B * cut.w;
+        hipLaunchKernelGGL((first_rows_kernel<CIN, COUT>), dim3(std::min(a.groups, 2 * n_cu)), dim3(FR_THREADS),
+                           (FirstRowsCfg<CIN, COUT>::lds_bytes(cut.h, c.W)), st, a);
+        return true;
+    });
+}
+
 // conv0 of a later section with its pooling as one launch (bf16 NHWC map -> fp32 x and, if r is given, ReLU(x) as
 // bf16); false when the channel pair has no fused kernel, and nothing was launched.
 template <class F>
@@ -934,6 +984,10 @@ inline LwSectionPlan plan_lw_section(const Section& sec, const LwLayerDev* d, bo
             if (decltype(cellc)::value != 4 && d[0].kchunks != K::KCH) return false;
             return cut(pl.first, [&](int& h, int& w) { return K::choose(sec.PH, sec.PW, h, w); });
         });
+    if (first)
+        first_rows_by_layer(d[0], c, [&](auto cin, auto cout) {
+            return cut(pl.first_rows, [&](int& h, int& w) { return FirstRowsCfg<decltype(cin)::value, decltype(cout)::value>::choose(sec.PH, c.W, h, w); });
+        });
     else
         conv_pool_by_channels(c.Cin, c.Cout, [&](auto ci, auto co) {
             return cut(pl.pool, [&](int& h, int& w) { return ConvPoolCfg<decltype(ci)::value, decltype(co)::value>::choose(sec.PH, sec.PW, h, w); });
@@ -1086,8 +1140,10 @@ inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w
             const LwSectionPlan& pl = s->lw_plan[si];
             // conv0 + pooling, then both blocks, on the strip kernels
             if (strips_preferred(pl, sec.conv0.Cout, B, s->n_cu)) {
-                if (si == 0) launch_first_pool(st, s->lw[li], W.wp_conv, d_w, sec, pl.first, B, obs, nullptr, s->lw_u);
-                else launch_strip_pool(st, s->lw[li], W.wp_conv, d_w, sec, pl.strip_pool, B, (const __bf16*)in, s->lw_u);
+                if (si == 0) {
+                    if (!launch_first_rows(st, s->lw[li], W.wp_conv, d_w, sec, pl.first_rows, B, s->n_cu, obs, s->lw_u))
+                        launch_first_pool(st, s->lw[li], W.wp_conv, d_w, sec, pl.first, B, obs, nullptr, s->lw_u);
+                } else launch_strip_pool(st, s->lw[li], W.wp_conv, d_w, sec, pl.strip_pool, B, (const __bf16*)in, s->lw_u);
                 __bf16* const y = last_sec ? s->feat : s->lw_r;
                 const int y_relu = last_sec ? 1 : 0, ldy = last_sec ? s->ldf : 0;
                 if (pl.pair.TH) launch_pair(st, &s->lw[li + 1], W.wp_conv, d_w, sec, pl.pair, B, s->n_cu, s->lw_u, y, y_relu, ldy);

@@ -1,13 +1,9 @@
 """Both residual blocks of a section in one launch: its strips on the CPU, its kernel against the oracle and the other kernels."""
 import random
 
-import numpy as np
 import pytest
 
-import oracle
-from paper_1910_06591_amd import seedinf, workloads as wl
-from tests import host_program
-from tests.parity import check_against_oracle, to_device
+from tests import batch_bits, host_program
 
 MAIN = r"""
 // per map: LDS bytes, the most pixel tiles of a wavefront and its limit, pixels of the incoming map asked for and needed, and
@@ -66,21 +62,4 @@ def test_strips_fit_lds_and_the_registers(tmp_path):
 def test_one_launch_gives_the_bits_of_two(orc, frame, sections, batch):
     """Rows of a large batch, whose blocks run in one launch, equal the same rows in a batch of one on the tile kernels,
     and the oracle."""
-    import torch
-    h, w, c = frame
-    cfg = dict(wl.CONFIGS["C3"], label=f"{h}x{w}x{c}, sections {sections}", index=131, obs_h=h, obs_w=w, obs_c=c, sections=list(sections), fc_units=16)
-    weights, batch_in = wl.make_weights(cfg), wl.make_batch(cfg, batch)
-    net = seedinf.SeedInfer(seedinf.make_arch(cfg, max_batch=batch), weights)
-    out = net.step(**to_device(batch_in))
-    torch.cuda.synchronize()
-    big = net.read_intermediate(0, batch).cpu().numpy()
-    got = {k: v.cpu().numpy() for k, v in out.items()}
-    for row in (0, 1, batch // 2, batch - 2, batch - 1):
-        part = {k: None if v is None else np.ascontiguousarray(v[[row]]) for k, v in batch_in.items()}
-        net.step(**to_device(part))
-        np.testing.assert_array_equal(net.read_intermediate(0, 1).cpu().numpy()[0], big[row])
-    net.close()
-    rows = [0, batch - 1]
-    pick = lambda v: None if v is None else np.ascontiguousarray(v[rows])  # noqa: E731
-    ref = orc.forward(oracle.make_arch(cfg), weights, pick(batch_in["obs"]), **{k: pick(batch_in[k]) for k in ("prev_action", "prev_reward", "h_in", "c_in", "uniforms")})
-    check_against_oracle({k: v[rows] for k, v in got.items()}, ref, 2e-2, pick(batch_in["uniforms"]))
+    batch_bits.check(orc, frame, sections, batch)
