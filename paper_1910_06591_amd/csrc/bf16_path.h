@@ -957,14 +957,13 @@ inline bool strip_by_width(int C, F go)
 
 // Whether both blocks in one launch (resnet_pair.h) beat a launch of strips per block: by the map cells walked, which the
 // longer halo of the one launch multiplies.  Measured at 256 images, us, strips -> one launch at so many times the cells:
-// 16 channels on 54 x 72 69 -> 42 (1.1), 60 x 96 92 -> 61 (1.29), 80 x 108 146 -> 122 (1.36), 50 x 150 142 -> 137 (1.62), 40 x 240
-// 186 -> 332; 32 on 36 x 48 65 -> 46 (1.13), 54 x 72 160 -> 140 (1.49), 45 x 60 107 -> 84 (1.5), 40 x 100 164 -> 206 (2.2); 64,
-// where matrix cores weigh more, on 18 x 24 50 -> 37 (1), 20 x 30 70 -> 58 (1.24), 12 x 60 81 -> 86 (1.4), 27 x 36 104 -> 122
-// (1.54); 128 on 14 x 18 83 -> 68 (1), 10 x 30 108 -> 132 (1.45).  Below the line at 1 to 1024 images alike (1 image: 32
-// channels on 36 x 48 34 -> 20, 64 on 18 x 24 38 -> 27).
-inline bool pair_preferred(const PairPlan& pair, const StripBlockPlan& strip, int C)
+// 16 channels on 60 x 96 83 -> 70 (1.30), 80 x 108 118 -> 118 (1.36), 50 x 150 105 -> 128 (1.63); 32 on 36 x 48 53 -> 39 (1.13),
+// 54 x 72 118 -> 122 (1.49), 45 x 60 88 -> 82 (1.5), 30 x 80 78 -> 89 (1.82); 64 on 18 x 24 42 -> 31 (1), 20 x 30 56 -> 51 (1.24),
+// 12 x 60 66 -> 65 (1.4), 27 x 36 83 -> 96 (1.54); 128 on 14 x 20 85 -> 64 (0.9), 10 x 30 89 -> 107 (1.45).  Alike at 1 to
+// 1024 images.
+inline bool pair_preferred(const PairPlan& pair, const StripBlockPlan& strip)
 {
-    return 20 * pair.cells <= (C >= 64 ? 26 : 31) * 2 * strip.cells;
+    return 20 * pair.cells <= 27 * 2 * strip.cells;
 }
 
 // The kernels that cover a section, d: its five convolutions.
@@ -1017,7 +1016,7 @@ inline LwSectionPlan plan_lw_section(const Section& sec, const LwLayerDev* d, bo
     if (pl.strips)
         strip_by_width(ba.Cin, [&](auto cc) {
             PairPlan pair;
-            if (pair.choose<decltype(cc)::value>(ba.H, ba.W) && pair_preferred(pair, pl.strip_block, ba.Cin)) pl.pair = pair;
+            if (pair.choose<decltype(cc)::value>(ba.H, ba.W) && pair_preferred(pair, pl.strip_block)) pl.pair = pair;
             return true;
         });
     return pl;
@@ -1049,27 +1048,22 @@ inline bool strips_preferred(const LwSectionPlan& pl, int C, int B, int n_cu)
 
 // Both residual blocks of a section: xb (bf16, the pooled map) -> y; x is the fp32 stream between them.
 inline void launch_strip_blocks(hipStream_t st, const LwLayerDev* d, const bf16x8* wp_conv, const float* d_w, const Section& sec,
-                                const StripBlockPlan& pl, int B, int n_cu, const __bf16* xb, float* x, __bf16* y, int y_relu, int ldy)
+                                const StripBlockPlan& pl, int B, const __bf16* xb, float* x, __bf16* y, int y_relu, int ldy)
 {
     strip_by_width(sec.conv0.Cout, [&](auto cc) {
         constexpr int CC = decltype(cc)::value;
         StripBlockArgs a{};
-        a.B = B; a.H = sec.PH; a.W = sec.PW; a.TH = pl.TH; a.strips = pl.strips; a.nblk = pl.blocks();
-        a.stack = pl.stack<CC>(B, sec.PH, sec.PW, n_cu);
-        a.groups = a.stack > 1 ? (B + a.stack - 1) / a.stack : B * pl.strips;
-        a.x_out = x; a.y_relu = y_relu; a.ldy = ldy;
-        const int rows = a.stack > 1 ? a.stack * (sec.PH + 1) - 1 : pl.conv_a_rows(pl.TH, pl.strips);
-        const size_t lds = StripCfg<CC>::lds_bytes(rows + 2, sec.PW);
-        auto weights = [&](int at, int conv) { a.wp[at] = wp_conv + d[conv].wp_off / 8; a.bias[at] = d_w + sec.block[conv].b_off; };
-        for (int i = 0; i < 2 * a.nblk; ++i) weights(i, i);
-        a.x_in = xb;
-        a.y = a.nblk == 2 ? y : nullptr;
+        a.B = B; a.H = sec.PH; a.W = sec.PW; a.TH = pl.TH; a.strips = pl.strips; a.groups = B * pl.strips;
+        const size_t lds = StripCfg<CC>::lds_bytes(pl.conv_a_rows(pl.TH, pl.strips) + 2, sec.PW);
+        auto weights = [&](int conv) {
+            for (int i = 0; i < 2; ++i) { a.wp[i] = wp_conv + d[conv + i].wp_off / 8; a.bias[i] = d_w + sec.block[conv + i].b_off; }
+        };
+        weights(0);
+        a.x_in = xb; a.x_out = x;
         hipLaunchKernelGGL((strip_block_kernel<CC, true>), dim3(a.groups), dim3(RS_THREADS), lds, st, a);
-        if (a.nblk == 1) {
-            weights(0, 2); weights(1, 3);
-            a.x_in = x; a.x_out = nullptr; a.y = y;
-            hipLaunchKernelGGL((strip_block_kernel<CC, false>), dim3(a.groups), dim3(RS_THREADS), lds, st, a);
-        }
+        weights(2);
+        a.x_in = x; a.x_out = nullptr; a.y = y; a.y_relu = y_relu; a.ldy = ldy;
+        hipLaunchKernelGGL((strip_block_kernel<CC, false>), dim3(a.groups), dim3(RS_THREADS), lds, st, a);
         return true;
     });
 }
@@ -1147,7 +1141,7 @@ inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w
                 __bf16* const y = last_sec ? s->feat : s->lw_r;
                 const int y_relu = last_sec ? 1 : 0, ldy = last_sec ? s->ldf : 0;
                 if (pl.pair.TH) launch_pair(st, &s->lw[li + 1], W.wp_conv, d_w, sec, pl.pair, B, s->n_cu, s->lw_u, y, y_relu, ldy);
-                else launch_strip_blocks(st, &s->lw[li + 1], W.wp_conv, d_w, sec, pl.strip_block, B, s->n_cu, s->lw_u, s->lw_x, y, y_relu, ldy);
+                else launch_strip_blocks(st, &s->lw[li + 1], W.wp_conv, d_w, sec, pl.strip_block, B, s->lw_u, s->lw_x, y, y_relu, ldy);
                 li += 5;
                 in = s->lw_r;
                 continue;

@@ -208,7 +208,7 @@ __global__ __launch_bounds__(RP_THREADS, 2) void resblock_pair_kernel(PairArgs p
         const bf16x8* wl[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) wl[k] = p.wp[k] + fg * FTW * S::KCH * 64;
-        StripWeights<C, FTW == 2> w;
+        StripWeights<C, C >= 64 ? 3 : 2> w;
         for (int it = first;;) {
             const Item t = item_at(it);
             const int next = it + wgs;
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(RP_THREADS, 2) void resblock_pair_kernel(PairArgs p
                     const int g = fresh_lane(lane) >> 4;
 #pragma unroll
                     for (int j = 0; j < FTW; ++j) bv[j] = *(const floatx4*)(p.bias[conv] + fg * FTW * 16 + g * CPL + j * 4);
-                    strip_conv<C, NT, RING, FTW == 2>(map, PL, P, pg, npa - 1, wl[conv], lane, w, acc, tail);
+                    strip_conv<C, NT, RING>(map, PL, P, pg, npa - 1, wl[conv], lane, w, acc, tail);
                 };
                 floatx4 acc[NT][FTW], bv[FTW];
                 // (every convolution requests the next one's first weights before its epilogue)

@@ -2,7 +2,7 @@
 // bf16_path.h): conv0 + pooling of a section, and its residual blocks, each in one launch over ONE LDS map that every
 // convolution rewrites in place.  (Both blocks in one launch where their halo allows it: resnet_pair.h.)
 //
-// A workgroup takes TH rows of an image (all W columns), a whole image or several stacked ones.  The map is planar
+// A workgroup takes TH rows of an image (all W columns).  The map is planar
 // bf16 [C/8][cells][8 channels]; a row is W + 1 cells, cell 0 of which is zero: it is the left border of its own row
 // and the right border of the row above (SAME padding without a second border column).  The output pixels of a
 // convolution are walked flat over the map, border cells included (computed, and kept zero): a tile is 16
@@ -18,15 +18,16 @@
 // unit) serve up to 9 pixel tiles instead of 4 or 5, and the halo that neighbouring strips recompute shrinks.
 // Weight packing: A fragments [feature tile][chunk][lane][8], k = tap * C + ci.
 //
-// Measured, 1024 images, us per launch, against the kernels that keep an input and an output map (resnet_blockfused.h,
-// resnet_convpool.h, resnet_convtile.h), a section's two blocks together: 64 channels on 36 x 48 915 -> 635, on 18 x 24
-// 222 -> 135, on 9 x 12 82 -> 45; 128 channels on 18 x 24 680 -> 475, on 9 x 12 199 -> 123; 32 channels on 36 x 48 333 ->
-// 240, on 27 x 36 174 -> 111; 16 channels on 54 x 72 273 -> 253.  conv0 + pooling: 64 -> 128 on 36 x 48 339 -> 292, 128 ->
-// 128 on 18 x 24 212 -> 126, 32 -> 64 on 36 x 48 120 -> 85, 16 -> 32 on 54 x 72 107 -> 77.
-// What bounds them now (64 channels on 36 x 48, cycles of a workgroup's 78 K): staging 15 K, about 5 K of it bank conflicts
-// of its writes (33 % of the kernel's LDS cycles, 46 % in the pooling kernel), the epilogue 22 K of memory, the two
-// convolutions 36 K for 18 K of MFMAs (two workgroups share the matrix cores).  HBM traffic by counters: 0.96 GB in the first
-// block, 1.21 in the second (fp32 in), 155 and 190 us at the copy rate; the MFMAs take 119 us.
+// Measured, 1024 images, us, a section's two blocks together: 64 channels on 36 x 48 647 -> 584, 128 on 18 x 24 573 -> 474; 512
+// images: 32 channels on 40 x 100 327 -> 268; 64 images: 16 on 60 x 400 173 -> 142; conv0 + pooling 64 -> 128 on 36 x 48 350 -> 296,
+// 64 -> 64 on 18 x 24 61 -> 39; before: a cell as one 16-byte access per lane (the lanes of a feature tile pair fetch the
+// packed weights' rows so that a lane's eight results are consecutive channels) instead of two of 8 bytes; border
+// cells skipped, not rewritten with zeros; weights two chunks in registers, not three (at 128 registers to a wavefront the third
+// spills now); no pointer picked at run time (its loads are flat ones and count as LDS traffic).  (The kernels
+// that keep an input and an output map took 915 us for 64 channels on 36 x 48, 680 for 128 on 18 x 24.)
+// What bounds them (64 channels on 36 x 48): HBM traffic 0.96 GB in the first block, 1.21 in the second (fp32 in), 155 and 190 us
+// at the copy rate; the MFMAs take 119 us; about 5 K of the staging's 15 K cycles of a workgroup are bank conflicts of its
+// writes.
 #pragma once
 #include "resnet_blockfused.h"
 
@@ -34,7 +35,7 @@ namespace seedinf {
 
 constexpr int RS_THREADS = 512;
 constexpr size_t RS_LDS_MAX = 80 * 1024;                    // two workgroups per compute unit
-constexpr int RS_MAX_STACK = 4;                             // images a workgroup stacks
+constexpr int RS_MAX_STACK = 4;                             // images a workgroup stacks (resnet_pair.h)
 
 template <int C>
 struct StripCfg {
@@ -65,9 +66,9 @@ __device__ __forceinline__ int xcd_run(int idx, int total)
 }
 
 // Zeroes a map's border cells: cell 0 of every row and the one behind the last row, the first and the last row where
-// they lie outside the image, and (period > 0) every row between stacked images.
+// they lie outside the image.
 template <int C>
-__device__ __forceinline__ void zero_borders(char* map, int PL, int P, int rows, bool top, bool bottom, int period, int tid)
+__device__ __forceinline__ void zero_borders(char* map, int PL, int P, int rows, bool top, bool bottom, int tid)
 {
     constexpr int NCG = C / 8, STEP = RS_THREADS / NCG;
     const bf16x8 z = {};
@@ -76,8 +77,6 @@ __device__ __forceinline__ void zero_borders(char* map, int PL, int P, int rows,
     for (int c = tid / NCG; c < P; c += STEP) {
         if (top) *(bf16x8*)(plane + c * 16) = z;
         if (bottom) *(bf16x8*)(plane + ((rows - 1) * P + c) * 16) = z;
-        if (period > 0)
-            for (int r = period; r < rows - 1; r += period) *(bf16x8*)(plane + (r * P + c) * 16) = z;
     }
 }
 
@@ -91,20 +90,18 @@ __device__ __forceinline__ int fresh_lane(int lane)
 // Pixel tiles whose map fragments strip_conv keeps requested ahead: divides NT so that a slot serves the same tiles in every chunk.
 constexpr int strip_ring(int NT) { return NT % 4 == 0 ? 4 : (NT % 3 == 0 ? 3 : (NT % 5 == 0 ? 5 : NT)); }
 
-// A wavefront's weight fragments: WS slots, requested WS - 1 chunks ahead.  Three where two feature groups or more pull 36
-// KiB and up per convolution through the vector L1 (64 channels on 36 x 48 370 -> 362 us, 128 on 18 x 24 257 -> 244); at
-// 32 channels the registers they take cost more (129 -> 147 us), and so at 16.
-// WIDE (FTW = 2): the two fragments together hold, for lane group g of the result, the eight consecutive channels 8 g ..
-// 8 g + 7 of the pair's 32 instead of four of each tile (the lanes fetch the rows of the packed weights in that order).
-template <int C, bool WIDE>
+// A wavefront's weight fragments: WS slots, requested WS - 1 chunks ahead.
+// With two feature tiles (FTW = 2) the two fragments together hold, for lane group g of the result, the eight consecutive
+// channels 8 g .. 8 g + 7 of the pair's 32 instead of four of each tile: the lanes fetch the rows of the packed weights in
+// that order.
+template <int C, int WS = 2>
 struct StripWeights {
     using K = StripCfg<C>;
-    static constexpr int FTW = K::FTW, KCH = K::KCH, WS = C >= 64 ? 3 : 2, WJ = WIDE ? 4 : KCH * 64;
-    static_assert(!WIDE || FTW == 2, "feature tile pairs");
+    static constexpr int FTW = K::FTW, KCH = K::KCH, WJ = 4;
     bf16x8 a[WS][FTW];
     __device__ static __forceinline__ int first(int lane)
     {
-        return WIDE ? ((lane & 8) >> 3) * KCH * 64 + (lane & 48) + (lane & 4) * 2 + (lane & 3) : lane;
+        return FTW == 2 ? ((lane & 8) >> 3) * KCH * 64 + (lane & 48) + (lane & 4) * 2 + (lane & 3) : lane;
     }
     __device__ __forceinline__ void request(const bf16x8* __restrict__ wl, int kc, int slot, int lane)
     {
@@ -123,12 +120,12 @@ struct StripWeights {
 // (0, 0) of its first pixel, plane 0): pixel q has tap (kh, kw) at cell q + kh * P + kw.  `last`: the region's last
 // pixel, which lanes past the end read again.  The weights' first chunks have been requested (start); tail() runs
 // behind the request of the last ones.
-template <int C, int NT, int RING = strip_ring(NT), bool WIDE = false, class Tail>
+template <int C, int NT, int RING, int WS, class Tail>
 __device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int pg, int last, const bf16x8* __restrict__ wl, int lane,
-                                           StripWeights<C, WIDE>& w, floatx4 (&acc)[NT][StripCfg<C>::FTW], Tail tail)
+                                           StripWeights<C, WS>& w, floatx4 (&acc)[NT][StripCfg<C>::FTW], Tail tail)
 {
     using K = StripCfg<C>;
-    constexpr int FTW = K::FTW, KCH = K::KCH, STEP = K::NPG * 256, WS = StripWeights<C, WIDE>::WS;
+    constexpr int FTW = K::FTW, KCH = K::KCH, STEP = K::NPG * 256;
     static_assert(NT % RING == 0, "a ring slot's tiles");
     // Map fragments travel in a ring of RING registers sets, RING tiles (of this chunk or the next) ahead of their use.
     // The order is pinned: left alone, the compiler saves registers by asking for every fragment right before its MFMAs,
@@ -180,7 +177,7 @@ __device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int p
     using D0 = std::integral_constant<int, 0>; using D1 = std::integral_constant<int, 1>; using D2 = std::integral_constant<int, 2>;
     using T = std::true_type; using F = std::false_type;
     constexpr int LEFT = KCH % WS == 0 ? WS : KCH % WS;      // chunks behind the loop
-    static_assert(KCH % WS <= 1 && (KCH % WS == 1 ? WS == 2 : WS == 3), "the last groups below");
+    static_assert(LEFT <= WS && (WS == 2 || KCH % WS == 0), "the last groups below");
 #pragma unroll 1
     for (int kc = 0; kc < KCH - LEFT; kc += WS) {
         chunk(kc, D0{}, T{}, T{});
@@ -192,20 +189,15 @@ __device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int p
         tail();
         chunk(KCH - 2, D1{}, F{}, T{});
         chunk(KCH - 1, D2{}, F{}, F{});
+    } else if constexpr (LEFT == 2) {
+        chunk(KCH - 2, D0{}, T{}, T{});
+        tail();
+        chunk(KCH - 1, D1{}, F{}, F{});
     } else {
         tail();
         chunk(KCH - 1, D0{}, F{}, F{});
     }
 }
-template <int C, int NT>
-__device__ __forceinline__ void strip_conv(const char* src, int PL, int P, int pg, int last, const bf16x8* __restrict__ wl, int lane,
-                                           floatx4 (&acc)[NT][StripCfg<C>::FTW])
-{
-    StripWeights<C, false> w;
-    w.start(wl, fresh_lane(lane));
-    strip_conv<C, NT>(src, PL, P, pg, last, wl, lane, w, acc, [] {});
-}
-
 // Calls phase(NT) for the number of pixel tiles this wavefront owns (uniform): a convolution and its epilogue with the
 // count a constant.  (Barriers inside: every wavefront passes the same number of them whatever its count.  The plans give
 // at most TPW; the clamp keeps a count beyond it from passing none.)
@@ -251,14 +243,13 @@ struct TileWalk {
 
 // ---- residual blocks ----------------------------------------------------------
 struct StripBlockArgs {
-    const void* x_in;                  // [B, H, W, C]: bf16 (X_BF16: the pooled map, whose values are bf16 by origin) or fp32
-    const bf16x8* wp[4];               // conv_a, conv_b of the first block (and of the second)
-    const float* bias[4];
-    float* x_out;                      // fp32 x' of the first block [B, H, W, C]; unused by a lone closing block
-    __bf16* y;                         // bf16 output of the closing block, or nullptr
+    const void* x_in;                  // [B, H, W, C]: bf16 (first block: the pooled map, whose values are bf16 by origin) or fp32
+    const bf16x8* wp[2];               // conv_a, conv_b
+    const float* bias[2];
+    float* x_out;                      // first block: fp32 x' [B, H, W, C]
+    __bf16* y;                         // second block
     int y_relu, ldy;                   // rectify y; ldy > 0: y is the feature matrix [B, ldy], (h, w, c) order
-    int B, H, W, TH, strips;           // strips of TH rows per image; strips == 1 with `stack` images per workgroup
-    int stack, nblk, groups;           // blocks in this launch (2: whole images only); workgroups
+    int B, H, W, TH, strips, groups;   // strips of TH rows per image; workgroups
 };
 
 struct StripBlockPlan {
@@ -281,10 +272,8 @@ struct StripBlockPlan {
         return best >= 0;
     }
     static int conv_a_rows(int th, int ns) { return ns == 1 ? th : (ns == 2 ? th + 1 : th + 2); }
-    // Whole images run both blocks in one launch: no halo, and x' is read back by the lanes that wrote it.
-    int blocks() const { return strips == 1 ? 2 : 1; }
-    // Small images are stacked while there are workgroups enough for two per compute unit: a lone 9 x 12 map gives a
-    // wavefront two to four tiles per weight fragment.
+    // Images that a workgroup of two per compute unit could stack.  (Whole images run in resnet_pair.h's launch, which stacks by
+    // its own plan; this one is what the plans' test measures the strip maps' LDS with.)
     template <int C>
     int stack(int B, int H, int W, int n_cu) const
     {
@@ -299,65 +288,53 @@ struct StripBlockPlan {
     }
 };
 
-template <int C, bool X_BF16>
+// FIRST: bf16 in, fp32 out; else fp32 in, bf16 out.
+template <int C, bool FIRST>
 __global__ __launch_bounds__(RS_THREADS, 4) void strip_block_kernel(StripBlockArgs p)
 {
     using K = StripCfg<C>;
-    constexpr int FTW = K::FTW, TPW = K::TPW;
+    constexpr int FTW = K::FTW, TPW = K::TPW, CPL = 4 * FTW;      // a lane's channels of a pixel
+    typedef __bf16 lane_bf16 __attribute__((ext_vector_type(CPL)));
     extern __shared__ __attribute__((aligned(16))) char rs_lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wg = xcd_run(blockIdx.x, p.groups);
-    const int P = p.W + 1, Hp = p.H + 1;
-    const bool stacked = p.stack > 1;
-    const int b = stacked ? wg * p.stack : wg / p.strips;
-    const int y0 = stacked ? 0 : (wg % p.strips) * p.TH;
+    const int P = p.W + 1;
+    const int b = wg / p.strips;
+    const int y0 = (wg % p.strips) * p.TH;
     const int ye = min(y0 + p.TH, p.H);                      // the strip's rows: y0 .. ye - 1
-    const int nimg = min(p.stack, p.B - b);
     // map row 0 is image row m0; conv_a covers image rows ya .. yz - 1, conv_b the strip's
     const int m0 = max(y0 - 2, -1), ya = max(y0 - 1, 0), yz = min(ye + 1, p.H);
     const int arow = ya - m0, brow = y0 - m0;
-    const int ra = stacked ? nimg * Hp - 1 : yz - ya, rb = stacked ? ra : ye - y0;
+    const int ra = yz - ya, rb = ye - y0;
     const int MR = arow + ra + 1;
     const int PL = K::plane(MR, p.W);
     const size_t img = (size_t)p.H * p.W * C;
 
-    // (image, row) of a map row; rows between stacked images and outside an image are zero
-    auto image_row = [&](int r, int& im, int& y) {
-        y = m0 + r;
-        im = 0;
-        if (stacked) {
-#pragma unroll
-            for (int k = 1; k < RS_MAX_STACK; ++k)
-                if (y >= Hp) { y -= Hp; ++im; }
-        }
-        return y >= 0 && y < p.H && im < nimg;
-    };
-
     // ---- R = ReLU(x) as bf16 ----
-    // The strip's pixels (of all stacked images) are one run of memory, so an item's address is a running offset and
+    // The strip's pixels are one run of memory, so an item's address is a running offset and
     // only its cell needs a (row, column) walk; the border cells are zeroed apart (walked cell by cell with the border in
     // it, the loop spent 25 K cycles of a workgroup against 15 K: 64 channels on 36 x 48, 334 -> 310 us).  All of a
     // thread's loads, or half of them in fp32, are requested before the first conversion.
     {
-        constexpr int UNR = X_BF16 ? 10 : 5, CSTEP = RS_THREADS / K::NCG;
+        constexpr int UNR = FIRST ? 10 : 5, CSTEP = RS_THREADS / K::NCG, EB = FIRST ? 2 : 4;
         static_assert(RS_THREADS % K::NCG == 0, "a thread keeps its channel group");
         const int cg = tid % K::NCG;
-        const int t0 = max(m0, 0), t1 = min(m0 + MR, p.H);      // image rows in the map (one image)
-        const int npx = stacked ? nimg * p.H * p.W : (t1 - t0) * p.W;
-        const char* src = (const char*)p.x_in + (b * img + (size_t)t0 * p.W * C) * (X_BF16 ? 2 : 4);
-        zero_borders<C>(rs_lds, PL, P, MR, m0 < 0, m0 + MR > p.H, stacked ? Hp : 0, tid);
+        const int t0 = max(m0, 0), t1 = min(m0 + MR, p.H);      // image rows in the map
+        const int npx = (t1 - t0) * p.W;
+        const char* src = (const char*)p.x_in + (b * img + (size_t)t0 * p.W * C) * EB;
+        zero_borders<C>(rs_lds, PL, P, MR, m0 < 0, m0 + MR > p.H, tid);
         RowWalk rw(tid / K::NCG, CSTEP, p.W);
         int px = tid / K::NCG;
-        uint32_t from = (uint32_t)(px * C + cg * 8) * (X_BF16 ? 2 : 4);
+        uint32_t from = (uint32_t)(px * C + cg * 8) * EB;
         char* const plane = rs_lds + (cg * PL + (t0 - m0) * P + 1) * 16;
         for (; px < npx; px += UNR * CSTEP) {
             floatx4 lo[UNR], hi[UNR];
             bf16x8 v[UNR];
 #pragma unroll
-            for (int u = 0; u < UNR; ++u, from += CSTEP * C * (X_BF16 ? 2 : 4)) {
+            for (int u = 0; u < UNR; ++u, from += CSTEP * C * EB) {
                 if (px + u * CSTEP >= npx) continue;
-                if constexpr (X_BF16) {
+                if constexpr (FIRST) {
                     v[u] = *(const bf16x8*)(src + from);
                 } else {
                     lo[u] = *(const floatx4*)(src + from);
@@ -366,15 +343,10 @@ __global__ __launch_bounds__(RS_THREADS, 4) void strip_block_kernel(StripBlockAr
             }
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
-                int r = rw.r;
-                if (stacked) {                                   // a zero row between images
-#pragma unroll
-                    for (int k = 1; k < RS_MAX_STACK; ++k) r += rw.r >= k * p.H;
-                }
-                char* cell = plane + (r * P + rw.c) * 16;
+                char* cell = plane + (rw.r * P + rw.c) * 16;
                 rw.next();
                 if (px + u * CSTEP >= npx) continue;
-                const bf16x8 raw = X_BF16 ? v[u] : to_bf16x8(lo[u], hi[u]);
+                const bf16x8 raw = FIRST ? v[u] : to_bf16x8(lo[u], hi[u]);
                 const bf16x4 l = relu_bf16x4(__builtin_shufflevector(raw, raw, 0, 1, 2, 3));
                 const bf16x4 h = relu_bf16x4(__builtin_shufflevector(raw, raw, 4, 5, 6, 7));
                 *(bf16x8*)cell = __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -384,108 +356,100 @@ __global__ __launch_bounds__(RS_THREADS, 4) void strip_block_kernel(StripBlockAr
     __syncthreads();
 
     const int fg = wave % K::NFG, pg = wave / K::NFG;
-    const int ft0 = fg * FTW;
-    // where lane group g's four channels of feature tile ft0 go in the map: plane (ft0 * 16 + 4 g) / 8, half g & 1
-    auto out_cell = [&](int g) { return rs_lds + ((ft0 * 2 + (g >> 1)) * PL) * 16 + (g & 1) * 8; };
-
     auto tiles_of = [&](int npix) { return ((npix + 15) / 16 - pg + K::NPG - 1) / K::NPG; };      // (at most TPW: the host's plan)
-    for (int blk = 0; blk < p.nblk; ++blk) {
-        // ---- U = ReLU(conv_a(R) + bias), in place ----
-        const int npa = ra * P - 1;
-        by_tiles<TPW>(tiles_of(npa), [&](auto ntc) {
-            constexpr int NT = decltype(ntc)::value;
-            if constexpr (NT == 0) {
-                __syncthreads();
-            } else {
-                floatx4 acc[NT][FTW];
-                strip_conv<C, NT>(rs_lds + (arow - 1) * P * 16, PL, P, pg, npa - 1, p.wp[2 * blk] + ft0 * K::KCH * 64, lane, acc);
-                const int ln = fresh_lane(lane), g = ln >> 4;
-                floatx4 bv[FTW];
+    auto convolve = [&](int conv, int row, int np, auto& acc, auto ntc) {
+        constexpr int NT = decltype(ntc)::value;
+        const bf16x8* const wl = p.wp[conv] + fg * FTW * K::KCH * 64;
+        StripWeights<C> w;
+        w.start(wl, fresh_lane(lane));
+        strip_conv<C, NT, strip_ring(NT)>(rs_lds + (row - 1) * P * 16, PL, P, pg, np - 1, wl, lane, w, acc, [] {});
+    };
+    auto join = [](const bf16x4 (&r)[FTW]) {
+        if constexpr (FTW == 2) return __builtin_shufflevector(r[0], r[1], 0, 1, 2, 3, 4, 5, 6, 7);
+        else return r[0];
+    };
+    // ---- U = ReLU(conv_a(R) + bias), in place (border cells keep their zeros) ----
+    const int npa = ra * P - 1;
+    by_tiles<TPW>(tiles_of(npa), [&](auto ntc) {
+        constexpr int NT = decltype(ntc)::value;
+        if constexpr (NT == 0) {
+            __syncthreads();
+        } else {
+            floatx4 acc[NT][FTW];
+            convolve(0, arow, npa, acc, ntc);
+            const int ln = fresh_lane(lane), g = ln >> 4;
+            floatx4 bv[FTW];
 #pragma unroll
-                for (int j = 0; j < FTW; ++j) bv[j] = *(const floatx4*)(p.bias[2 * blk] + (ft0 + j) * 16 + g * 4);
-                __syncthreads();                             // everybody has read R
-                TileWalk w(pg * 16 + (ln & 15), K::NPG * 16, P);
-                char* cell = out_cell(g) + (arow * P + 1 + w.q) * 16;
+            for (int j = 0; j < FTW; ++j) bv[j] = *(const floatx4*)(p.bias[0] + fg * FTW * 16 + g * CPL + j * 4);
+            __syncthreads();                                 // everybody has read R
+            TileWalk w(pg * 16 + (ln & 15), K::NPG * 16, P);
+            char* cell = rs_lds + (arow * P + 1 + w.q) * 16 + (FTW == 2 ? (fg * 4 + g) * PL * 16 : (g >> 1) * PL * 16 + (g & 1) * 8);
 #pragma unroll
-                for (int i = 0; i < NT; ++i, w.next(), cell += K::NPG * 256) {
-                    int im, y;
-                    const bool in = w.c < p.W && image_row(arow + w.r, im, y);
-                    if (i < NT - 1 || w.q < npa) {
+            for (int i = 0; i < NT; ++i, w.next(), cell += K::NPG * 256) {
+                bf16x4 r[FTW];
 #pragma unroll
-                        for (int j = 0; j < FTW; ++j) {
-                            bf16x4 o = {};
-                            if (in) o = relu_bf16x4(to_bf16x4(acc[i][j] + bv[j]));
-                            *(bf16x4*)(cell + j * 2 * PL * 16) = o;
-                        }
-                    }
-                }
+                for (int j = 0; j < FTW; ++j) r[j] = relu_bf16x4(to_bf16x4(acc[i][j] + bv[j]));
+                if (w.c < p.W && (i < NT - 1 || w.q < npa)) *(lane_bf16*)cell = join(r);
             }
-        });
-        __syncthreads();
-        // ---- x' = x + conv_b(U) + bias ----
-        const int npb = rb * P - 1;
-        const bool closing = blk + 1 == p.nblk;
-        by_tiles<TPW>(tiles_of(npb), [&](auto ntc) {
-            constexpr int NT = decltype(ntc)::value;
-            if constexpr (NT == 0) {
-                if (!closing) __syncthreads();
-            } else {
-                floatx4 acc[NT][FTW];
-                strip_conv<C, NT>(rs_lds + (brow - 1) * P * 16, PL, P, pg, npb - 1, p.wp[2 * blk + 1] + ft0 * K::KCH * 64, lane, acc);
-                const int ln = fresh_lane(lane), g = ln >> 4;
-                floatx4 bv[FTW];
+        }
+    });
+    __syncthreads();
+    // ---- x' = x + conv_b(U) + bias ----
+    const int npb = rb * P - 1;
+    by_tiles<TPW>(tiles_of(npb), [&](auto ntc) {
+        constexpr int NT = decltype(ntc)::value;
+        if constexpr (NT > 0) {
+            floatx4 acc[NT][FTW];
+            convolve(1, brow, npb, acc, ntc);
+            const int ln = fresh_lane(lane), g = ln >> 4;
+            const int f0 = fg * FTW * 16 + g * CPL;
+            floatx4 bv[FTW];
 #pragma unroll
-                for (int j = 0; j < FTW; ++j) bv[j] = *(const floatx4*)(p.bias[2 * blk + 1] + (ft0 + j) * 16 + g * 4);
-                if (!closing) __syncthreads();               // everybody has read U: the next R overwrites it
-                TileWalk w(pg * 16 + (ln & 15), K::NPG * 16, P);
-                char* cell = out_cell(g) + (brow * P + 1 + w.q) * 16;
-                const int f0 = ft0 * 16 + g * 4;
-                // residuals are requested XB tiles ahead of their use: one tile at a time, each waits out a trip to memory
-                constexpr int XB = C == 16 ? 4 : 2;
-                floatx4 r[XB][FTW];
-                int at[XB], yo[XB];                          // element offsets from image b; -1: no pixel
-                auto request = [&](int i) {
-                    int im, y;
-                    const bool in = w.c < p.W && image_row(brow + w.r, im, y) && (i < NT - 1 || w.q < npb);
-                    const int pl = (y * p.W + w.c) * C + f0;
-                    at[i % XB] = in ? im * (int)img + pl : -1;
-                    yo[i % XB] = p.ldy > 0 ? im * p.ldy + pl : at[i % XB];
-                    w.next();
-                    const int from = max(at[i % XB], 0);
+            for (int j = 0; j < FTW; ++j) bv[j] = *(const floatx4*)(p.bias[1] + f0 + j * 4);
+            TileWalk w(pg * 16 + (ln & 15), K::NPG * 16, P);
+            // residuals are requested XB tiles ahead of their use: one tile at a time, each waits out a trip to memory
+            constexpr int XB = C == 16 ? 4 : 2;
+            lane_bf16 rb16[XB];
+            floatx4 r32[XB][FTW];
+            int at[XB];                                      // element offset from the image; -1: no pixel
+            auto request = [&](int i) {
+                at[i % XB] = w.c < p.W && (i < NT - 1 || w.q < npb) ? ((y0 + w.r) * p.W + w.c) * C + f0 : -1;
+                w.next();
+                const int from = max(at[i % XB], 0);
+                if constexpr (FIRST) {
+                    rb16[i % XB] = *(const lane_bf16*)((const __bf16*)p.x_in + b * img + from);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < FTW; ++j) r32[i % XB][j] = *(const floatx4*)((const float*)p.x_in + b * img + from + j * 4);
+                }
+            };
+#pragma unroll
+            for (int i = 0; i < XB && i < NT; ++i) request(i);
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                const int u = i % XB;
+                if (at[u] >= 0) {
+                    bf16x4 t[FTW];
 #pragma unroll
                     for (int j = 0; j < FTW; ++j) {
-                        if (blk == 0) {
-                            if constexpr (X_BF16) r[i % XB][j] = to_floatx4(*(const bf16x4*)((const __bf16*)p.x_in + b * img + from + j * 16));
-                            else r[i % XB][j] = *(const floatx4*)((const float*)p.x_in + b * img + from + j * 16);
+                        floatx4 v = acc[i][j] + bv[j];
+                        if constexpr (FIRST) {
+                            const bf16x4 x = j == 0 ? __builtin_shufflevector(rb16[u], rb16[u], 0, 1, 2, 3)
+                                                    : __builtin_shufflevector(rb16[u], rb16[u], CPL - 4, CPL - 3, CPL - 2, CPL - 1);
+                            v += to_floatx4(x);
+                            *(floatx4*)(p.x_out + b * img + at[u] + j * 4) = v;
                         } else {
-                            r[i % XB][j] = *(const floatx4*)(p.x_out + b * img + from + j * 16);     // this lane's own x' of the first block
+                            v += r32[u][j];
+                            t[j] = to_bf16x4(v);
+                            if (p.y_relu) t[j] = relu_bf16x4(t[j]);
                         }
                     }
-                };
-#pragma unroll
-                for (int i = 0; i < XB && i < NT; ++i) request(i);
-#pragma unroll
-                for (int i = 0; i < NT; ++i, cell += K::NPG * 256) {
-                    const int u = i % XB;
-                    if (at[u] >= 0) {
-#pragma unroll
-                        for (int j = 0; j < FTW; ++j) {
-                            const floatx4 v = acc[i][j] + bv[j] + r[u][j];
-                            if (!closing) *(bf16x4*)(cell + j * 2 * PL * 16) = relu_bf16x4(to_bf16x4(v));
-                            if (!closing || !p.y) {
-                                *(floatx4*)(p.x_out + b * img + at[u] + j * 16) = v;
-                            } else {
-                                const bf16x4 t = to_bf16x4(v);
-                                *(bf16x4*)(p.y + (p.ldy > 0 ? (size_t)b * p.ldy : b * img) + yo[u] + j * 16) = p.y_relu ? relu_bf16x4(t) : t;
-                            }
-                        }
-                    }
-                    if (i + XB < NT) request(i + XB);
+                    if constexpr (!FIRST) *(lane_bf16*)(p.y + (p.ldy > 0 ? (size_t)b * p.ldy : b * img) + at[u]) = join(t);
                 }
+                if (i + XB < NT) request(i + XB);
             }
-        });
-        if (!closing) __syncthreads();
-    }
+        }
+    });
 }
 
 // ---- conv0 of a later section with its pooling --------------------------------
@@ -548,7 +512,7 @@ __global__ __launch_bounds__(RS_THREADS, 4) void strip_pool_kernel(StripPoolArgs
         const int cg = tid % K::NCG;
         const int t0 = max(m0, 0), t1 = min(m0 + MR, p.H), npx = (t1 - t0) * p.W;
         const char* src = (const char*)(p.in + ((size_t)b * p.H + t0) * p.W * C);
-        zero_borders<C>(rs_lds, PL, P, MR, m0 < 0, m0 + MR > p.H, 0, tid);
+        zero_borders<C>(rs_lds, PL, P, MR, m0 < 0, m0 + MR > p.H, tid);
         RowWalk rw(tid / K::NCG, CSTEP, p.W);
         int px = tid / K::NCG;
         uint32_t from = (uint32_t)(px * C + cg * 8) * 2;
@@ -578,17 +542,23 @@ __global__ __launch_bounds__(RS_THREADS, 4) void strip_pool_kernel(StripPoolArgs
                 __syncthreads();
             } else {
                 floatx4 acc[NT][FTW];
-                strip_conv<C, NT>(rs_lds, PL, P, pg, npix - 1, p.wp + (size_t)(fbase + ft0) * K::KCH * 64, lane, acc);
+                const bf16x8* const wl = p.wp + (size_t)(fbase + ft0) * K::KCH * 64;
+                StripWeights<C> w;
+                w.start(wl, fresh_lane(lane));
+                strip_conv<C, NT, strip_ring(NT)>(rs_lds, PL, P, pg, npix - 1, wl, lane, w, acc, [] {});
                 floatx4 bv[FTW];
 #pragma unroll
-                for (int j = 0; j < FTW; ++j) bv[j] = *(const floatx4*)(p.bias + (fbase + ft0 + j) * 16 + g * 4);
+                for (int j = 0; j < FTW; ++j) bv[j] = *(const floatx4*)(p.bias + (fbase + ft0) * 16 + g * 4 * FTW + j * 4);
                 __syncthreads();                             // everybody has read the input
-                char* cell = rs_lds + ((ft0 * 2 + (g >> 1)) * PL + P + 1 + pg * 16 + n) * 16 + (g & 1) * 8;
+                char* cell = rs_lds + (P + 1 + pg * 16 + n) * 16 + (FTW == 2 ? (fg * 4 + g) * PL * 16 : (g >> 1) * PL * 16 + (g & 1) * 8);
 #pragma unroll
                 for (int i = 0; i < NT; ++i, cell += K::NPG * 256) {
                     if (i == NT - 1 && (pg + K::NPG * i) * 16 + n >= npix) continue;
+                    bf16x4 r[FTW];
 #pragma unroll
-                    for (int j = 0; j < FTW; ++j) *(bf16x4*)(cell + j * 2 * PL * 16) = to_bf16x4(acc[i][j] + bv[j]);
+                    for (int j = 0; j < FTW; ++j) r[j] = to_bf16x4(acc[i][j] + bv[j]);
+                    if constexpr (FTW == 2) *(bf16x8*)cell = __builtin_shufflevector(r[0], r[1], 0, 1, 2, 3, 4, 5, 6, 7);
+                    else *(bf16x4*)cell = r[0];
                 }
             }
         });

@@ -54,7 +54,7 @@ def test_strips_fit_lds_and_the_registers(tmp_path):
 @pytest.mark.gpu
 @pytest.mark.parametrize("frame,sections,batch", [
     ((120, 192, 3), (16,), 300),          # four strips, inner ones with halos on both sides
-    ((107, 144, 4), (32,), 130),          # six, the last one shorter
+    ((119, 80, 4), (32,), 130),           # three
     ((59, 37, 3), (64,), 200),            # two of 15 rows
     ((9, 13, 1), (16,), 1100),            # stacks of four, feature rows padded to whole chunks, a last stack of fewer images
     ((9, 13, 16), (16, 32), 1025),
