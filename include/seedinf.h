@@ -332,11 +332,14 @@ void seed_infer_destroy(seed_infer_t* handle);
  *                        actor out of [0, n_actors), the same actor twice in
  *                        one batch, more than max_batch rows.
  *   seed_batcher_submit  closes the batch (rows in the order they were added):
- *                        host->device copies on the copy stream, then on the
+ *                        host->device copies of the frames on the copy stream
+ *                        (the first of a large batch start while rows are
+ *                        added, unless a row was reserved), and on the
  *                        compute stream: gather the rows' states by actor,
  *                        seed_infer_step_ext (done flags reset states; epsilon
- *                        optional), scatter the new states and actions back,
- *                        copy the actions to pinned host memory.  Returns at
+ *                        optional; the torso of leading rows may start before
+ *                        the last frames have arrived), scatter the new states
+ *                        and actions back and to pinned host memory.  Returns at
  *                        once with a ticket; the other staging set can be
  *                        filled while this batch is in flight (the call waits
  *                        only if that set's own earlier batch is unfinished).

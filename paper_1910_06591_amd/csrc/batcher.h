@@ -1,48 +1,68 @@
 // Host batching front-end: staging, state gather/scatter and the pipelined
 // round (copy stream + compute stream).  Included at the end of seedinf.hip.
 #pragma once
+#include <atomic>
 
 namespace seedinf {
 
-// rows of `table` picked by `idx` -> dense rows of `out` (one thread per element)
-__global__ __launch_bounds__(256) void gather_rows_kernel(const float* __restrict__ table, const int32_t* __restrict__ idx,
-                                                          float* __restrict__ out, int rows, int width)
+// What a batch's step reads besides the frames, one block per row: the actor's recurrent state and last action, and the
+// row's small inputs, which come straight from the pinned staging set (a few dozen bytes a row: copied one array at a time
+// they were five transfers).  Launched before the frames have arrived.
+struct BatchRows {
+    // pinned host memory
+    const int32_t* actor; const float* reward; const uint8_t* done; const float* uniforms; const float* epsilon; const float* explore;
+    // device
+    int32_t* d_actor; float* d_reward; uint8_t* d_done; float* d_uniforms; float* d_epsilon; float* d_explore;
+    int32_t* d_prev_action; float* d_h_in; float* d_c_in;
+    float* st_h; float* st_c; int32_t* st_action;            // per actor
+    int A, Hn;
+};
+__global__ __launch_bounds__(256) void batch_gather_kernel(BatchRows p)
 {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (long)rows * width) return;
-    const int r = (int)(i / width), c = (int)(i % width);
-    out[i] = table[(size_t)idx[r] * width + c];
+    const int r = blockIdx.x, tid = threadIdx.x;
+    const int actor = p.actor[r];
+    for (int i = tid; i < p.Hn; i += 256) {
+        p.d_h_in[(size_t)r * p.Hn + i] = p.st_h[(size_t)actor * p.Hn + i];
+        p.d_c_in[(size_t)r * p.Hn + i] = p.st_c[(size_t)actor * p.Hn + i];
+    }
+    if (p.uniforms)
+        for (int i = tid; i < p.A; i += 256) p.d_uniforms[(size_t)r * p.A + i] = p.uniforms[(size_t)r * p.A + i];
+    if (tid == 0) {
+        p.d_actor[r] = actor;
+        p.d_prev_action[r] = p.st_action[actor];
+        p.d_reward[r] = p.reward[r];
+        p.d_done[r] = p.done[r];
+        if (p.epsilon) p.d_epsilon[r] = p.epsilon[r];
+    }
+    if (p.epsilon && tid < 2) p.d_explore[2 * r + tid] = p.explore[2 * r + tid];
 }
 
-__global__ __launch_bounds__(256) void scatter_rows_kernel(const float* __restrict__ in, const int32_t* __restrict__ idx,
-                                                           float* __restrict__ table, int rows, int width)
+// The step's new states and actions back to their actors, and the actions to pinned host memory.
+__global__ __launch_bounds__(256) void batch_scatter_kernel(BatchRows p, const float* __restrict__ h_out, const float* __restrict__ c_out,
+                                                            const int32_t* __restrict__ actions, int32_t* __restrict__ actions_host)
 {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (long)rows * width) return;
-    const int r = (int)(i / width), c = (int)(i % width);
-    table[(size_t)idx[r] * width + c] = in[i];
-}
-
-__global__ __launch_bounds__(256) void gather_i32_kernel(const int32_t* __restrict__ table, const int32_t* __restrict__ idx,
-                                                         int32_t* __restrict__ out, int rows)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < rows) out[i] = table[idx[i]];
-}
-
-__global__ __launch_bounds__(256) void scatter_i32_kernel(const int32_t* __restrict__ in, const int32_t* __restrict__ idx,
-                                                          int32_t* __restrict__ table, int rows)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < rows) table[idx[i]] = in[i];
+    const int r = blockIdx.x, tid = threadIdx.x;
+    const int actor = p.d_actor[r];
+    for (int i = tid; i < p.Hn; i += 256) {
+        p.st_h[(size_t)actor * p.Hn + i] = h_out[(size_t)r * p.Hn + i];
+        p.st_c[(size_t)actor * p.Hn + i] = c_out[(size_t)r * p.Hn + i];
+    }
+    if (tid == 0) {
+        const int a = actions[r];
+        p.st_action[actor] = a;
+        actions_host[r] = a;
+    }
 }
 
 }  // namespace seedinf
+
+constexpr int BATCHER_CHUNKS = 8;
 
 struct seed_batcher {
     seed_infer* h = nullptr;
     int n_actors = 0, max_rows = 0, A = 0, Hn = 0;
     size_t frame = 0;
+    int chunk = 0;                      // rows whose torso starts together while later frames travel
     hipStream_t copy_s = nullptr, comp_s = nullptr;
     // per-actor device state
     float* st_h = nullptr; float* st_c = nullptr; int32_t* st_action = nullptr;
@@ -56,8 +76,12 @@ struct seed_batcher {
         int32_t* d_prev_action = nullptr; int32_t* d_actions = nullptr;
         float* d_h_in = nullptr; float* d_c_in = nullptr; float* d_h_out = nullptr; float* d_c_out = nullptr;
         float* d_logits = nullptr; float* d_value = nullptr;
-        hipEvent_t copied = nullptr, finished = nullptr;
+        hipEvent_t ready[BATCHER_CHUNKS] = {};   // the frames of the first k + 1 chunks have arrived; the last in use: all
+        hipEvent_t finished = nullptr;
+        int chunks = 0;                 // of `ready` recorded
         int rows = 0;                   // rows added to the batch being filled
+        int sent = 0;                   // leading rows whose frames are on their way to the device
+        bool open = false;              // a row was reserved: its frame may be written until submit
         int result_rows = 0;            // rows of the submitted batch `ticket`
         int ticket = -1;
         bool in_flight = false;
@@ -88,7 +112,7 @@ static void batcher_free(seed_batcher* b)
         void* dev[] = {s.d_obs, s.d_reward, s.d_done, s.d_actor, s.d_uniforms, s.d_epsilon, s.d_explore, s.d_prev_action,
                        s.d_actions, s.d_h_in, s.d_c_in, s.d_h_out, s.d_c_out, s.d_logits, s.d_value};
         for (void* p : dev) if (p) (void)hipFree(p);
-        if (s.copied) (void)hipEventDestroy(s.copied);
+        for (hipEvent_t e : s.ready) if (e) (void)hipEventDestroy(e);
         if (s.finished) (void)hipEventDestroy(s.finished);
     }
     if (b->st_h) (void)hipFree(b->st_h);
@@ -138,7 +162,7 @@ static seed_status_t batcher_alloc(seed_batcher* b)
             B_TRY(b, hipMalloc(&s.d_h_out, R * Hn * sizeof(float)));
             B_TRY(b, hipMalloc(&s.d_c_out, R * Hn * sizeof(float)));
         }
-        B_TRY(b, hipEventCreateWithFlags(&s.copied, hipEventDisableTiming));
+        for (hipEvent_t& e : s.ready) B_TRY(b, hipEventCreateWithFlags(&e, hipEventDisableTiming));
         B_TRY(b, hipEventCreateWithFlags(&s.finished, hipEventDisableTiming));
     }
     B_TRY(b, hipDeviceSynchronize());
@@ -156,6 +180,10 @@ extern "C" seed_status_t seed_batcher_create(seed_infer_t* h, int32_t n_actors, 
     b->h = h; b->n_actors = n_actors; b->max_rows = a.max_batch; b->A = a.num_actions; b->Hn = a.lstm_units;
     b->frame = (size_t)a.obs_h * a.obs_w * a.obs_c;
     b->seen.assign((size_t)n_actors, -1);
+    // whole rounds of the torso over the compute units, at most BATCHER_CHUNKS of them
+    int n_cu = 0;
+    if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || n_cu <= 0) n_cu = 256;
+    b->chunk = ((a.max_batch + BATCHER_CHUNKS - 1) / BATCHER_CHUNKS + n_cu - 1) / n_cu * n_cu;
     seed_status_t st = batcher_alloc(b);
     if (st != SEED_OK) { g_create_err = b->err; batcher_free(b); return st; }
     *out = b;
@@ -166,19 +194,36 @@ extern "C" void seed_batcher_destroy(seed_batcher_t* b) { batcher_free(b); }
 extern "C" const char* seed_batcher_last_error(const seed_batcher_t* b) { return b ? b->err.c_str() : g_create_err.c_str(); }
 extern "C" void* seed_batcher_stream(seed_batcher_t* b) { return b ? (void*)b->comp_s : nullptr; }
 
-extern "C" seed_status_t seed_batcher_reserve(seed_batcher_t* b, int32_t actor, float prev_reward, uint8_t done,
-                                              uint8_t** obs_slot)
+// Frames travel while later rows are still being added, in transfers of at least this many bytes (each costs about 9 us more;
+// a round of 512 DMLab frames is 10.6 MB, 193 us of PCIe in one transfer).  A whole round, frames in host memory to
+// actions in host memory: 433 -> 359 us; the copy to pinned memory, 260 us here where neither side of it is in cache, is what is left
+// to overlap with, and stores past the caches or items handed out to whichever thread is awake made it no shorter.
+constexpr size_t BATCHER_SEND_BYTES = (size_t)1 << 21;
+
+// Starts the transfer of the filled rows [sent, rows) if they are worth one.
+static seed_status_t batcher_send(seed_batcher* b, seed_batcher::Set& s, int rows, size_t at_least)
 {
-    if (!b) return SEED_ERR_INVALID_ARG;
+    const size_t bytes = (size_t)(rows - s.sent) * b->frame;
+    if (bytes == 0 || bytes < at_least) return SEED_OK;
+    const size_t from = (size_t)s.sent * b->frame;
+    B_TRY(b, hipMemcpyAsync(s.d_obs + from, s.obs + from, bytes, hipMemcpyHostToDevice, b->copy_s));
+    s.sent = rows;
+    // (the last event is for all rows, at submit)
+    while (s.chunks < BATCHER_CHUNKS - 1 && s.sent >= (s.chunks + 1) * b->chunk) B_TRY(b, hipEventRecord(s.ready[s.chunks++], b->copy_s));
+    return SEED_OK;
+}
+
+static seed_status_t batcher_row(seed_batcher* b, int32_t actor, float prev_reward, uint8_t done, uint8_t** obs_slot)
+{
     auto fail = [&](seed_status_t st, const char* m) { b->err = m; return st; };
-    if (!obs_slot) return fail(SEED_ERR_INVALID_ARG, "obs_slot is NULL");
     if (actor < 0 || actor >= b->n_actors) return fail(SEED_ERR_INVALID_ARG, "actor out of range");
     seed_batcher::Set& s = b->set[b->fill];
     if (s.in_flight) {
         // this staging set's earlier batch must have left the host buffers before they are overwritten
         B_TRY(b, hipEventSynchronize(s.finished));
         s.in_flight = false;
-        s.rows = 0;
+        s.rows = s.sent = s.chunks = 0;
+        s.open = false;
         s.ticket = -1;                  // its results were never collected and are about to be overwritten
     }
     if (s.rows >= b->max_rows) return fail(SEED_ERR_BATCH_TOO_LARGE, "the batch already holds max_batch rows");
@@ -192,15 +237,27 @@ extern "C" seed_status_t seed_batcher_reserve(seed_batcher_t* b, int32_t actor, 
     return SEED_OK;
 }
 
+extern "C" seed_status_t seed_batcher_reserve(seed_batcher_t* b, int32_t actor, float prev_reward, uint8_t done,
+                                              uint8_t** obs_slot)
+{
+    if (!b) return SEED_ERR_INVALID_ARG;
+    if (!obs_slot) { b->err = "obs_slot is NULL"; return SEED_ERR_INVALID_ARG; }
+    const seed_status_t st = batcher_row(b, actor, prev_reward, done, obs_slot);
+    if (st == SEED_OK) b->set[b->fill].open = true;
+    return st;
+}
+
 extern "C" seed_status_t seed_batcher_add(seed_batcher_t* b, int32_t actor, const uint8_t* obs_host, float prev_reward,
                                           uint8_t done)
 {
     if (!b) return SEED_ERR_INVALID_ARG;
     if (!obs_host) { b->err = "obs_host is NULL"; return SEED_ERR_INVALID_ARG; }
     uint8_t* slot = nullptr;
-    seed_status_t st = seed_batcher_reserve(b, actor, prev_reward, done, &slot);
-    if (st == SEED_OK) memcpy(slot, obs_host, b->frame);
-    return st;
+    seed_status_t st = batcher_row(b, actor, prev_reward, done, &slot);
+    if (st != SEED_OK) return st;
+    memcpy(slot, obs_host, b->frame);
+    seed_batcher::Set& s = b->set[b->fill];
+    return s.open ? SEED_OK : batcher_send(b, s, s.rows, BATCHER_SEND_BYTES);
 }
 
 extern "C" seed_status_t seed_batcher_add_many(seed_batcher_t* b, int32_t n, const int32_t* actors, const uint8_t* obs_host,
@@ -208,25 +265,39 @@ extern "C" seed_status_t seed_batcher_add_many(seed_batcher_t* b, int32_t n, con
 {
     if (!b) return SEED_ERR_INVALID_ARG;
     if (n < 0 || !actors || !obs_host || !prev_rewards || !dones) { b->err = "n is negative or a pointer is NULL"; return SEED_ERR_INVALID_ARG; }
-    std::vector<uint8_t*> slot((size_t)n);
     int32_t ok = 0;
+    uint8_t* slot = nullptr;
     seed_status_t st = SEED_OK;
     for (; ok < n; ++ok) {
-        st = seed_batcher_reserve(b, actors[ok], prev_rewards[ok], dones[ok], &slot[ok]);
+        st = batcher_row(b, actors[ok], prev_rewards[ok], dones[ok], &slot);
         if (st != SEED_OK) break;
     }
-    // the frame copies are the expensive part: large batches go over the handle's persistent host threads, in
-    // pieces of about a megabyte
-    const int32_t per = (int32_t)std::max<size_t>(1, ((size_t)1 << 20) / b->frame);
+    if (ok == 0) return st;
+    // The frame copies are the expensive part: large batches go over the handle's persistent host threads, in pieces of
+    // about a quarter of a megabyte, and the calling thread sends on whatever is complete from the front after each
+    // piece of its own.
+    seed_batcher::Set& s = b->set[b->fill];
+    const int32_t first = s.rows - ok;
+    const int32_t per = (int32_t)std::max<size_t>(1, ((size_t)1 << 18) / b->frame);
     const int pieces = (ok + per - 1) / per;
-    auto copy = [&](int t) {
-        const int32_t i1 = std::min(ok, (t + 1) * per);
-        for (int32_t i = t * per; i < i1; ++i) memcpy(slot[i], obs_host + (size_t)i * b->frame, b->frame);
-    };
     HostPool* pool = pieces > 1 ? host_pool(b->h) : nullptr;
+    std::vector<std::atomic<uint8_t>> copied((size_t)pieces);
+    for (auto& c : copied) c.store(0, std::memory_order_relaxed);
+    int front = 0;                                           // pieces complete from the front
+    seed_status_t sent = SEED_OK;
+    const std::thread::id caller = std::this_thread::get_id();
+    auto copy = [&](int t) {
+        const int32_t i0 = t * per, i1 = std::min(ok, i0 + per);
+        memcpy(s.obs + (size_t)(first + i0) * b->frame, obs_host + (size_t)i0 * b->frame, (size_t)(i1 - i0) * b->frame);
+        copied[t].store(1, std::memory_order_release);
+        if (s.open || sent != SEED_OK || std::this_thread::get_id() != caller) return;
+        while (front < pieces && copied[front].load(std::memory_order_acquire)) ++front;
+        sent = batcher_send(b, s, first + std::min(ok, front * per), BATCHER_SEND_BYTES);
+    };
     if (pool) pool->run(pieces, copy);
     else for (int t = 0; t < pieces; ++t) copy(t);
-    return st;
+    if (!s.open && sent == SEED_OK) sent = batcher_send(b, s, s.rows, BATCHER_SEND_BYTES);
+    return st != SEED_OK ? st : sent;
 }
 
 extern "C" seed_status_t seed_batcher_submit(seed_batcher_t* b, const float* uniforms_host, const float* epsilon_host,
@@ -247,44 +318,34 @@ extern "C" seed_status_t seed_batcher_submit(seed_batcher_t* b, const float* uni
         memcpy(s.epsilon, epsilon_host, R * sizeof(float));
         memcpy(s.explore, explore_host, R * 2 * sizeof(float));
     }
-    // host -> device on the copy stream (overlaps the previous batch's compute)
+    // the frames not yet sent, on the copy stream (overlaps the previous batch's compute); beside them, on the compute
+    // stream, the rows' states and small inputs; the step waits for both
     hipStream_t cs = b->copy_s, ks = b->comp_s;
-    B_TRY(b, hipMemcpyAsync(s.d_obs, s.obs, R * b->frame, hipMemcpyHostToDevice, cs));
-    B_TRY(b, hipMemcpyAsync(s.d_reward, s.reward, R * sizeof(float), hipMemcpyHostToDevice, cs));
-    B_TRY(b, hipMemcpyAsync(s.d_done, s.done, R, hipMemcpyHostToDevice, cs));
-    B_TRY(b, hipMemcpyAsync(s.d_actor, s.actor, R * sizeof(int32_t), hipMemcpyHostToDevice, cs));
-    if (uniforms_host) B_TRY(b, hipMemcpyAsync(s.d_uniforms, s.uniforms, R * A * sizeof(float), hipMemcpyHostToDevice, cs));
-    if (epsilon_host) {
-        B_TRY(b, hipMemcpyAsync(s.d_epsilon, s.epsilon, R * sizeof(float), hipMemcpyHostToDevice, cs));
-        B_TRY(b, hipMemcpyAsync(s.d_explore, s.explore, R * 2 * sizeof(float), hipMemcpyHostToDevice, cs));
-    }
-    B_TRY(b, hipEventRecord(s.copied, cs));
-    B_TRY(b, hipStreamWaitEvent(ks, s.copied, 0));
-    // compute stream: gather state, step, scatter state, actions back
     const bool rec = Hn > 0;
-    if (rec) {
-        const unsigned nb = (unsigned)((R * Hn + 255) / 256);
-        hipLaunchKernelGGL(gather_rows_kernel, dim3(nb), dim3(256), 0, ks, b->st_h, s.d_actor, s.d_h_in, R, (int)Hn);
-        hipLaunchKernelGGL(gather_rows_kernel, dim3(nb), dim3(256), 0, ks, b->st_c, s.d_actor, s.d_c_in, R, (int)Hn);
-        hipLaunchKernelGGL(gather_i32_kernel, dim3((R + 255) / 256), dim3(256), 0, ks, b->st_action, s.d_actor, s.d_prev_action, R);
-    }
+    if (seed_status_t st = batcher_send(b, s, R, 1); st != SEED_OK) return st;
+    // one more event for the rows behind the last whole chunk, if there are any
+    int events = s.chunks;
+    if (R > events * b->chunk) B_TRY(b, hipEventRecord(s.ready[events++], cs));
+    const FrameArrival arrival{b->chunk, events, s.ready};
+    BatchRows br{};
+    br.actor = s.actor; br.reward = s.reward; br.done = s.done;
+    br.uniforms = uniforms_host ? s.uniforms : nullptr;
+    br.epsilon = epsilon_host ? s.epsilon : nullptr; br.explore = s.explore;
+    br.d_actor = s.d_actor; br.d_reward = s.d_reward; br.d_done = s.d_done; br.d_uniforms = s.d_uniforms; br.d_epsilon = s.d_epsilon; br.d_explore = s.d_explore;
+    br.d_prev_action = s.d_prev_action; br.d_h_in = s.d_h_in; br.d_c_in = s.d_c_in;
+    br.st_h = b->st_h; br.st_c = b->st_c; br.st_action = b->st_action; br.A = (int)A; br.Hn = (int)Hn;
+    hipLaunchKernelGGL(batch_gather_kernel, dim3(R), dim3(256), 0, ks, br);
     seed_step_ext_t ext{};
     ext.struct_size = sizeof(ext);
     ext.done = rec ? s.d_done : nullptr;
     ext.epsilon = epsilon_host ? s.d_epsilon : nullptr;
     ext.explore_uniforms = epsilon_host ? s.d_explore : nullptr;
-    seed_status_t st = seed_infer_step_ext(b->h, R, s.d_obs, rec ? s.d_prev_action : nullptr, rec ? s.d_reward : nullptr,
+    seed_status_t st = step_impl(b->h, R, s.d_obs, rec ? s.d_prev_action : nullptr, rec ? s.d_reward : nullptr,
                                            rec ? s.d_h_in : nullptr, rec ? s.d_c_in : nullptr,
                                            uniforms_host ? s.d_uniforms : nullptr, &ext, s.d_actions, s.d_logits, s.d_value,
-                                           rec ? s.d_h_out : nullptr, rec ? s.d_c_out : nullptr, nullptr, ks);
+                                           rec ? s.d_h_out : nullptr, rec ? s.d_c_out : nullptr, nullptr, ks, false, &arrival);
     if (st != SEED_OK) { b->err = b->h->err; return st; }
-    if (rec) {
-        const unsigned nb = (unsigned)((R * Hn + 255) / 256);
-        hipLaunchKernelGGL(scatter_rows_kernel, dim3(nb), dim3(256), 0, ks, s.d_h_out, s.d_actor, b->st_h, R, (int)Hn);
-        hipLaunchKernelGGL(scatter_rows_kernel, dim3(nb), dim3(256), 0, ks, s.d_c_out, s.d_actor, b->st_c, R, (int)Hn);
-    }
-    hipLaunchKernelGGL(scatter_i32_kernel, dim3((R + 255) / 256), dim3(256), 0, ks, s.d_actions, s.d_actor, b->st_action, R);
-    B_TRY(b, hipMemcpyAsync(s.actions, s.d_actions, R * sizeof(int32_t), hipMemcpyDeviceToHost, ks));
+    hipLaunchKernelGGL(batch_scatter_kernel, dim3(R), dim3(256), 0, ks, br, s.d_h_out, s.d_c_out, s.d_actions, s.actions);
     B_TRY(b, hipEventRecord(s.finished, ks));
     B_TRY(b, hipGetLastError());
     s.ticket = b->next_ticket;
@@ -294,7 +355,7 @@ extern "C" seed_status_t seed_batcher_submit(seed_batcher_t* b, const float* uni
     b->fill ^= 1;
     // the set that is filled next starts empty; if its own batch is still in flight the first add waits for it
     seed_batcher::Set& n = b->set[b->fill];
-    if (!n.in_flight) n.rows = 0;
+    if (!n.in_flight) { n.rows = n.sent = n.chunks = 0; n.open = false; }
     return SEED_OK;
 }
 
@@ -311,7 +372,8 @@ extern "C" seed_status_t seed_batcher_wait(seed_batcher_t* b, int32_t ticket, in
         *n_rows = s.result_rows;
         if (s.in_flight) {              // finished: the set may be refilled
             s.in_flight = false;
-            s.rows = 0;
+            s.rows = s.sent = s.chunks = 0;
+            s.open = false;
         }
         return SEED_OK;
     }

@@ -1103,14 +1103,12 @@ inline void launch_strip_pool(hipStream_t st, const LwLayerDev& d, const bf16x8*
     });
 }
 
-// Torso and linear layer over B rows: leaves the rectified linear-layer output of row r in row r of
-// fc_bf16 / fc_f32.
-inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w, hipStream_t st, int B, const uint8_t* obs,
-                                   hipEvent_t ev0, hipEvent_t ev1, std::string& err)
+// Torso over B rows of frames: the features of the first in row `row0` of the feature matrix.
+inline void bf16_torso(Bf16State* s, const Plan& p, const float* d_w, hipStream_t st, int row0, int B, const uint8_t* obs)
 {
     const seed_arch_t& a = p.arch;
     const Bf16WeightSet& W = s->ws[s->active];
-    if (ev0) (void)hipEventRecord(ev0, st);
+    __bf16* const feat = s->feat + (size_t)row0 * s->ldf;
     if (a.torso == SEED_TORSO_RESNET && s->torso_kind == TORSO_NONE) {
         // layer by layer: conv0 -> pool -> (conv_a, conv_b) x 2 per section, activations in HBM
         const void* in = obs;
@@ -1138,7 +1136,7 @@ inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w
                     if (!launch_first_rows(st, s->lw[li], W.wp_conv, d_w, sec, pl.first_rows, B, s->n_cu, obs, s->lw_u))
                         launch_first_pool(st, s->lw[li], W.wp_conv, d_w, sec, pl.first, B, obs, nullptr, s->lw_u);
                 } else launch_strip_pool(st, s->lw[li], W.wp_conv, d_w, sec, pl.strip_pool, B, (const __bf16*)in, s->lw_u);
-                __bf16* const y = last_sec ? s->feat : s->lw_r;
+                __bf16* const y = last_sec ? feat : s->lw_r;
                 const int y_relu = last_sec ? 1 : 0, ldy = last_sec ? s->ldf : 0;
                 if (pl.pair.TH) launch_pair(st, &s->lw[li + 1], W.wp_conv, d_w, sec, pl.pair, B, s->n_cu, s->lw_u, y, y_relu, ldy);
                 else launch_strip_blocks(st, &s->lw[li + 1], W.wp_conv, d_w, sec, pl.strip_block, B, s->lw_u, s->lw_x, y, y_relu, ldy);
@@ -1167,7 +1165,7 @@ inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w
             for (int blk = 0; blk < 2; ++blk) {
                 const bool closing = last_sec && blk == 1;          // the torso's last layer writes the rectified features
                 const bool to_next = !last_sec && blk == 1;         // the next section's conv0 takes x un-rectified
-                __bf16* y = closing ? s->feat : s->lw_r;
+                __bf16* y = closing ? feat : s->lw_r;
                 const int y_relu = to_next ? 0 : 1, ldy = closing ? s->ldf : 0;
                 // (two launches over larger tiles where the one-launch block is bound by operand delivery; conv_b adds
                 // and writes x in place: it reads no pixel of x but its own)
@@ -1191,7 +1189,7 @@ inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w
         }
     } else if (a.torso == SEED_TORSO_RESNET) {
         TorsoArgs t{};
-        t.obs = obs; t.feat = s->feat; t.ldf = s->ldf; t.B = B;
+        t.obs = obs; t.feat = feat; t.ldf = s->ldf; t.B = B;
         for (int i = 0; i < 4; ++i) t.sec[i] = W.sec[i];
         const int grid = B < s->n_cu ? B : s->n_cu;
         constexpr int LDS_DM = Net3<DmS1, DmS2, DmS3>::LDS_BYTES;
@@ -1203,7 +1201,7 @@ inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w
             hipLaunchKernelGGL((resnet4_bf16_kernel<FbS1, DmS2, DmS3, FbS4>), dim3(grid), dim3(RN_THREADS), LDS_FB, st, t);
     } else if (s->stack_fused) {
         R2d2TorsoArgs t{};
-        t.obs = obs; t.feat = s->feat; t.ldf = s->ldf; t.B = B;
+        t.obs = obs; t.feat = feat; t.ldf = s->ldf; t.B = B;
         t.w1 = W.wp_conv + s->stack[0].wp_off / 8; t.w2 = W.wp_conv + s->stack[1].wp_off / 8; t.w3 = W.wp_conv + s->stack[2].wp_off / 8;
         t.b1 = d_w + p.convs[0].b_off; t.b2 = d_w + p.convs[1].b_off; t.b3 = d_w + p.convs[2].b_off;
         const dim3 grid(B < s->n_cu ? B : s->n_cu);
@@ -1216,7 +1214,7 @@ inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w
             const bool last = l + 1 == p.convs.size();
             ConvStackArgs ca{};
             ca.x = x; ca.wp = W.wp_conv + s->stack[l].wp_off / 8; ca.bias = d_w + c.b_off;
-            ca.koff = s->koff + s->stack[l].koff_off; ca.y = last ? s->feat : s->act[l & 1];
+            ca.koff = s->koff + s->stack[l].koff_off; ca.y = last ? feat : s->act[l & 1];
             ca.B = B; ca.H = c.H; ca.W = c.W; ca.Cin = c.Cin; ca.OH = c.OH; ca.OW = c.OW; ca.Cout = c.Cout;
             ca.stride = c.stride; ca.kchunks = s->stack[l].kchunks; ca.scale = l == 0 ? 1.0f / 255.0f : 1.0f;
             const int nft = c.Cout / 16;
@@ -1229,8 +1227,14 @@ inline seed_status_t bf16_torso_fc(Bf16State* s, const Plan& p, const float* d_w
             x = ca.y;
         }
     }
-    if (ev1) (void)hipEventRecord(ev1, st);
-    // linear layer + ReLU -> bf16 (for the core GEMM) and fp32 (for heads / taps)
+}
+
+// Linear layer + ReLU over B rows of features -> bf16 (for the core GEMM) and fp32 (for heads / taps): row r's output in
+// row r of fc_bf16 / fc_f32.
+inline seed_status_t bf16_fc(Bf16State* s, const Plan& p, hipStream_t st, int B, std::string& err)
+{
+    const seed_arch_t& a = p.arch;
+    const Bf16WeightSet& W = s->ws[s->active];
     {
         GemmArgs g{};
         g.x1 = s->feat; g.ld1 = s->ldf; g.kc1 = s->kc_fc; g.k2 = 0;
@@ -1278,17 +1282,6 @@ inline seed_status_t bf16_core(Bf16State* s, const Plan& p, const float* d_w, hi
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { err = std::string("kernel launch: ") + hipGetErrorString(e); return SEED_ERR_DEVICE; }
     return SEED_OK;
-}
-
-// One step: torso, linear layer, recurrent core and dueling hidden layers.
-inline seed_status_t bf16_step(Bf16State* s, const Plan& p, const float* d_w, hipStream_t st, int B, const uint8_t* obs,
-                               const int32_t* prev_action, const float* prev_reward, const float* h_in,
-                               const float* c_in, const uint8_t* done, float* h_out, float* c_out, float* d_hid,
-                               const float** core, int* ld_core, hipEvent_t ev0, hipEvent_t ev1, std::string& err)
-{
-    const seed_status_t st0 = bf16_torso_fc(s, p, d_w, st, B, obs, ev0, ev1, err);
-    if (st0 != SEED_OK) return st0;
-    return bf16_core(s, p, d_w, st, 0, B, prev_action, prev_reward, h_in, c_in, done, h_out, c_out, d_hid, core, ld_core, err);
 }
 
 inline seed_status_t bf16_read_intermediate(Bf16State* s, const Plan& p, int which, int B, float* dst, hipStream_t st,

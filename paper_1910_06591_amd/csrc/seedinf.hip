@@ -338,10 +338,24 @@ static void launch_heads(hipStream_t s, const HeadsArgs& ha)
     else launch_heads_p<64>(s, ha);
 }
 
+// Frames that are still on their way to the device: rows k * chunk .. are there when ready[k] has passed, the rest with ready[n - 1].
+struct FrameArrival { int chunk, n; const hipEvent_t* ready; };
+
 // Torso and linear layer over B rows (rows of the handle's linear-layer buffers).
-static seed_status_t run_torso_fc(seed_infer* h, hipStream_t s, int B, const uint8_t* obs)
+static seed_status_t run_torso_fc(seed_infer* h, hipStream_t s, int B, const uint8_t* obs, const FrameArrival* arrival = nullptr)
 {
     const Plan& p = h->plan;
+    if (arrival && p.arch.precision == SEED_PRECISION_BF16 && h->ev.empty()) {
+        // the torso of the rows that are there runs beside the transfer of the others
+        const size_t frame = (size_t)p.arch.obs_h * p.arch.obs_w * p.arch.obs_c;
+        for (int k = 0; k < arrival->n; ++k) {
+            const int r0 = k * arrival->chunk, r1 = k + 1 < arrival->n ? r0 + arrival->chunk : B;
+            HIP_TRY(h, hipStreamWaitEvent(s, arrival->ready[k], 0));
+            if (r1 > r0) bf16_torso(h->bf, p, h->d_w, s, r0, r1 - r0, obs + r0 * frame);
+        }
+        return bf16_fc(h->bf, p, s, B, h->err);
+    }
+    if (arrival) HIP_TRY(h, hipStreamWaitEvent(s, arrival->ready[arrival->n - 1], 0));
     const bool prof = !h->ev.empty() && h->ev_used < SEED_PROFILE_SLOTS;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (prof) { ev0 = h->ev[2 * h->ev_used]; ev1 = h->ev[2 * h->ev_used + 1]; ++h->ev_used; }
@@ -352,7 +366,10 @@ static seed_status_t run_torso_fc(seed_infer* h, hipStream_t s, int B, const uin
         HIP_TRY(h, hipGetLastError());
         return SEED_OK;
     }
-    return bf16_torso_fc(h->bf, p, h->d_w, s, B, obs, ev0, ev1, h->err);
+    if (ev0) (void)hipEventRecord(ev0, s);
+    bf16_torso(h->bf, p, h->d_w, s, 0, B, obs);
+    if (ev1) (void)hipEventRecord(ev1, s);
+    return bf16_fc(h->bf, p, s, B, h->err);
 }
 
 // Recurrent core, heads and action selection for the B rows that start at row `row0` of the linear layer's
@@ -513,7 +530,8 @@ static seed_status_t step_impl(seed_infer_t* h, int32_t B, const uint8_t* obs,
                                const float* h_in, const float* c_in, const float* uniforms,
                                const seed_step_ext_t* ext,
                                int32_t* action_out, float* logits_out, float* value_out,
-                               float* h_out, float* c_out, float* probs_out, void* hip_stream, bool static_ws)
+                               float* h_out, float* c_out, float* probs_out, void* hip_stream, bool static_ws,
+                               const FrameArrival* arrival = nullptr)
 {
     if (!h) return SEED_ERR_INVALID_ARG;
     const Plan& p = h->plan;
@@ -553,7 +571,7 @@ static seed_status_t step_impl(seed_infer_t* h, int32_t B, const uint8_t* obs,
 
     hipStream_t s = (hipStream_t)hip_stream;
     if (!static_ws) {
-        seed_status_t st = run_torso_fc(h, s, B, obs);
+        seed_status_t st = run_torso_fc(h, s, B, obs, arrival);
         if (st != SEED_OK) return st;
         return run_core_heads(h, s, 0, B, prev_action, prev_reward, h_in, c_in, done, h_out, c_out, uniforms, epsilon, explore_u,
                               action_out, logits_out, value_out, probs_out);
