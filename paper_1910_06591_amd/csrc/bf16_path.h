@@ -686,6 +686,17 @@ inline void launch_gemm(hipStream_t st, const GemmArgs& g, int tile_groups, int 
         // small batches: one tile group per block with K split over its four wavefronts puts four times as many
         // compute units to work as the group-per-wavefront kernel below (measured: 4.9 vs 8.1 us at 64 rows, 6.2 vs
         // 8.2 at 512, slower at 1024)
+        if constexpr (EPI == EPI_LSTM) {
+            // where blocks of 16 rows would be two to a compute unit, which then pulls a gate group's weights twice, and
+            // blocks of 32 rows one: those, with K over eight wavefronts (Atari agent's step at 144 rows 40.9 -> 38.6 us,
+            // 200 41.6 -> 39.9, 256 40.1 -> 38.8; 256 units at 272 to 512 rows within 0.5 %)
+            const long b32 = (long)((g.rows + 31) / 32) * tile_groups;
+            if ((long)((g.rows + 15) / 16) * tile_groups > n_cu && b32 <= n_cu) {
+                hipLaunchKernelGGL((gemm_bf16_splitk_kernel<2, EPI, 8>), dim3((g.rows + 31) / 32, tile_groups), dim3(512),
+                                   4 * 2 * 4 * 64 * sizeof(floatx4), st, g);
+                return;
+            }
+        }
         if ((long)((g.rows + 15) / 16) * tile_groups <= want) {
             hipLaunchKernelGGL((gemm_bf16_splitk_kernel<1, EPI, 4>), dim3((g.rows + 15) / 16, tile_groups), dim3(256),
                                4 * 1 * 4 * 64 * sizeof(floatx4), st, g);
