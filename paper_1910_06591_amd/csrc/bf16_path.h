@@ -552,16 +552,19 @@ inline seed_status_t bf16_create(const Plan& p, const float* d_w, Bf16State** ou
     BF_TRY(gemm_lds_set_attributes<EPI_RELU>());
     BF_TRY(gemm_lds_set_attributes<EPI_LSTM>());
 
-    // the LDS-tiled layer-by-layer convolution and the fused torso kernels may use more than 64 KiB of LDS
-    BF_TRY(hipFuncSetAttribute((const void*)conv3x3_lds_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LT_LDS_MAX));
-    BF_TRY(hipFuncSetAttribute((const void*)conv3x3_lds_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LT_LDS_MAX));
-    BF_TRY(hipFuncSetAttribute((const void*)conv3x3_lds_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LT_LDS_MAX));
-    {
-        // the per-section kernels of the layer-by-layer ResNet path may ask for more than 64 KiB as well
+    // more than 64 KiB of LDS has to be asked for, by every kernel that this network may launch
+    if (a.torso == SEED_TORSO_RESNET && s->torso_kind == TORSO_NONE) {
         hipError_t e = hipSuccess;
         auto set = [&](const void* f, size_t bytes) {
             if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
         };
+        set((const void*)conv3x3_lds_kernel<1>, LT_LDS_MAX);
+        set((const void*)conv3x3_lds_kernel<2>, LT_LDS_MAX);
+        set((const void*)conv3x3_lds_kernel<4>, LT_LDS_MAX);
+        set((const void*)resblock_fused_kernel<16>, RB_LDS_MAX);
+        set((const void*)resblock_fused_kernel<32>, RB_LDS_MAX);
+        set((const void*)resblock_fused_kernel<64>, RB_LDS_MAX);
+        set((const void*)resblock_fused_kernel<128>, RB_LDS_MAX);
         set((const void*)conv_pool_kernel<16, 16>, CP_LDS_MAX);
         set((const void*)conv_pool_kernel<16, 32>, CP_LDS_MAX);
         set((const void*)conv_pool_kernel<32, 32>, CP_LDS_MAX);
@@ -588,10 +591,6 @@ inline seed_status_t bf16_create(const Plan& p, const float* d_w, Bf16State** ou
         set((const void*)first_pool_kernel<64, 16>, FirstPoolCfg<64, 16>::LDS_MAX);
         BF_TRY(e);
     }
-    BF_TRY(hipFuncSetAttribute((const void*)resblock_fused_kernel<16>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)RB_LDS_MAX));
-    BF_TRY(hipFuncSetAttribute((const void*)resblock_fused_kernel<32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)RB_LDS_MAX));
-    BF_TRY(hipFuncSetAttribute((const void*)resblock_fused_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)RB_LDS_MAX));
-    BF_TRY(hipFuncSetAttribute((const void*)resblock_fused_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)RB_LDS_MAX));
     if (s->stack_fused) {
         BF_TRY(hipFuncSetAttribute((const void*)r2d2_torso_bf16_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, r2d2::LDS_BYTES));
         BF_TRY(hipFuncSetAttribute((const void*)r2d2_torso_bf16_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, r2d2::LDS_BYTES));
