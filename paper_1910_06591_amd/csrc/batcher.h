@@ -290,7 +290,7 @@ extern "C" seed_status_t seed_batcher_add_many(seed_batcher_t* b, int32_t n, con
         const int32_t i0 = t * per, i1 = std::min(ok, i0 + per);
         memcpy(s.obs + (size_t)(first + i0) * b->frame, obs_host + (size_t)i0 * b->frame, (size_t)(i1 - i0) * b->frame);
         copied[t].store(1, std::memory_order_release);
-        if (s.open || sent != SEED_OK || std::this_thread::get_id() != caller) return;
+        if (s.open || std::this_thread::get_id() != caller || sent != SEED_OK) return;      // (`front` and `sent` are the caller's)
         while (front < pieces && copied[front].load(std::memory_order_acquire)) ++front;
         sent = batcher_send(b, s, first + std::min(ok, front * per), BATCHER_SEND_BYTES);
     };

@@ -25,6 +25,8 @@
 // the epilogues between them 8 K of vector instructions that no MFMA covers, because all eight wavefronts pass them together.
 // Random data also lowers the clock: the same launches on zeros take 7 - 17 % less.
 #pragma once
+#include <algorithm>
+
 #include "resnet_strip.h"
 
 namespace seedinf {
