@@ -13,16 +13,17 @@
 // that is stored.  Workgroups are persistent, and the next strip's pixels arrive beside the map (asynchronous loads, as
 // they lie in memory) from the last convolution's end on.
 //
-// Measured, 1024 images, us, one launch against strips with x in memory: 32 channels on 36 x 48 (two strips of 18 rows)
-// 282 -> 165, on 27 x 36 115 -> 98, on 14 x 18 47 -> 29; 16 channels on 54 x 72 279 -> 146; 64 channels on 18 x 24 166 -> 137, on 9 x
-// 12 47 -> 38; 128 on 9 x 12 149 -> 129.  In the order found: everything the epilogues and the x phase know about a pixel
-// worked out once per strip shape, not per phase (a wavefront's two vector instructions per pixel and phase are its time: 32
-// channels on 36 x 48 184 -> 171); a lane's feature tiles one run of eight channels, so that a cell is one 16-byte access;
+// Measured, 1024 images, us, one launch against the strip kernels with x in memory as they are now: 32 channels on 36 x 48 (two
+// strips of 18 rows) 200 -> 144; 16 channels on 54 x 72 224 -> 124; 64 channels on 18 x 24 135 -> 109, on 9 x 12 55 -> 33; 128 on 9 x
+// 12 133 -> 106.  In the order found (32 channels on 36 x 48): everything the epilogues and the x phase know about a pixel
+// worked out once per strip shape, not per phase (a wavefront's two vector instructions per pixel and phase are its time:
+// 184 -> 171 us); a lane's feature tiles one run of eight channels, so that a cell is one 16-byte access;
 // fragments of all of a wavefront's tiles requested ahead (ring of 9 instead of 3); the next convolution's first weights
 // requested before the epilogue; loops written out, not indexed by the block (a pointer picked at run time makes its
 // loads flat ones, which count as LDS traffic too: 171 -> 165).
-// What bounds it: of about 40 K cycles per strip (32 channels on 36 x 48) the four convolutions are 28 K for 20 K of MFMAs,
-// the epilogues between them 8 K of vector instructions that no MFMA covers, because all eight wavefronts pass them together.
+// What bounds it (32 channels on 36 x 48): by counters the matrix cores are busy 45 % of the time (55 % at 64 channels, 68 % at 128);
+// the rest is mostly the epilogues between the convolutions, vector instructions that no MFMA covers because all eight
+// wavefronts pass them together, and the fragments' first trip behind each barrier.
 // Random data also lowers the clock: the same launches on zeros take 7 - 17 % less.
 #pragma once
 #include <algorithm>
