@@ -307,7 +307,7 @@ extern "C" seed_status_t seed_batcher_submit(seed_batcher_t* b, const float* uni
     auto fail = [&](seed_status_t st, const char* m) { b->err = m; return st; };
     seed_batcher::Set& s = b->set[b->fill];
     const seed_arch_t& a = b->h->plan.arch;
-    const int R = s.rows;
+    const int R = s.in_flight ? 0 : s.rows;                  // (in flight: the rows are the unfinished batch's)
     if (R == 0) return fail(SEED_ERR_INVALID_ARG, "the batch is empty");
     if (a.select == SEED_SELECT_GUMBEL && !uniforms_host) return fail(SEED_ERR_INVALID_ARG, "Gumbel-max selection needs uniforms");
     if (a.select == SEED_SELECT_GREEDY && uniforms_host) return fail(SEED_ERR_INVALID_ARG, "greedy selection takes no uniforms (pass NULL)");

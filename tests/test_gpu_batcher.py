@@ -115,3 +115,30 @@ def test_batcher_feed_forward_and_errors(orc):
         bat.wait(t + 7)                                           # unknown ticket
     bat.close()
     net.close()
+
+
+def test_empty_submit_while_both_sets_are_in_flight():
+    """A third submit without rows is refused and leaves the two batches in flight as they are: both tickets can be
+    collected, their actions and the actors' states are those of a batcher that was never asked."""
+    cfg = dict(wl.CONFIGS["C3"], index=54)
+    w = wl.make_weights(cfg, bf16_representable=True)
+    net = seedinf.SeedInfer(seedinf.make_arch(cfg, max_batch=6), w)
+    frames, rew, dn = wl.make_obs(cfg, 12, seed=31), np.linspace(-1, 1, 6, dtype=np.float32), np.zeros(6, np.uint8)
+    un = [wl.make_uniforms(cfg, 6, seed=k) for k in range(3)]
+    actors = np.arange(6, dtype=np.int32)
+    results = []
+    for asked in (False, True):
+        bat = seedinf.Batcher(net, 6)
+        tickets = []
+        for k in range(2):
+            bat.add_many(actors, frames[6 * k:6 * k + 6], rew, dn)
+            tickets.append(bat.submit(un[k]))
+        if asked:
+            with pytest.raises(seedinf.SeedError, match="empty"):
+                bat.submit(un[2])
+        got = [bat.wait(t) for t in tickets]
+        results.append((*got, *(x for a in range(6) for x in bat.read_state(a))))
+        bat.close()
+    for plain, asked in zip(*results):
+        np.testing.assert_array_equal(plain, asked)
+    net.close()
