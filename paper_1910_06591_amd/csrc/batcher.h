@@ -76,7 +76,8 @@ struct seed_batcher {
         int32_t* d_prev_action = nullptr; int32_t* d_actions = nullptr;
         float* d_h_in = nullptr; float* d_c_in = nullptr; float* d_h_out = nullptr; float* d_c_out = nullptr;
         float* d_logits = nullptr; float* d_value = nullptr;
-        hipEvent_t ready[BATCHER_CHUNKS] = {};   // the frames of the first k + 1 chunks have arrived; the last in use: all
+        hipEvent_t ready[BATCHER_CHUNKS] = {};   // the frames of the first there[k] rows have arrived; the last in use: all
+        int there[BATCHER_CHUNKS] = {};
         hipEvent_t finished = nullptr;
         int chunks = 0;                 // of `ready` recorded
         int rows = 0;                   // rows added to the batch being filled
@@ -195,22 +196,34 @@ extern "C" const char* seed_batcher_last_error(const seed_batcher_t* b) { return
 extern "C" void* seed_batcher_stream(seed_batcher_t* b) { return b ? (void*)b->comp_s : nullptr; }
 
 // Frames travel while later rows are still being added, in transfers of at least this many bytes (each costs about 9 us more;
-// a round of 512 DMLab frames is 10.6 MB, 193 us of PCIe in one transfer).  A whole round, frames in host memory to
-// actions in host memory: 433 -> 359 us; the copy to pinned memory, 260 us here where neither side of it is in cache, is what is left
-// to overlap with, and stores past the caches or items handed out to whichever thread is awake made it no shorter.
+// a round of 512 DMLab frames is 10.6 MB, 193 us of PCIe in one transfer).
 constexpr size_t BATCHER_SEND_BYTES = (size_t)1 << 21;
 
-// Starts the transfer of the filled rows [sent, rows) if they are worth one.
-static seed_status_t batcher_send(seed_batcher* b, seed_batcher::Set& s, int rows, size_t at_least)
+// Starts the transfer of the filled rows [sent, rows).
+static seed_status_t batcher_copy(seed_batcher* b, seed_batcher::Set& s, int rows)
 {
-    const size_t bytes = (size_t)(rows - s.sent) * b->frame;
-    if (bytes == 0 || bytes < at_least) return SEED_OK;
-    const size_t from = (size_t)s.sent * b->frame;
-    B_TRY(b, hipMemcpyAsync(s.d_obs + from, s.obs + from, bytes, hipMemcpyHostToDevice, b->copy_s));
+    const size_t from = (size_t)s.sent * b->frame, bytes = (size_t)(rows - s.sent) * b->frame;
+    if (bytes) B_TRY(b, hipMemcpyAsync(s.d_obs + from, s.obs + from, bytes, hipMemcpyHostToDevice, b->copy_s));
     s.sent = rows;
-    // (the last event is for all rows, at submit)
-    while (s.chunks < BATCHER_CHUNKS - 1 && s.sent >= (s.chunks + 1) * b->chunk) B_TRY(b, hipEventRecord(s.ready[s.chunks++], b->copy_s));
     return SEED_OK;
+}
+
+// Event k: the leading `rows` rows have arrived once what was sent so far has.
+static seed_status_t batcher_mark(seed_batcher* b, seed_batcher::Set& s, int k, int rows)
+{
+    B_TRY(b, hipEventRecord(s.ready[k], b->copy_s));
+    s.there[k] = rows;
+    return SEED_OK;
+}
+
+// A transfer before the submit, if the rows are worth one, and an event for the whole chunks that it completes (the last
+// event is the submit's).
+static seed_status_t batcher_send(seed_batcher* b, seed_batcher::Set& s, int rows)
+{
+    if ((size_t)(rows - s.sent) * b->frame < BATCHER_SEND_BYTES) return SEED_OK;
+    if (seed_status_t st = batcher_copy(b, s, rows); st != SEED_OK) return st;
+    const int whole = rows / b->chunk * b->chunk, marked = s.chunks ? s.there[s.chunks - 1] : 0;
+    return whole > marked && s.chunks < BATCHER_CHUNKS - 1 ? batcher_mark(b, s, s.chunks++, whole) : SEED_OK;
 }
 
 static seed_status_t batcher_row(seed_batcher* b, int32_t actor, float prev_reward, uint8_t done, uint8_t** obs_slot)
@@ -257,7 +270,7 @@ extern "C" seed_status_t seed_batcher_add(seed_batcher_t* b, int32_t actor, cons
     if (st != SEED_OK) return st;
     memcpy(slot, obs_host, b->frame);
     seed_batcher::Set& s = b->set[b->fill];
-    return s.open ? SEED_OK : batcher_send(b, s, s.rows, BATCHER_SEND_BYTES);
+    return s.open ? SEED_OK : batcher_send(b, s, s.rows);
 }
 
 extern "C" seed_status_t seed_batcher_add_many(seed_batcher_t* b, int32_t n, const int32_t* actors, const uint8_t* obs_host,
@@ -293,11 +306,11 @@ extern "C" seed_status_t seed_batcher_add_many(seed_batcher_t* b, int32_t n, con
         copied[t].store(1, std::memory_order_release);
         if (s.open || std::this_thread::get_id() != caller || sent != SEED_OK) return;      // (`front` and `sent` are the caller's)
         while (front < pieces && copied[front].load(std::memory_order_acquire)) ++front;
-        sent = batcher_send(b, s, first + std::min(ok, front * per), BATCHER_SEND_BYTES);
+        sent = batcher_send(b, s, first + std::min(ok, front * per));
     };
     if (pool) pool->run(pieces, copy);
     else for (int t = 0; t < pieces; ++t) copy(t);
-    if (!s.open && sent == SEED_OK) sent = batcher_send(b, s, s.rows, BATCHER_SEND_BYTES);
+    if (!s.open && sent == SEED_OK) sent = batcher_send(b, s, s.rows);
     return st != SEED_OK ? st : sent;
 }
 
@@ -321,13 +334,14 @@ extern "C" seed_status_t seed_batcher_submit(seed_batcher_t* b, const float* uni
     }
     // the frames not yet sent, on the copy stream (overlaps the previous batch's compute); beside them, on the compute
     // stream, the rows' states and small inputs; the step waits for both
-    hipStream_t cs = b->copy_s, ks = b->comp_s;
+    hipStream_t ks = b->comp_s;
     const bool rec = Hn > 0;
-    if (seed_status_t st = batcher_send(b, s, R, 1); st != SEED_OK) return st;
-    // one more event for the rows behind the last whole chunk, if there are any
+    if (seed_status_t st = batcher_copy(b, s, R); st != SEED_OK) return st;
+    // one more event for the rows behind the last one's, if there are any
     int events = s.chunks;
-    if (R > events * b->chunk) B_TRY(b, hipEventRecord(s.ready[events++], cs));
-    const FrameArrival arrival{b->chunk, events, s.ready};
+    if (events == 0 || s.there[events - 1] < R)
+        if (seed_status_t st = batcher_mark(b, s, events++, R); st != SEED_OK) return st;
+    const FrameArrival arrival{events, s.there, s.ready};
     BatchRows br{};
     br.actor = s.actor; br.reward = s.reward; br.done = s.done;
     br.uniforms = uniforms_host ? s.uniforms : nullptr;

@@ -338,8 +338,8 @@ static void launch_heads(hipStream_t s, const HeadsArgs& ha)
     else launch_heads_p<64>(s, ha);
 }
 
-// Frames that are still on their way to the device: rows k * chunk .. are there when ready[k] has passed, the rest with ready[n - 1].
-struct FrameArrival { int chunk, n; const hipEvent_t* ready; };
+// Frames that are still on their way to the device: the first rows[k] are there when ready[k] has passed, all with the last of n.
+struct FrameArrival { int n; const int* rows; const hipEvent_t* ready; };
 
 // Torso and linear layer over B rows (rows of the handle's linear-layer buffers).
 static seed_status_t run_torso_fc(seed_infer* h, hipStream_t s, int B, const uint8_t* obs, const FrameArrival* arrival = nullptr)
@@ -348,10 +348,9 @@ static seed_status_t run_torso_fc(seed_infer* h, hipStream_t s, int B, const uin
     if (arrival && p.arch.precision == SEED_PRECISION_BF16 && h->ev.empty()) {
         // the torso of the rows that are there runs beside the transfer of the others
         const size_t frame = (size_t)p.arch.obs_h * p.arch.obs_w * p.arch.obs_c;
-        for (int k = 0; k < arrival->n; ++k) {
-            const int r0 = k * arrival->chunk, r1 = k + 1 < arrival->n ? r0 + arrival->chunk : B;
+        for (int k = 0, r0 = 0; k < arrival->n; r0 = arrival->rows[k++]) {
             HIP_TRY(h, hipStreamWaitEvent(s, arrival->ready[k], 0));
-            if (r1 > r0) bf16_torso(h->bf, p, h->d_w, s, r0, r1 - r0, obs + r0 * frame);
+            bf16_torso(h->bf, p, h->d_w, s, r0, arrival->rows[k] - r0, obs + r0 * frame);
         }
         return bf16_fc(h->bf, p, s, B, h->err);
     }

@@ -7,12 +7,24 @@ from paper_1910_06591_amd import seedinf, workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("name", ["C3", "C4"])
-def test_rounds_equal_steps(name):
+NETS = {
+    "C2": dict(wl.CONFIGS["C2"], index=61),               # greedy, with epsilon-greedy exploration
+    "C3": dict(wl.CONFIGS["C3"], index=61),
+    "C4": dict(wl.CONFIGS["C4"], index=61),
+    # layer by layer; 13 x 15 x 16 features: rows padded to whole chunks of 32
+    "layers": dict(wl.CONFIGS["C3"], label="50x60x3, sections 16 16", obs_h=50, obs_w=60, sections=[16, 16], index=61),
+}
+
+
+@pytest.mark.parametrize("depth", [1, 2])
+@pytest.mark.parametrize("name", ["C2", "C3", "C4", "layers"])
+def test_rounds_equal_steps(name, depth):
     """Rounds of whole chunks, ragged ones, rows added one by one and in groups, and reserved rows written only before the
-    submit (which hold the frames back), two in flight: actions and states are those of seed_infer_step on the same rows."""
+    submit (which hold the frames back): actions and states are those of seed_infer_step on the same rows.  One round
+    at a time the frames travel while rows are added and the torso starts chunk by chunk (700 rows: 512, then
+    188); with a batch in flight they go at the submit."""
     import torch
-    cfg = dict(wl.CONFIGS[name], index=61)
+    cfg = NETS[name]
     n, A, Hn = 700, cfg["num_actions"], cfg["lstm_units"]
     rng = np.random.default_rng(5)
     weights = wl.make_weights(cfg, bf16_representable=True)
@@ -28,7 +40,7 @@ def test_rounds_equal_steps(name):
         idx = torch.from_numpy(actors).long().cuda()
         got = bat.wait(ticket)
         rec = dict(prev_action=last[idx], prev_reward=args["rewards"], h_in=h[idx], c_in=c[idx], done=args["dones"]) if Hn else {}
-        out = ref.step(args["obs"], uniforms=args["uniforms"], **rec)
+        out = ref.step(args["obs"], **args["select"], **rec)
         np.testing.assert_array_equal(got, out["action"].cpu().numpy())
         last[idx] = out["action"]
         if Hn:
@@ -39,7 +51,10 @@ def test_rounds_equal_steps(name):
         actors = rng.permutation(n)[:rows].astype(np.int32)
         pick = rng.integers(0, n, rows)
         obs, rew, dn = frames[pick], rng.standard_normal(rows).astype(np.float32), (rng.random(rows) < 0.1).astype(np.uint8)
-        un = wl.make_uniforms(cfg, rows, seed=int(rng.integers(1 << 30)))
+        if cfg["select"] == 1:
+            select = dict(uniforms=wl.make_uniforms(cfg, rows, seed=int(rng.integers(1 << 30))))
+        else:
+            select = dict(epsilon=rng.random(rows, dtype=np.float32) * np.float32(0.5), explore_uniforms=rng.random((rows, 2), dtype=np.float32))
         print(f"{name} rows {rows} {plan}", flush=True)
         if plan == "one":
             for i in range(rows):
@@ -54,9 +69,10 @@ def test_rounds_equal_steps(name):
                 bat.add_many(actors[i0:i1], obs[i0:i1], rew[i0:i1], dn[i0:i1])
             for slot, i in slots:
                 slot[...] = obs[i]
-        args = dict(obs=torch.from_numpy(obs).cuda(), rewards=torch.from_numpy(rew).cuda(), dones=torch.from_numpy(dn).cuda(), uniforms=torch.from_numpy(un).cuda())
-        pending.append((bat.submit(un), actors, args))
-        if len(pending) == 2:
+        args = dict(obs=torch.from_numpy(obs).cuda(), rewards=torch.from_numpy(rew).cuda(), dones=torch.from_numpy(dn).cuda(),
+                    select={k: torch.from_numpy(v).cuda() for k, v in select.items()})
+        pending.append((bat.submit(**select), actors, args))
+        if len(pending) == depth:
             check(pending.pop(0))
     while pending:
         check(pending.pop(0))
