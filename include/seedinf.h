@@ -334,7 +334,8 @@ void seed_infer_destroy(seed_infer_t* handle);
  *   seed_batcher_submit  closes the batch (rows in the order they were added):
  *                        host->device copies of the frames on the copy stream
  *                        (the first of a large batch start while rows are
- *                        added, unless a row was reserved), and on the
+ *                        added, unless a row was reserved or another batch is
+ *                        in flight), and on the
  *                        compute stream: gather the rows' states by actor,
  *                        seed_infer_step_ext (done flags reset states; epsilon
  *                        optional; the torso of leading rows may start before

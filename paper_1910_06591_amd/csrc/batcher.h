@@ -196,7 +196,9 @@ extern "C" const char* seed_batcher_last_error(const seed_batcher_t* b) { return
 extern "C" void* seed_batcher_stream(seed_batcher_t* b) { return b ? (void*)b->comp_s : nullptr; }
 
 // Frames travel while later rows are still being added, in transfers of at least this many bytes (each costs about 9 us more;
-// a round of 512 DMLab frames is 10.6 MB, 193 us of PCIe in one transfer).
+// a round of 512 DMLab frames is 10.6 MB, 193 us of PCIe in one transfer), unless another batch is in flight: then the link is busy
+// with that batch's frames or the device with its step, cutting this one's frames up only adds the 9 us, and they
+// go in one transfer at the submit.
 constexpr size_t BATCHER_SEND_BYTES = (size_t)1 << 21;
 
 // Starts the transfer of the filled rows [sent, rows).
@@ -220,7 +222,7 @@ static seed_status_t batcher_mark(seed_batcher* b, seed_batcher::Set& s, int k, 
 // event is the submit's).
 static seed_status_t batcher_send(seed_batcher* b, seed_batcher::Set& s, int rows)
 {
-    if ((size_t)(rows - s.sent) * b->frame < BATCHER_SEND_BYTES) return SEED_OK;
+    if (b->set[b->fill ^ 1].in_flight || (size_t)(rows - s.sent) * b->frame < BATCHER_SEND_BYTES) return SEED_OK;
     if (seed_status_t st = batcher_copy(b, s, rows); st != SEED_OK) return st;
     const int whole = rows / b->chunk * b->chunk, marked = s.chunks ? s.there[s.chunks - 1] : 0;
     return whole > marked && s.chunks < BATCHER_CHUNKS - 1 ? batcher_mark(b, s, s.chunks++, whole) : SEED_OK;
