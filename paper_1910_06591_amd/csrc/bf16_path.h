@@ -688,9 +688,11 @@ inline void launch_gemm(hipStream_t st, const GemmArgs& g, int tile_groups, int 
         if constexpr (EPI == EPI_LSTM) {
             // where blocks of 16 rows would be two to a compute unit, which then pulls a gate group's weights twice, and
             // blocks of 32 rows one: those, with K over eight wavefronts (Atari agent's step at 144 rows 40.9 -> 38.6 us,
-            // 200 41.6 -> 39.9, 256 40.1 -> 38.8; 256 units at 272 to 512 rows within 0.5 %)
+            // 200 41.6 -> 39.9, 256 40.1 -> 38.8), where those have work: with 24 chunks of K the step gains 1 - 4.6 % (256
+            // inputs and 512 units, 384 and 384, 512 and 256), with 16, two to a wavefront, the second reduction costs more
+            // (the DMLab agent's step at 257 rows 75.3 -> 75.9 us, 512 76.0 -> 76.5)
             const long b32 = (long)((g.rows + 31) / 32) * tile_groups;
-            if ((long)((g.rows + 15) / 16) * tile_groups > n_cu && b32 <= n_cu) {
+            if (kct >= 24 && (long)((g.rows + 15) / 16) * tile_groups > n_cu && b32 <= n_cu) {
                 hipLaunchKernelGGL((gemm_bf16_splitk_kernel<2, EPI, 8>), dim3((g.rows + 31) / 32, tile_groups), dim3(512),
                                    4 * 2 * 4 * 64 * sizeof(floatx4), st, g);
                 return;
