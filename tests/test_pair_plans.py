@@ -51,6 +51,30 @@ def test_strips_fit_lds_and_the_registers(tmp_path):
     assert sum(line != "-" for line in out) > len(out) // 2
 
 
+def test_stacks_go_by_whole_rounds(tmp_path):
+    """Images per workgroup on 256 compute units: one while a round holds the batch, then as many as keep the rounds few."""
+    main = r"""
+int main()
+{
+    int H, W, C, B;
+    while (scanf("%d %d %d %d", &H, &W, &C, &B) == 4)
+        strip_by_width(C, [&](auto cc) {
+            PairPlan p;
+            p.choose<decltype(cc)::value>(H, W);
+            printf("%d\n", p.stack<decltype(cc)::value>(B, H, W, 256));
+            return true;
+        });
+}
+"""
+    batches = (1, 256, 257, 511, 512, 513, 768, 769, 1000, 1024)
+    want = {(9, 12, 16): (1, 1, 2, 2, 2, 3, 3, 4, 4, 4), (9, 12, 64): (1, 1, 2, 2, 2, 3, 3, 4, 4, 4),
+            (18, 24, 32): (1, 1, 2, 2, 2, 1, 1, 2, 2, 2), (13, 13, 64): (1, 1, 2, 2, 2, 3, 3, 2, 2, 2),
+            (18, 24, 64): (1,) * 10, (36, 48, 32): (1,) * 10}                # one fits; strips
+    cases = [(*m, b) for m in want for b in batches]
+    out = host_program.build(tmp_path, main)([" ".join(map(str, c)) for c in cases])
+    assert dict(zip(cases, map(int, out))) == {(*m, b): s for m, stacks in want.items() for b, s in zip(batches, stacks)}
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("frame,sections,batch", [
     ((120, 192, 3), (16,), 300),          # four strips, inner ones with halos on both sides
