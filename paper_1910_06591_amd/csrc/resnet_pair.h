@@ -34,6 +34,7 @@ namespace seedinf {
 
 constexpr int RP_THREADS = 512;
 constexpr size_t RP_LDS_MAX = 160 * 1024;                   // one workgroup per compute unit
+constexpr int RP_MAX_STACK = 4;                             // images a workgroup stacks
 
 template <int C>
 struct PairCfg {
@@ -99,7 +100,7 @@ struct PairPlan {
         if (strips != 1) return 1;
         int images = 1;
         long best = 0;
-        for (int s = 1; s <= RS_MAX_STACK && (s == 1 || K::fits(s * (H + 1) - 1, s * H * W, W)); ++s) {
+        for (int s = 1; s <= RP_MAX_STACK && (s == 1 || K::fits(s * (H + 1) - 1, s * H * W, W)); ++s) {
             const int workgroups = (B + s - 1) / s, tiles = (K::S::tiles(s * (H + 1) - 1, W) + K::S::NPG - 1) / K::S::NPG;
             const long cost = (long)((workgroups + n_cu - 1) / n_cu) * (K::TPW / 3 + tiles);
             if (s == 1 || cost < best) { best = cost; images = s; }
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(RP_THREADS, 2) void resblock_pair_kernel(PairArgs p
                     int y = t.m0 + 1 + tw.r, im = 0;         // row and image of the stack
                     if (stacked) {
 #pragma unroll
-                        for (int k = 1; k < RS_MAX_STACK; ++k)
+                        for (int k = 1; k < RP_MAX_STACK; ++k)
                             if (y >= Hp) { y -= Hp; ++im; }
                     }
                     // (a stack's separating rows have y = H)

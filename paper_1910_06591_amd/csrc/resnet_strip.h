@@ -35,7 +35,6 @@ namespace seedinf {
 
 constexpr int RS_THREADS = 512;
 constexpr size_t RS_LDS_MAX = 80 * 1024;                    // two workgroups per compute unit
-constexpr int RS_MAX_STACK = 4;                             // images a workgroup stacks (resnet_pair.h)
 
 template <int C>
 struct StripCfg {
@@ -272,20 +271,6 @@ struct StripBlockPlan {
         return best >= 0;
     }
     static int conv_a_rows(int th, int ns) { return ns == 1 ? th : (ns == 2 ? th + 1 : th + 2); }
-    // Images that a workgroup of two per compute unit could stack.  (Whole images run in resnet_pair.h's launch, which stacks by
-    // its own plan; this one is what the plans' test measures the strip maps' LDS with.)
-    template <int C>
-    int stack(int B, int H, int W, int n_cu) const
-    {
-        if (strips != 1) return 1;
-        int images = 1;
-        for (int s = 2; s <= RS_MAX_STACK; ++s) {
-            const int rows = s * (H + 1) - 1;
-            if ((B + s - 1) / s < 2 * n_cu || !StripCfg<C>::fits(rows, rows + 2, W)) break;
-            images = s;
-        }
-        return images;
-    }
 };
 
 // FIRST: bf16 in, fp32 out; else fp32 in, bf16 out.

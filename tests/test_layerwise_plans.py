@@ -9,7 +9,7 @@ from tests import host_program
 MAIN = r"""
 // the strip plans of a section: per plan LDS bytes of its largest map and of the launch, the most pixel tiles of a wavefront
 // and the accumulators' limit, and whether the strips cover every row once
-static void strips(const Section& sec, int rows)
+static void strips(const Section& sec)
 {
     const int H = sec.PH, W = sec.PW, C = sec.conv0.Cout;
     strip_by_width(C, [&](auto cc) {
@@ -17,16 +17,15 @@ static void strips(const Section& sec, int rows)
         auto tiles = [&](int r, int w) { return (K::tiles(r, w) + K::NPG - 1) / K::NPG; };
         StripBlockPlan b;
         if (b.choose<decltype(cc)::value>(H, W)) {
-            const int stack = b.stack<decltype(cc)::value>(rows, H, W, 256);
             int lds_rows = 0, most = 0;
             for (int s = 0; s < b.strips; ++s) {
                 const int y0 = s * b.TH, ye = std::min(y0 + b.TH, H);
-                const int ra = stack > 1 ? stack * (H + 1) - 1 : std::min(ye + 1, H) - std::max(y0 - 1, 0);
+                const int ra = std::min(ye + 1, H) - std::max(y0 - 1, 0);
                 lds_rows = std::max(lds_rows, ra + 2);
                 most = std::max(most, tiles(ra, W));
             }
-            const bool cover = (long)b.TH * b.strips >= H && (long)b.TH * (b.strips - 1) < H && (stack == 1 || b.strips == 1);
-            const size_t asked = K::lds_bytes((stack > 1 ? stack * (H + 1) - 1 : b.conv_a_rows(b.TH, b.strips)) + 2, W);
+            const bool cover = (long)b.TH * b.strips >= H && (long)b.TH * (b.strips - 1) < H;
+            const size_t asked = K::lds_bytes(b.conv_a_rows(b.TH, b.strips) + 2, W);
             printf("%zu %zu %d %d %d ", K::lds_bytes(lds_rows, W), asked, most, K::TPW, cover && asked <= RS_LDS_MAX);
         }
         const ConvLayer& c = sec.conv0;
@@ -55,7 +54,7 @@ int main()
         for (int& s : sections) if (scanf("%d", &s) != 1) return 1;
         const Plan p = resnet(h, w, c, sections);
         if (what[0] == 's') {
-            strips(p.sections[0], rows);
+            strips(p.sections[0]);
         } else if (what[0] == 'b') {
             const LwLayout l = lw_layout(p, rows);
             printf("%zu %zu %zu %zu %zu\n", l.c0, l.u, l.r, l.x, l.end);
@@ -141,7 +140,7 @@ def test_strips_are_chosen_where_they_are_faster(program):
 
 def test_strips_fit_lds_and_the_accumulators(program):
     """A strip's map fits the LDS a workgroup asks for and its pixel tiles the accumulators (a wavefront with more would
-    drop them), for every map, ragged strips and stacks of images, as the kernels work their rows out."""
+    drop them), for every map and ragged strips, as the kernels work their rows out."""
     rng = random.Random(2)
     maps = [(1, 1), (2, 3), (9, 12), (17, 11), (36, 48), (54, 72), (2048, 2), (2, 500), (1, 1020), (300, 250)]
     maps += [(rng.randint(1, 200), rng.randint(1, 300)) for _ in range(300)]
