@@ -818,16 +818,22 @@ inline bool first_rows_by_layer(const LwLayerDev& d, const ConvLayer& c, F go)
     }
 }
 
-// The first layer with its pooling to x as bf16, pooled down the rows (resnet_rows.h): false, and nothing launched, where
-// first_pool_kernel is the faster one.  With strips of one pooled row a third of the convolution rows are computed twice (16
+// Whether the first layer pooled down its rows (resnet_rows.h) is faster than first_pool_kernel.  With strips of one pooled row a
+// third of the convolution rows are computed twice (16
 // planes on 20 x 300, 256 frames: 24 -> 28 us against 40 x 400 x 3, two rows, 68 -> 55); and a strip is a compute unit's half, so with few of
 // them the tiles use more of the chip (72 x 96 x 3 -> 64 channels, 288 strips: 9.0 -> 10.5, 576: 16.2 -> 14.3; -> 32, 256: 10.6 ->
 // 8.6, 128: 6.8 -> 7.8; 144 x 192 x 4 -> 64, 288: 8.7 -> 10.5).
+inline bool first_rows_preferred(const TileCut& cut, int B, int n_cu)
+{
+    return cut.h >= 2 && (long)B * cut.w >= 2L * n_cu;
+}
+
+// The first layer with its pooling to x as bf16, pooled down the rows: false, and nothing launched, where first_pool_kernel is the faster one.
 inline bool launch_first_rows(hipStream_t st, const LwLayerDev& d, const bf16x8* wp_conv, const float* d_w, const Section& sec,
                               const TileCut& cut, int B, int n_cu, const uint8_t* obs, __bf16* x)
 {
     const ConvLayer& c = sec.conv0;
-    if (cut.h < 2 || (long)B * cut.w < 2L * n_cu) return false;
+    if (!first_rows_preferred(cut, B, n_cu)) return false;
     return first_rows_by_layer(d, c, [&](auto cin, auto cout) {
         constexpr int CIN = decltype(cin)::value, COUT = decltype(cout)::value;
         FirstRowsArgs a{};

@@ -43,15 +43,29 @@ def test_strips_fit_lds_and_the_registers(tmp_path):
     assert sum(line != "-" for line in out) > len(out) // 3
 
 
+# frames, section, rows; the kernels at that many rows and at one (first layer, blocks)
+CASES = [
+    ((72, 96, 3), (32,), 131, "rows9 pair:2", "tile tile"),                # four strips
+    ((73, 100, 4), (64,), 60, "rows4 strip", "tile tile"),                 # odd height: a padded row above; a last column strip of four pixels
+    ((31, 44, 1), (16,), 600, "rows16 pair*3", "tile pair*1"),             # one strip, 22 pooled columns
+    ((57, 61, 16), (16,), 300, "rows10 pair*2", "tile tile"),              # odd both ways, 16 planes
+    ((50, 34, 16), (32,), 300, "rows13 pair*2", "tile pair*1"),
+    ((50, 60, 1), (32,), 300, "rows13 pair*1", "tile tile"),
+    ((60, 64, 4), (16,), 300, "rows15 pair*2", "tile tile"),
+    ((36, 60, 16), (64,), 300, "rows5 pair*1", "tile tile"),
+    ((20, 200, 3), (64,), 131, "rows2 strip", "tile strip"),               # the thinnest strips: two pooled rows
+    ((20, 240, 16), (16,), 300, "rows2 pair*1", "tile tile"),
+    ((2, 4, 3), (16,), 512, "tile pair*2", "tile pair*1"),                 # one pooled row: stays on the tile kernel
+    ((40, 400, 3), (32,), 64, "tile tile", "tile tile"),                   # blocks on tiles: so does the first layer
+]
+
+
+def test_cases_take_the_kernels_they_compare(tmp_path):
+    out = batch_bits.routes(tmp_path, [(b, f, s) for f, s, rows, *_ in CASES for b in (rows, 1)])
+    assert list(zip(out[::2], out[1::2])) == [(many, one) for *_, many, one in CASES]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("frame,sections,batch", [
-    ((72, 96, 3), (32,), 131),            # four strips
-    ((73, 100, 4), (64,), 60),            # odd height: a padded row above; a last column strip of four pixels
-    ((31, 44, 1), (16,), 600),            # one strip, 22 pooled columns
-    ((57, 61, 16), (16,), 300),           # odd both ways, 16 planes
-    ((50, 34, 16), (32,), 300),
-    ((2, 4, 3), (16,), 512),              # one pooled row: stays on the tile kernel
-    ((40, 400, 3), (32,), 64),            # strips of two pooled rows
-], ids=str)
+@pytest.mark.parametrize("frame,sections,batch", [c[:3] for c in CASES], ids=str)
 def test_pooling_down_the_rows_gives_the_tile_kernels_bits(orc, frame, sections, batch):
     batch_bits.check(orc, frame, sections, batch)

@@ -516,7 +516,7 @@ def test_largest_batch_the_interface_allows(orc, precision):
 
 
 @pytest.mark.parametrize("label,over", [
-    # 34 x 22 frames: maps of 17 x 11 and 9 x 6, whole images, stacked from 1024 rows on; every width
+    # 34 x 22 frames: maps of 17 x 11 and 9 x 6, whole images, stacked where a round does not hold the batch; every width
     ("16/32/64", dict(obs_h=34, obs_w=22, sections=[16, 32, 64])),
     ("32/64/128", dict(obs_h=34, obs_w=22, sections=[32, 64, 128])),
     ("64/128/128", dict(obs_h=33, obs_w=21, sections=[64, 128, 128])),
@@ -544,10 +544,10 @@ def test_bf16_strip_kernels_stack_small_images(orc, label, over):
     ("64/128/128", dict(obs_h=21, obs_w=33, sections=[64, 128, 128])),
 ])
 def test_bf16_stacks_of_four_images(orc, label, over):
-    """The largest stacks (two workgroups per compute unit left over, so from 2045 rows on): all four places of a
-    stack and a ragged last one of three images."""
+    """The largest stacks (one round of 256 workgroups, where four images fit): all four places of a stack and a ragged
+    last one of three images."""
     cfg = dict(wl.CONFIGS["C3"], label=f"stacks of four {label}", index=125, **over)
-    B, rows = 4 * 512 + 3, [0, 1, 2, 3, 2048, 2049, 2050]
+    B, rows = 4 * 256 - 1, [0, 1, 2, 3, 1020, 1021, 1022]
     weights, batch = wl.make_weights(cfg), wl.make_batch(cfg, B)
     net = seedinf.SeedInfer(seedinf.make_arch(cfg, max_batch=B), weights)
     net.step(**to_device(batch))
