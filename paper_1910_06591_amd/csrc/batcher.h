@@ -80,6 +80,7 @@ struct seed_batcher {
         int there[BATCHER_CHUNKS] = {};
         hipEvent_t finished = nullptr;
         int chunks = 0;                 // of `ready` recorded
+        int marked = 0;                 // rows sent when the last of them was
         int rows = 0;                   // rows added to the batch being filled
         int sent = 0;                   // leading rows whose frames are on their way to the device
         bool open = false;              // a row was reserved: its frame may be written until submit
@@ -215,6 +216,7 @@ static seed_status_t batcher_mark(seed_batcher* b, seed_batcher::Set& s, int k, 
 {
     B_TRY(b, hipEventRecord(s.ready[k], b->copy_s));
     s.there[k] = rows;
+    s.marked = s.sent;
     return SEED_OK;
 }
 
@@ -339,10 +341,10 @@ extern "C" seed_status_t seed_batcher_submit(seed_batcher_t* b, const float* uni
     hipStream_t ks = b->comp_s;
     const bool rec = Hn > 0;
     if (seed_status_t st = batcher_copy(b, s, R); st != SEED_OK) return st;
-    // one more event for the rows behind the last one's, if there are any
+    // one more event for the rows behind the last one's, unless that one came behind the last transfer
     int events = s.chunks;
-    if (events == 0 || s.there[events - 1] < R)
-        if (seed_status_t st = batcher_mark(b, s, events++, R); st != SEED_OK) return st;
+    if (events > 0 && s.marked == R) s.there[events - 1] = R;
+    else if (seed_status_t st = batcher_mark(b, s, events++, R); st != SEED_OK) return st;
     const FrameArrival arrival{events, s.there, s.ready};
     BatchRows br{};
     br.actor = s.actor; br.reward = s.reward; br.done = s.done;
