@@ -818,11 +818,12 @@ inline bool first_rows_by_layer(const LwLayerDev& d, const ConvLayer& c, F go)
     }
 }
 
-// Whether the first layer pooled down its rows (resnet_rows.h) is faster than first_pool_kernel.  With strips of one pooled row a
-// third of the convolution rows are computed twice (16
-// planes on 20 x 300, 256 frames: 24 -> 28 us against 40 x 400 x 3, two rows, 68 -> 55); and a strip is a compute unit's half, so with few of
-// them the tiles use more of the chip (72 x 96 x 3 -> 64 channels, 288 strips: 9.0 -> 10.5, 576: 16.2 -> 14.3; -> 32, 256: 10.6 ->
-// 8.6, 128: 6.8 -> 7.8; 144 x 192 x 4 -> 64, 288: 8.7 -> 10.5).
+// Whether the first layer pooled down its rows (resnet_rows.h) is faster than first_pool_kernel.  Both forced, us, tiles -> rows:
+// strips of one pooled row compute a third of the convolution rows twice (16 planes on 20 x 300, 256 frames 23.1 -> 27.1, 1024
+// 85 -> 95), of two a fifth (16 planes on 20 x 240, 300 frames 22.2 -> 20.9, 1024 68 -> 60; 20 x 200 x 3 -> 64 channels, 256
+// 34 -> 26); and a strip is a compute unit's half, so with few of them the tiles use more of the chip (72 x 96 x 3 -> 64
+// channels, 288 strips 10.1 -> 10.0, 576 15.9 -> 13.8; -> 32, 128 strips 7.3 -> 7.6, 256 10.6 -> 8.2, 512 18.3 -> 12.5): from
+// two strips per unit on every width measured is ahead.
 inline bool first_rows_preferred(const TileCut& cut, int B, int n_cu)
 {
     return cut.h >= 2 && (long)B * cut.w >= 2L * n_cu;
@@ -977,8 +978,9 @@ inline bool strip_by_width(int C, F go)
 // longer halo of the one launch multiplies.  Measured at 256 images, us, strips -> one launch at so many times the cells:
 // 16 channels on 60 x 96 83 -> 70 (1.30), 80 x 108 118 -> 118 (1.36), 50 x 150 105 -> 128 (1.63); 32 on 36 x 48 53 -> 39 (1.13),
 // 54 x 72 118 -> 122 (1.49), 45 x 60 88 -> 82 (1.5), 30 x 80 78 -> 89 (1.82); 64 on 18 x 24 42 -> 31 (1), 20 x 30 56 -> 51 (1.24),
-// 12 x 60 66 -> 65 (1.4), 27 x 36 83 -> 96 (1.54); 128 on 14 x 20 85 -> 64 (0.9), 10 x 30 89 -> 107 (1.45).  Alike at 1 to
-// 1024 images.
+// 12 x 60 66 -> 65 (1.4), 27 x 36 83 -> 96 (1.54); 128 on 14 x 20 85 -> 64 (0.9), 10 x 30 89 -> 107 (1.45).  The line does not
+// depend on the batch: below it the steps of twelve networks with strips in place of the one launch were slower or alike (1.00
+// to 1.56 times) at each of 23 counts from 32 to 1000 images, between whole rounds over the compute units too.
 inline bool pair_preferred(const PairPlan& pair, const StripBlockPlan& strip)
 {
     return 20 * pair.cells <= 27 * 2 * strip.cells;
@@ -1055,6 +1057,8 @@ inline LwSectionPlan plan_lw_section(const Section& sec, const LwLayerDev* d, bo
 //   145).
 // * One strip for one tile, and 128 channels (two launches instead of four), are faster at any batch (1 image: 64 channels on
 //   9 x 12 23 -> 18, 128 on 18 x 24 82 -> 61).
+// These are times of a launch of strips per block.  Where both blocks run in one launch strips are ahead from fewer images
+// on than these lines say (32 channels on 36 x 48, tiles -> one launch: 32 images 27 -> 23, 64 31 -> 26).
 inline bool strips_preferred(const LwSectionPlan& pl, int C, int B, int n_cu)
 {
     if (!pl.strips || !pl.block.h) return pl.strips;

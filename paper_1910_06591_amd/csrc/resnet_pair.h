@@ -13,15 +13,15 @@
 // that is stored.  Workgroups are persistent, and the next strip's pixels arrive beside the map (asynchronous loads, as
 // they lie in memory) from the last convolution's end on.
 //
-// Measured, 1024 images, us, one launch against the strip kernels with x in memory as they are now: 32 channels on 36 x 48 (two
-// strips of 18 rows) 200 -> 144; 16 channels on 54 x 72 224 -> 124; 64 channels on 18 x 24 135 -> 109, on 9 x 12 55 -> 33; 128 on 9 x
-// 12 133 -> 106.  In the order found (32 channels on 36 x 48): everything the epilogues and the x phase know about a pixel
+// Measured in one run, 1024 images, us, two launches of strips with x in memory -> this one: 32 channels on 36 x 48 (two strips of 18
+// rows) 233 -> 172; 16 channels on 54 x 72 233 -> 146; 64 channels on 18 x 24 161 -> 131, on 9 x 12 64 -> 40; 128 on 9 x 12 170 ->
+// 131 (in the agents' steps 156, 134, 118, 35 and 119).  In the order found (32 channels on 36 x 48): everything the epilogues and the x phase know about a pixel
 // worked out once per strip shape, not per phase (a wavefront's two vector instructions per pixel and phase are its time:
 // 184 -> 171 us); a lane's feature tiles one run of eight channels, so that a cell is one 16-byte access;
 // fragments of all of a wavefront's tiles requested ahead (ring of 9 instead of 3); the next convolution's first weights
 // requested before the epilogue; loops written out, not indexed by the block (a pointer picked at run time makes its
 // loads flat ones, which count as LDS traffic too: 171 -> 165).
-// What bounds it (32 channels on 36 x 48): by counters the matrix cores are busy 45 % of the time (55 % at 64 channels, 68 % at 128);
+// What bounds it (32 channels on 36 x 48): by counters the matrix cores are busy 46 % of the time (56 % at 64 channels, 68 % at 128);
 // the rest is mostly the epilogues between the convolutions, vector instructions that no MFMA covers because all eight
 // wavefronts pass them together, and the fragments' first trip behind each barrier.
 // Random data also lowers the clock: the same launches on zeros take 7 - 17 % less.

@@ -5,18 +5,19 @@
 // that holds a pixel holds the pixels below it too, so the vertical maximum of three convolution rows is one instruction
 // per value on the accumulators, one row shared with the next pooled row, and bias, scale, rounding and the trip to LDS
 // are paid on pooled rows only.  (The maximum commutes with all of those, so the bits are first_pool_kernel's, which pools
-// rounded values from a convolution tile in LDS.)  The horizontal maximum takes three reads per pooled pixel instead
+// rounded values from a convolution tile in LDS: of numbers below 2.6e36, the range of the packed maximum in both kernels.
+// Sums that are infinite or NaN, from weights of that size, are carried by neither.)  The horizontal maximum takes three reads per pooled pixel instead
 // of nine.  The weights stay in registers; workgroups are persistent, and the next strip's rows are on their way in
 // registers while this one's are convolved.
 //
 // K layout and packed weights as in first_pool_kernel: frames of up to 4 planes in cells of 4 channels, chunk kc = kernel rows
 // 2 kc and 2 kc + 1, two adjacent columns per lane group; 16 planes in two planes of 8 channels, k = tap * 16 + plane.
 //
-// Measured, 1024 frames, us, against first_pool_kernel: 72 x 96 x 3 -> 32 channels 113 -> 68, -> 64 204 -> 136, -> 16 64 -> 43; 16
-// planes -> 16 channels on 108 x 144 254 -> 201, on 90 x 120 176 -> 123 (one strip after the other without the
-// rows ahead 74, 150, 54, 213, 138).  By counters (72 x 96 x 3 -> 32; 108 x 144 x 16) the vector instructions are 0.44 times
-// the tile kernel's, LDS reads 0.3 / 0.5 times, and the wavefronts wait 38 / 58 % of the time, mostly for each other at
-// the two barriers of a strip: with 16 planes a strip is four pooled rows, four or five units of work to a wavefront.
+// Measured in one run, 1024 frames, us, against first_pool_kernel: 72 x 96 x 3 -> 32 channels 118 -> 72, -> 64 195 -> 143, -> 16
+// 64 -> 40; 16 planes -> 16 channels on 108 x 144 212 -> 185, on 90 x 120 156 -> 121 (in the agents' steps 65, 135, -, 172 and
+// 114; the rows ahead are worth 6 to 20 % of them).  By counters (72 x 96 x 3 -> 32; 108 x 144 x 16) the
+// wavefronts wait 40 / 58 % of the time, mostly for each other at the two barriers of a strip: with 16 planes a strip is
+// four pooled rows, four or five units of work to a wavefront.
 // (The same kernel on the 16-channel bf16 input of a later section is no faster than strip_pool_kernel, 88 -> 87.)
 #pragma once
 #include <cfloat>
