@@ -333,6 +333,10 @@ extern "C" seed_status_t seed_batcher_submit(seed_batcher_t* b, const float* uni
     if (a.select == SEED_SELECT_GUMBEL && !uniforms_host) return fail(SEED_ERR_INVALID_ARG, "Gumbel-max selection needs uniforms");
     if (a.select == SEED_SELECT_GREEDY && uniforms_host) return fail(SEED_ERR_INVALID_ARG, "greedy selection takes no uniforms (pass NULL)");
     if ((epsilon_host == nullptr) != (explore_host == nullptr)) return fail(SEED_ERR_INVALID_ARG, "epsilon and explore_uniforms must be given together");
+    // (before anything is enqueued: a copy or launch that went ahead would stand when the step is refused)
+    int dev = -1;
+    B_TRY(b, hipGetDevice(&dev));
+    if (dev != b->h->device) return fail(SEED_ERR_INVALID_ARG, "current HIP device differs from the handle's device");
     const size_t A = (size_t)b->A, Hn = (size_t)b->Hn;
     if (uniforms_host) memcpy(s.uniforms, uniforms_host, R * A * sizeof(float));
     if (epsilon_host) {
