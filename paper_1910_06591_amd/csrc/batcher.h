@@ -80,7 +80,7 @@ struct seed_batcher {
         int there[BATCHER_CHUNKS] = {};
         hipEvent_t finished = nullptr;
         int chunks = 0;                 // of `ready` recorded
-        int marked = 0;                 // rows sent when the last of them was
+        int marked = 0;                 // rows sent when the last of them was (before the submit)
         int rows = 0;                   // rows added to the batch being filled
         int sent = 0;                   // leading rows whose frames are on their way to the device
         bool open = false;              // a row was reserved: its frame may be written until submit
@@ -219,7 +219,6 @@ static seed_status_t batcher_mark(seed_batcher* b, seed_batcher::Set& s, int k, 
 {
     B_TRY(b, hipEventRecord(s.ready[k], b->copy_s));
     s.there[k] = rows;
-    s.marked = s.sent;
     return SEED_OK;
 }
 
@@ -230,7 +229,11 @@ static seed_status_t batcher_send(seed_batcher* b, seed_batcher::Set& s, int row
     if (b->set[b->fill ^ 1].in_flight || (size_t)(rows - s.sent) * b->frame < BATCHER_SEND_BYTES) return SEED_OK;
     if (seed_status_t st = batcher_copy(b, s, rows); st != SEED_OK) return st;
     const int whole = rows / b->chunk * b->chunk, marked = s.chunks ? s.there[s.chunks - 1] : 0;
-    return whole > marked && s.chunks < BATCHER_CHUNKS - 1 ? batcher_mark(b, s, s.chunks++, whole) : SEED_OK;
+    if (whole <= marked || s.chunks >= BATCHER_CHUNKS - 1) return SEED_OK;
+    if (seed_status_t st = batcher_mark(b, s, s.chunks, whole); st != SEED_OK) return st;
+    ++s.chunks;
+    s.marked = rows;
+    return SEED_OK;
 }
 
 static seed_status_t batcher_row(seed_batcher* b, int32_t actor, float prev_reward, uint8_t done, uint8_t** obs_slot)
